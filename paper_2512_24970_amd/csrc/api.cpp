@@ -51,6 +51,11 @@ struct DBuf {
         }
         bytes = b;
     }
+    // room for at least b bytes, contents not kept
+    void reserve(size_t b)
+    {
+        if (bytes < b) alloc(b);
+    }
     void release()
     {
         if (p) (void)hipFree(p);
@@ -1353,6 +1358,25 @@ void set_batch_impl(rbsog_ctx* c, int R, const rbsog_params* params, const int32
     HIP_OK(hipStreamSynchronize(c->stream));
 }
 
+// Whether this device's kernels can read the caller's `bytes` bytes of doubles
+// in place: an allocation of this device that holds them all.  Anything else
+// (another device's memory, a buffer the runtime cannot describe) is copied by
+// the runtime, which checks it.
+bool readable_here(const rbsog_ctx* c, const void* p, size_t bytes)
+{
+    if (reinterpret_cast<uintptr_t>(p) % sizeof(double) != 0) return false;
+    hipPointerAttribute_t at{};
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeDevice || at.device != c->device ||
+        hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const size_t off = (size_t)(static_cast<const char*>(p) - static_cast<const char*>(base));
+    return off <= size && bytes <= size - off;
+}
+
 void need_system(rbsog_ctx* c) { require(c->have_system, RBSOG_E_STATE, "no system set"); }
 
 }  // namespace
@@ -1548,19 +1572,31 @@ rbsog_status rbsog_set_positions(rbsog_ctx* ctx, const double* pos, int ptrs_on_
         require(pos != nullptr || ctx->n_user == 0, RBSOG_E_ARG, "pos is NULL");
         const int n = ctx->n_user;
         if (n == 0) return;
-        std::vector<double> hp(3 * (size_t)n);
-        if (ptrs_on_device)
-            HIP_OK(hipMemcpy(hp.data(), pos, sizeof(double) * hp.size(), hipMemcpyDeviceToHost));
-        else
-            std::memcpy(hp.data(), pos, sizeof(double) * hp.size());
-        for (double v : hp) require(std::isfinite(v), RBSOG_E_NONFINITE, "non-finite position");
-        ctx->export_tmp.alloc(sizeof(double) * hp.size());
-        HIP_OK(hipMemcpyAsync(ctx->export_tmp.p, hp.data(), sizeof(double) * hp.size(), hipMemcpyHostToDevice,
-                              ctx->stream));
-        launch_set_positions(ctx->plan, ctx->export_tmp.as<double>(), ctx->stream);
+        const size_t bytes = sizeof(double) * 3 * (size_t)n;
+        const double* src = pos;
+        if (ptrs_on_device && readable_here(ctx, pos, bytes)) {
+            // read in place; the caller's work on the default stream comes first
+            if (ctx->stream != nullptr) {
+                HIP_OK(hipEventRecord(ctx->ev_fork, nullptr));
+                HIP_OK(hipStreamWaitEvent(ctx->stream, ctx->ev_fork, 0));
+            }
+        } else {
+            ctx->export_tmp.reserve(bytes);
+            HIP_OK(hipMemcpy(ctx->export_tmp.p, pos, bytes,
+                             ptrs_on_device ? hipMemcpyDefault : hipMemcpyHostToDevice));
+            HIP_OK(hipStreamSynchronize(nullptr));  // a copy on the device returns early
+            src = ctx->export_tmp.as<double>();
+        }
+        launch_set_positions(ctx->plan, src, ctx->stream);
         HIP_OK(hipGetLastError());
+        const auto h = read_scalars(ctx);
+        if (h[0].badpos) {
+            launch_refuse_positions(ctx->plan, ctx->stream);
+            HIP_OK(hipStreamSynchronize(ctx->stream));
+            throw Error(RBSOG_E_NONFINITE, "non-finite position");
+        }
         bool stale = false;
-        for (const auto& h : read_scalars(ctx)) stale = stale || h.stale != 0;
+        for (const auto& x : h) stale = stale || x.stale != 0;
         ctx->stale = stale;
         ctx->forces_valid = false;
     });

@@ -139,6 +139,9 @@ struct DeviceScalars {
     int32_t rebuild;      // the lists are rebuilt in this step
     int32_t nonfinite;    // a non-finite position or force was produced
     int32_t stale;        // positions set by the caller moved an atom more than skin/2 from its build position
+    int32_t badpos;       // (system 0) the caller's new positions hold a non-finite value
+    int32_t pad0;
+    double prev_disp2;    // max_disp2 before the caller's new positions, put back when they are refused
     int64_t n_builds;     // list builds since the system was set
     int32_t max_core;     // largest core / candidate list seen (true sizes)
     int32_t max_cand;

@@ -2495,13 +2495,54 @@ __global__ void k_from_user(RB_ARGS, const int32_t* type, const double* pos, con
     s.inv[i] = i;
 }
 
-// New positions from the caller (user order), wrapped into the box; the
-// lists stay.  Raises the system's stale flag when an atom now sits more
-// than skin/2 from where it was at the last build, and keeps the largest
-// displacement.
-__global__ void k_set_pos(RB_ARGS, const double* pos)
+// Raise the device maximum of squared displacements (d2 >= 0, compared by bit
+// pattern) and a flag from a whole block.  Same-address atomics serialise: one
+// per block, and only where it would change the value (one per wavefront took
+// 366 us of a 10^6-ion call).
+__device__ inline void block_raise(double d2, bool flagged, unsigned long long* slot, int32_t* flag)
+{
+    __shared__ double red[kBlock / 64];
+    const bool any = __syncthreads_or(flagged);
+    double m = d2;
+    for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const double b = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+        const unsigned long long bits = (unsigned long long)__double_as_longlong(b);
+        if (bits > __atomic_load_n(slot, __ATOMIC_RELAXED)) atomicMax(slot, bits);
+        if (any && __atomic_load_n(flag, __ATOMIC_RELAXED) == 0) atomicOr(flag, 1);
+    }
+}
+
+// First pass over the caller's new positions (user order): raises badpos of
+// the batch if a value is not finite, and restarts each system's displacement
+// tracking (the old maximum is kept for a refusal).
+__global__ __launch_bounds__(kBlock) void k_check_pos(RB_ARGS, const double* pos, DeviceScalars* sc0)
 {
     RB_SYS(blockIdx.x)
+    const int i = lb * blockDim.x + threadIdx.x;
+    bool bad = false;
+    if (i < s.n) {
+        const size_t u = 3 * ((size_t)s.user_off + i);
+        bad = !finite3(pos[u], pos[u + 1], pos[u + 2]);
+    }
+    if (lb == 0 && threadIdx.x == 0) {
+        s.sc->prev_disp2 = s.sc->max_disp2;
+        s.sc->max_disp2 = 0.0;
+        s.sc->stale = 0;
+    }
+    if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(&sc0->badpos, 1);
+}
+
+// Second pass, skipped when a value was not finite: the positions wrapped
+// into the box; the lists stay.  Raises the system's stale flag when an atom
+// now sits more than skin/2 from where it was at the last build, and keeps
+// the largest displacement.
+__global__ __launch_bounds__(kBlock) void k_set_pos(RB_ARGS, const double* pos, const DeviceScalars* sc0)
+{
+    RB_SYS(blockIdx.x)
+    if (sc0->badpos) return;
     const int i = lb * blockDim.x + threadIdx.x;
     double d2 = 0.0;
     if (i < s.n) {
@@ -2517,17 +2558,15 @@ __global__ void k_set_pos(RB_ARGS, const double* pos)
         const double dz = min_image(z - s.zr[i], s.L[2], s.invL[2]);
         d2 = (dx * dx + dy * dy) + dz * dz;
     }
-    if (__ballot(d2 > s.half_skin2) && (threadIdx.x & 63) == 0) atomicOr(&s.sc->stale, 1);
-    double m = d2;
-    for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
-    if ((threadIdx.x & 63) == 0) atomicMax((unsigned long long*)&s.sc->max_disp2, (unsigned long long)__double_as_longlong(m));
+    block_raise(d2, d2 > s.half_skin2, (unsigned long long*)&s.sc->max_disp2, &s.sc->stale);
 }
 
-__global__ void k_clear_stale(DeviceScalars* sc, int R)
+// Refused positions: the displacement maximum of before, the mark lowered.
+__global__ void k_refuse_pos(DeviceScalars* sc, int R)
 {
     for (int r = threadIdx.x; r < R; r += blockDim.x) {
-        sc[r].stale = 0;
-        sc[r].max_disp2 = 0.0;
+        sc[r].max_disp2 = sc[r].prev_disp2;
+        sc[r].badpos = 0;
     }
 }
 
@@ -2871,9 +2910,12 @@ void launch_shell_samples(const Plan& P, int32_t* out, int32_t* n_out, hipStream
 
 void launch_set_positions(const Plan& P, const double* pos, hipStream_t st)
 {
-    k_clear_stale<<<1, 64, 0, st>>>(P.sc, P.R);
-    if (P.atoms.blocks > 0) k_set_pos<<<P.atoms.blocks, kBlock, 0, st>>>(RB_MAP(atoms), pos);
+    if (P.atoms.blocks <= 0) return;
+    k_check_pos<<<P.atoms.blocks, kBlock, 0, st>>>(RB_MAP(atoms), pos, P.sc);
+    k_set_pos<<<P.atoms.blocks, kBlock, 0, st>>>(RB_MAP(atoms), pos, P.sc);
 }
+
+void launch_refuse_positions(const Plan& P, hipStream_t st) { k_refuse_pos<<<1, 64, 0, st>>>(P.sc, P.R); }
 
 void launch_batch_ids(const Plan& P, int32_t* out, int32_t* n_out, hipStream_t st)
 {

@@ -294,8 +294,10 @@ void launch_batch_ids(const Plan& P, int32_t* out, int32_t* n_out, hipStream_t s
 void launch_shell_samples(const Plan& P, int32_t* out, int32_t* n_out, hipStream_t st);
 // positions from the caller's [N][3] array (user order, device); raises the
 // stale flag of a system with an atom more than skin/2 from its build
-// position and records the largest displacement
+// position and records the largest displacement; if a value is not finite it
+// only raises badpos of system 0, and launch_refuse_positions must follow
 void launch_set_positions(const Plan& P, const double* pos, hipStream_t st);
+void launch_refuse_positions(const Plan& P, hipStream_t st);
 void launch_from_user(const Plan& P, const int32_t* type, const double* pos, const double* vel, hipStream_t st);
 
 }  // namespace rbsog
