@@ -316,7 +316,8 @@ typedef struct {
     int32_t pair_block; /* atoms per workgroup of the pair kernel: 64, 128, 256 (default 256) */
     int32_t pair_ku;    /* neighbour positions fetched ahead per lane (shell-batch tile): 4, 8 (4) */
     int32_t rho_mpl;    /* k-modes per lane of the rho kernel (64 rho_mpl per workgroup): 1, 2 (1) */
-    int32_t kf_block;   /* atoms per workgroup of the k-space force kernel: 64, 128, 256 (256) */
+    int32_t kf_block;   /* threads per workgroup of the k-space force kernel: 64, 128, 256 (256); a
+                           small system takes more (its modes are split over wavefronts) */
     int32_t kf_aux;     /* 1: the k-space force follows rho on the second stream, beside the pair
                            kernel; 0: it runs after the pair kernel on the context's stream (1) */
 } rbsog_tuning;

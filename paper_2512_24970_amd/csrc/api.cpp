@@ -111,7 +111,7 @@ struct rbsog_ctx {
     int list_chunks = 8;
     std::vector<int> list_mode_r;    // staging class of each system (kListPerAtom: per-atom kernel)
     double row_slack = 1.25;
-    DBuf ktab, kcdf, kmodes, krho_part, krho, pair_part, vir_part, fin_part, kin_part, export_tmp, snap, sogk, neartab;
+    DBuf ktab, kcdf, kmodes, krho_part, krho, kf_part, pair_part, vir_part, fin_part, kin_part, export_tmp, snap, sogk, neartab;
     DBuf flux_part, at_ew, ufix;
     // mean-square displacement: [n_user][3] last positions, then [n_user][3]
     // unwrapped displacements; which systems have a marked origin
@@ -319,7 +319,13 @@ Plan one(const rbsog_ctx* c, int r)
     P.tune = c->plan.tune;
     P.atoms.blocks = blocks_for(s.n, kBlock);
     P.pair_atoms.blocks = blocks_for(s.n, P.tune.pair_block);
-    P.kf_atoms.blocks = blocks_for(s.n, P.tune.kf_block);
+    P.kf_threads = c->plan.kf_threads;
+    P.kf_split = c->plan.kf_split;
+    P.kf_sliced = c->plan.kf_sliced;
+    const bool grouped = k.kf_groups > 1;
+    const int kf_apb = P.kf_threads / std::max(1, k.kf_waves);  // atoms of a workgroup
+    P.kf_atoms.blocks = blocks_for(s.n, grouped ? P.kf_threads : kf_apb);
+    P.kf_part.blocks = grouped ? k.kf_groups * blocks_for(s.n, kf_apb) : 0;
     P.cells.blocks = s.n > 0 ? s.ncell : 0;
     P.list_cells.blocks = s.n > 0 ? s.ncell * s.list_parts : 0;
     P.atom1.blocks = s.n;
@@ -357,11 +363,18 @@ void plan_launches(rbsog_ctx* c)
     P.sc = c->scalars.as<DeviceScalars>();
     P.R = c->R;
     P.fin_grid = 1;
-    for (const auto& s : c->hs) P.fin_grid = std::max(P.fin_grid, fin_blocks(s.n));
-    constexpr int kShapes = 10 + kListPerAtom;
+    P.kf_threads = P.tune.kf_block;
+    P.kf_split = P.kf_sliced = false;
+    for (int r = 0; r < c->R; ++r) {
+        P.fin_grid = std::max(P.fin_grid, fin_blocks(c->hs[r].n, c->hk[r].n_modes));
+        P.kf_threads = std::max(P.kf_threads, 64 * c->hk[r].kf_waves);
+        if (c->hk[r].kf_slices > 1) P.kf_split = true;
+        if (c->hk[r].kf_waves > 1) P.kf_sliced = true;
+    }
+    constexpr int kShapes = 11 + kListPerAtom;
     Shape* dst[kShapes] = {&P.atoms, &P.pair_atoms, &P.kf_atoms, &P.cells, &P.atom1, &P.modes64, &P.rho,
                            &P.modes1, &P.rows64, &P.list_cells, &P.list_by_cap[0], &P.list_by_cap[1],
-                           &P.list_by_cap[2]};
+                           &P.list_by_cap[2], &P.kf_part};
     static_assert(kListPerAtom == 3, "one staging-class shape per capacity");
     std::vector<std::vector<int2>> m(kShapes + kMaxListChunks);
     const bool maps = c->R > 1;
@@ -369,7 +382,7 @@ void plan_launches(rbsog_ctx* c)
         const Plan o = one(c, r);
         const Shape* sh[kShapes] = {&o.atoms, &o.pair_atoms, &o.kf_atoms, &o.cells, &o.atom1, &o.modes64, &o.rho,
                                     &o.modes1, &o.rows64, &o.list_cells, &o.list_by_cap[0], &o.list_by_cap[1],
-                                    &o.list_by_cap[2]};
+                                    &o.list_by_cap[2], &o.kf_part};
         for (int q = 0; q < kShapes; ++q) {
             if (maps)
                 for (int b = 0; b < sh[q]->blocks; ++b) m[q].push_back(make_int2(r, b));
@@ -605,7 +618,7 @@ void enqueue_forces(rbsog_ctx* c, bool energy, bool kick, bool build = false)
     }
     c->begin(RBSOG_PHASE_RHO, true);
     launch_rho(P, c->mixed, ax);
-    launch_rho_finalize(P, ax);
+    launch_rho_finalize(P, energy, ax);
     c->end();
     if (aux_kf) {
         c->begin(RBSOG_PHASE_KFORCE, true);
@@ -757,7 +770,7 @@ void autotune(rbsog_ctx* c, int reps)
     };
     try_shape(best);
     launch_rho(c->plan, c->mixed, st);
-    launch_rho_finalize(c->plan, st);
+    launch_rho_finalize(c->plan, false, st);
     launch_pair(c->plan, c->coef, c->mixed, false, st);
     launch_finalize(c->plan, false, st);
     // a first pick of the k-space force workgroup size, the kernel alone
@@ -1231,7 +1244,7 @@ void set_batch_impl(rbsog_ctx* c, int R, const rbsog_params* params, const int32
                      hipMemcpyHostToDevice));
     std::vector<std::vector<int32_t>> em(R);
     std::vector<std::vector<double>> ecoef(R);
-    size_t cdf_doubles = 0, cdf_ints = 0, n_modes_all = 0, rho_part_all = 0;
+    size_t cdf_doubles = 0, cdf_ints = 0, n_modes_all = 0, rho_part_all = 0, kf_part_all = 0;
     for (int r = 0; r < R; ++r) {
         const rbsog_params& p = prm[r];
         KDev& k = c->hk[r];
@@ -1266,12 +1279,19 @@ void set_batch_impl(rbsog_ctx* c, int R, const rbsog_params* params, const int32
         // quarters read four atoms at a time
         k.chunk = (std::max(1, (n + k.n_chunks - 1) / k.n_chunks) + 15) & ~15;
         k.n_chunks = std::max(1, (n + k.chunk - 1) / k.chunk);
+        kforce_split(n, k.n_modes, &k.kf_slices, &k.kf_groups);
+        k.kf_len = blocks_for(k.n_modes, k.kf_slices * k.kf_groups);
+        k.kf_pad = round_up(std::max(n, 1), 64);
+        if (k.kf_groups > 1) kf_part_all += (size_t)k.kf_groups * kKfAccMax * k.kf_pad;
         n_modes_all += (size_t)k.n_modes;
         rho_part_all += 2 * (size_t)k.n_chunks * k.n_modes_pad;
     }
+    // grouped systems always take a wavefront per slice
+    for (auto& k : c->hk) k.kf_waves = (k.kf_groups > 1 || n_waves < (size_t)kKfFill) ? k.kf_slices : 1;
     c->kcdf.alloc(sizeof(double) * std::max<size_t>(1, cdf_doubles) + sizeof(int32_t) * cdf_ints);
     c->kmodes.alloc(std::max<size_t>(1, n_modes_all) * (sizeof(ModeRec) + 3 * sizeof(int32_t)));
     c->krho_part.alloc(sizeof(double) * std::max<size_t>(1, rho_part_all));
+    c->kf_part.alloc(sizeof(double) * kf_part_all);
     c->krho.alloc(sizeof(double) * 3 * std::max<size_t>(1, n_modes_all));  // rho (2), g (1)
     {
         double* dd = c->kcdf.as<double>();
@@ -1280,6 +1300,7 @@ void set_batch_impl(rbsog_ctx* c, int R, const rbsog_params* params, const int32
         int32_t* mm = reinterpret_cast<int32_t*>(mr + std::max<size_t>(1, n_modes_all));
         double* rp = c->krho_part.as<double>();
         double* rh = c->krho.as<double>();
+        double* kp = c->kf_part.as<double>();
         double* gh = rh + 2 * std::max<size_t>(1, n_modes_all);
         auto put = [](void* dst, const void* src, size_t b) {
             if (b) HIP_OK(hipMemcpy(dst, src, b, hipMemcpyHostToDevice));
@@ -1320,6 +1341,8 @@ void set_batch_impl(rbsog_ctx* c, int R, const rbsog_params* params, const int32
             rh += 2 * (size_t)k.n_modes;
             k.mode_g = gh;
             gh += (size_t)k.n_modes;
+            k.kf_part = k.kf_groups > 1 ? kp : nullptr;
+            if (k.kf_groups > 1) kp += (size_t)k.kf_groups * kKfAccMax * k.kf_pad;
         }
     }
 

@@ -73,7 +73,7 @@ __device__ inline KDev global_view(KDev k)
     k.off = glob(k.off), k.len = glob(k.len);
     k.g0cdf = glob(k.g0cdf), k.g2cdf = glob(k.g2cdf), k.comp_cdf = glob(k.comp_cdf);
     k.m = glob(k.m), k.modes = glob(k.modes);
-    k.rho_part = glob(k.rho_part), k.rho = glob(k.rho);
+    k.rho_part = glob(k.rho_part), k.rho = glob(k.rho), k.kf_part = glob(k.kf_part);
     k.sog_c = glob(k.sog_c), k.sog_s2 = glob(k.sog_s2);
     return k;
 }
@@ -1851,23 +1851,27 @@ __global__ __launch_bounds__(kBlock) void k_rho(RB_ARGS, const KDev* __restrict_
     }
 }
 
-// Sum of F^(k) terms at k^2 (value and -F^'(k)/k) for the mode virial.
+// g = -F^'(k)/(k F^(k)) of a mode (strain derivative of F^) by one wavefront,
+// the Gaussians over its lanes; every lane returns it.
 __device__ inline double mode_g(const KDev& k, double k2)
 {
     double F = 0.0, G = 0.0;
-    for (int m = 0; m < k.n_sog; ++m) {
+    for (int m = threadIdx.x & 63; m < k.n_sog; m += 64) {
         const double e = k.sog_c[m] * exp(-0.5 * k.sog_s2[m] * k2);
         F += e;
         G = fma(e, k.sog_s2[m], G);
     }
+    F = wave_sum(F);
+    G = wave_sum(G);
     return F > 0.0 ? G / F : 0.0;
 }
 
-// rho_p = sum over chunks (fixed tree), then the per-mode force coefficients.
-__global__ __launch_bounds__(64) void k_rho_finalize(RB_ARGS, const KDev* __restrict__ kd)
+// rho_p = sum over chunks (fixed tree), then the per-mode force coefficients
+// and, with energies, the mode's g (in the force-sum reduction, whose blocks
+// are few, the full sum's exponentials took 3.6 ms of a 4096-ion evaluation).
+__global__ __launch_bounds__(64) void k_rho_finalize(RB_ARGS, const KDev* __restrict__ kd, int energy)
 {
     RB_SYS(blockIdx.x)
-    (void)s;
     const KDev k = global_view(kd[rb_m.x]);
     const int p = lb;
     const int lane = threadIdx.x;
@@ -1881,10 +1885,15 @@ __global__ __launch_bounds__(64) void k_rho_finalize(RB_ARGS, const KDev* __rest
     }
     re = wave_sum(re);
     im = wave_sum(im);
+    ModeRec& r = k.modes[p];
+    if (energy) {
+        const double kx = s.two_pi_L[0] * r.mx, ky = s.two_pi_L[1] * r.my, kz = s.two_pi_L[2] * r.mz;
+        const double g = mode_g(k, (kx * kx + ky * ky) + kz * kz);
+        if (lane == 0) k.mode_g[p] = g;
+    }
     if (lane == 0) {
         k.rho[2 * p] = re;
         k.rho[2 * p + 1] = im;
-        ModeRec& r = k.modes[p];
         const double cf = r.coef;
         r.A = cf * im;
         r.B = cf * re;
@@ -1902,9 +1911,9 @@ __global__ __launch_bounds__(256) void k_finalize_part(const DevSys* __restrict_
 {
     const int r = blockIdx.x / grid, b = blockIdx.x - r * grid;
     const DevSys s = global_view(sys[r]);
-    const int nf = fin_blocks(s.n);
-    if (b >= nf) return;  // a smaller system of a batch
     const KDev k = global_view(kd[r]);
+    const int nf = fin_blocks(s.n, k.n_modes);
+    if (b >= nf) return;  // a smaller system of a batch
     const double* part = s.pair_part;
     const int nb = (s.n + 63) / 64;  // wavefront partials
     const int w0 = nb * b / nf, w1 = nb * (b + 1) / nf;  // nb * 32 fits 32 bits
@@ -1923,17 +1932,14 @@ __global__ __launch_bounds__(256) void k_finalize_part(const DevSys* __restrict_
     double ue = 0.0;
     double wk[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     const int nm = s.n > 0 ? k.n_modes : 0;  // an empty system sums no modes
-    const int m0 = nm * b / nf, m1 = nm * (b + 1) / nf;
+    const int m0 = (int)((long long)nm * b / nf), m1 = (int)((long long)nm * (b + 1) / nf);
     for (int p = m0 + (int)threadIdx.x; p < m1; p += blockDim.x) {
         const ModeRec mr = k.modes[p];
         ue += mr.e;
         if (energy) {
             // strain derivative of the mode's energy: e (delta_ab - g k_a k_b)
-            // g of the mode, kept for the per-atom shares of the fused pass
             const double kx = s.two_pi_L[0] * mr.mx, ky = s.two_pi_L[1] * mr.my, kz = s.two_pi_L[2] * mr.mz;
-            const double g = mode_g(k, (kx * kx + ky * ky) + kz * kz);
-            k.mode_g[p] = g;
-            const double eg = mr.e * g;
+            const double eg = mr.e * k.mode_g[p];
             wk[0] += mr.e - eg * kx * kx;
             wk[1] += mr.e - eg * ky * ky;
             wk[2] += mr.e - eg * kz * kz;
@@ -1959,14 +1965,14 @@ __global__ __launch_bounds__(256) void k_finalize_part(const DevSys* __restrict_
 }
 
 // Second pass: one wavefront per system; lane q adds quantity q of the
-// system's fin_blocks(n) block sums in block order, and the evaluation's
+// system's fin_blocks block sums in block order, and the evaluation's
 // scalars are written from them.
-__global__ __launch_bounds__(64) void k_finalize(const DevSys* __restrict__ sys, int energy)
+__global__ __launch_bounds__(64) void k_finalize(const DevSys* __restrict__ sys, const KDev* __restrict__ kd, int energy)
 {
     const DevSys s = global_view(sys[blockIdx.x]);
     const int q = threadIdx.x;
     double t = 0.0;
-    const int nf = fin_blocks(s.n);
+    const int nf = fin_blocks(s.n, kd[blockIdx.x].n_modes);
     // every row is read (all loads in flight together); rows past nf add 0
     if (q < kFin) {
 #pragma unroll
@@ -1995,12 +2001,160 @@ __global__ __launch_bounds__(64) void k_finalize(const DevSys* __restrict__ sys,
     }
 }
 
-// k-space force of eq. (29) (or eq. 23) on one atom per lane, looping over all
-// modes two at a time; adds the short-range force minus the momentum
-// correction, optionally the closing half kick of velocity Verlet.  The mixed
-// form takes Im(e^{-i theta} rho) coef in FP32 and accumulates in FP64.
+// Sums over modes [p0, p1) for one atom per lane, two modes at a time:
+// acc[0..2] += w m with w = Im(e^{-i theta} rho) coef, and with FLUX acc[3] +=
+// re = Re(e^{-i theta} rho) coef and acc[4..9] += re g m_a m_b (xx, yy, zz,
+// xy, xz, yz).  The mixed form takes w and re in FP32 and accumulates in FP64.
+template <bool FLUX>
+constexpr int kKfAcc = FLUX ? 10 : 3;
+
+// Position of an atom as the phases take it: scaled so that phase = m . u (in
+// turns, or in units of 2 pi / 1024 for the FP64 table), and the fixed-point record.
+struct KPos {
+    double4 u;
+    uint4 fix;
+};
+template <bool MIXED, bool IPH>
+__device__ inline KPos kspace_pos(const DevSys& s, int i)
+{
+    const double4 P = s.p[i];
+    const double sc = MIXED ? 1.0 : (double)kTableSize;
+    return KPos{make_double4(P.x * (sc * s.invL[0]), P.y * (sc * s.invL[1]), P.z * (sc * s.invL[2]), 0.0),
+                IPH ? s.ufix[i] : make_uint4(0, 0, 0, 0)};
+}
+
+template <bool MIXED, bool FLUX, bool IPH>
+__device__ inline void kspace_modes(const KDev& k, const double2* tab, const KPos& at, int p0, int p1, double* acc)
+{
+    const double4 U = at.u;
+    const uint4 Uf = at.fix;
+    auto one = [&](const ModeRec& mr, int p, double gm) {
+        double w, re = 0.0;
+        if (MIXED) {
+            float c, sn;
+            if (IPH) {
+                const float tf = turns_fix(k.m[3 * p], k.m[3 * p + 1], k.m[3 * p + 2], Uf);
+                c = __builtin_amdgcn_cosf(tf);
+                sn = __builtin_amdgcn_sinf(tf);
+            } else {
+                sincos_turns_f32(mode_phase(mr.mx, mr.my, mr.mz, U), c, sn);
+            }
+            // Im(e^{-i theta} rho) * coef = c * A - s * B
+            w = (double)fmaf(c, mr.Af, -(sn * mr.Bf));
+            // Re(e^{-i theta} rho) * coef = c * B + s * A
+            if (FLUX) re = (double)fmaf(c, mr.Bf, sn * mr.Af);
+        } else {
+            double c, sn;
+            sincos1024(mode_phase(mr.mx, mr.my, mr.mz, U), tab, c, sn);
+            w = fma(c, mr.A, -(sn * mr.B));
+            if (FLUX) re = fma(c, mr.B, sn * mr.A);
+        }
+        acc[0] = fma(w, mr.mx, acc[0]);
+        acc[1] = fma(w, mr.my, acc[1]);
+        acc[2] = fma(w, mr.mz, acc[2]);
+        if (FLUX) {
+            acc[3] += re;
+            const double rg = re * gm;
+            const double ax = rg * mr.mx, ay = rg * mr.my;
+            acc[4] = fma(ax, mr.mx, acc[4]);
+            acc[5] = fma(ay, mr.my, acc[5]);
+            acc[6] = fma(rg * mr.mz, mr.mz, acc[6]);
+            acc[7] = fma(ax, mr.my, acc[7]);
+            acc[8] = fma(ax, mr.mz, acc[8]);
+            acc[9] = fma(ay, mr.mz, acc[9]);
+        }
+    };
+    int p = p0;
+    for (; p + 2 <= p1; p += 2) {
+        const ModeRec m0 = k.modes[p];
+        const ModeRec m1 = k.modes[p + 1];
+        one(m0, p, FLUX ? k.mode_g[p] : 0.0);
+        one(m1, p + 1, FLUX ? k.mode_g[p + 1] : 0.0);
+    }
+    if (p < p1) one(k.modes[p], p, FLUX ? k.mode_g[p] : 0.0);
+}
+
+// Sums of atom i over mode slices [q0, q1), kf_len modes each: each slice
+// summed by itself, the slices added in order, so the result does not depend
+// on whether one wavefront or several take them.
+template <bool MIXED, bool FLUX, bool IPH>
+__device__ inline void kspace_slices(const KDev& k, const double2* tab, const KPos& at, int q0, int q1, double* acc)
+{
+    constexpr int N = kKfAcc<FLUX>;
+    for (int q = q0; q < q1; ++q) {
+        double one[N] = {};
+        kspace_modes<MIXED, FLUX, IPH>(k, tab, at, min(k.n_modes, q * k.kf_len), min(k.n_modes, (q + 1) * k.kf_len),
+                                       one);
+#pragma unroll
+        for (int c = 0; c < N; ++c) acc[c] = q == q0 ? one[c] : acc[c] + one[c];
+    }
+}
+
+// Adds up the sums of a block's slices, one wavefront each, in slice order
+// through LDS; the result is slice 0's.  Thread ta of a slice holds atom ta of
+// the block's A atoms.  kSlicePass quantities at a time bound the LDS.
+constexpr int kSlicePass = 5;
+template <int N>
+__device__ inline void slice_sum(double* acc, double* sm, int slices, int slice, int A, int ta)
+{
+    if (slices == 1) return;
+#pragma unroll
+    for (int c0 = 0; c0 < N; c0 += kSlicePass) {
+        constexpr int W = N < kSlicePass ? N : kSlicePass;
+        static_assert(N % W == 0, "whole passes");
+        if (c0 > 0) __syncthreads();
+        if (slice > 0)
+#pragma unroll
+            for (int c = 0; c < W; ++c) sm[((slice - 1) * W + c) * A + ta] = acc[c0 + c];
+        __syncthreads();
+        if (slice == 0)
+            for (int q = 1; q < slices; ++q)
+#pragma unroll
+                for (int c = 0; c < W; ++c) acc[c0 + c] += sm[((q - 1) * W + c) * A + ta];
+    }
+}
+
+template <bool MIXED>
+__device__ inline void load_sincos_table(const KDev& k, double2* tab)
+{
+    if (MIXED) return;
+    for (int t = threadIdx.x; t < kTableSize; t += blockDim.x) tab[t] = make_double2(k.table[2 * t], k.table[2 * t + 1]);
+    __syncthreads();
+}
+
+// A system of few atoms and very many modes (the full sum): group g of its
+// mode groups summed per atom into kf_part[g][c][atom]; k_kforce adds the
+// groups.  Blocks as in k_kforce, one set per group.
+template <bool MIXED, bool FLUX, bool IPH>
+__global__ __launch_bounds__(kKfThreads) void k_kforce_part(RB_ARGS, const KDev* __restrict__ kd)
+{
+    RB_SYS(blockIdx.x)
+    const KDev k = global_view(kd[rb_m.x]);
+    extern __shared__ double slice_sm[];
+    __shared__ double2 tab[MIXED ? 1 : kTableSize];
+    load_sincos_table<MIXED>(k, tab);
+    const int A = blockDim.x >> __builtin_ctz(k.kf_slices);
+    const int nblk = (s.n + A - 1) / A;
+    const int group = lb / nblk;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int slice = wave >> __builtin_ctz(A >> 6);
+    const int ta = threadIdx.x - slice * A;
+    const int i = (lb - group * nblk) * A + ta;
+    const int part = group * k.kf_slices + slice;
+    double acc[kKfAcc<FLUX>] = {};
+    if (i < s.n) kspace_slices<MIXED, FLUX, IPH>(k, tab, kspace_pos<MIXED, IPH>(s, i), part, part + 1, acc);
+    slice_sum<kKfAcc<FLUX>>(acc, slice_sm, k.kf_slices, slice, A, ta);
+    if (slice == 0 && i < s.n)
+#pragma unroll
+        for (int c = 0; c < kKfAcc<FLUX>; ++c) k.kf_part[((size_t)group * kKfAcc<FLUX> + c) * k.kf_pad + i] = acc[c];
+}
+
 // k-space force of eq. (29) (eq. (23) for the full sum) of each atom,
 // F_k = -k_e q_i sum_p (2 pi m_p / L) coef_p Im(e^{-i theta} rho_p).
+// The loop over modes is bound by FP64 issue (phases, accumulation), and a
+// small system has too few atoms to fill the SIMDs with one atom per lane:
+// its modes are cut into kf_slices contiguous slices whose sums are added in
+// order, one wavefront each where the launch has too few (kf_waves).
 // FUSED = false: written into the total-force arrays, which hold it until
 // k_combine adds the short-range part (it needs only the positions and rho,
 // so it can run on the second stream beside the pair kernel).  FUSED: the
@@ -2010,81 +2164,52 @@ __global__ __launch_bounds__(64) void k_finalize(const DevSys* __restrict__ sys,
 // (k_e/2) q_i Re(e^{-i theta} rho_p) coef_p, and of its virial, that times
 // (delta_ab - g_p k_a k_b); with the pair kernel's shares and the final
 // velocity they give the stress and heat-flux partials of eqs. (50)-(51).
-template <bool MIXED, bool FUSED, bool KICK, int KE, bool IPH>
-__global__ __launch_bounds__(kBlock) void k_kforce(RB_ARGS, const KDev* __restrict__ kd)
+// SPLIT: some system of the launch has slices (a kernel without the loop over
+// them is 3 % faster at 10^6 ions).
+template <bool MIXED, bool FUSED, bool KICK, int KE, bool IPH, bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? kKfThreads : kBlock) void k_kforce(RB_ARGS, const KDev* __restrict__ kd)
 {
     constexpr bool ENERGY = KE > 0;
     constexpr bool FLUX = FUSED && KE == 2;
+    constexpr int N = kKfAcc<FLUX>;
     RB_SYS(blockIdx.x)
     const KDev k = global_view(kd[rb_m.x]);
+    extern __shared__ double slice_sm[];
     __shared__ double2 tab[MIXED ? 1 : kTableSize];
-    if (!MIXED) {
-        for (int t = threadIdx.x; t < kTableSize; t += blockDim.x)
-            tab[t] = make_double2(k.table[2 * t], k.table[2 * t + 1]);
-        __syncthreads();
-    }
-    const int i = lb * blockDim.x + threadIdx.x;
+    const bool grouped = SPLIT && k.kf_groups > 1;
+    const int slices = (SPLIT && !grouped) ? k.kf_waves : 1;  // wavefronts an atom's modes are dealt to
+    if (!grouped) load_sincos_table<MIXED>(k, tab);
+    const int A = blockDim.x >> __builtin_ctz(slices);  // powers of two
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int slice = SPLIT ? wave >> __builtin_ctz(A >> 6) : 0;
+    const int ta = threadIdx.x - slice * A;
+    const int i = lb * A + ta;
     double ke = 0.0;
     bool bad = false;
     double fl[kFluxPart];
     if (FLUX)
         for (int c = 0; c < kFluxPart; ++c) fl[c] = 0.0;
-    if (i < s.n) {
-        const double4 Pi = s.p[i];
-        const double sc = MIXED ? 1.0 : (double)kTableSize;
-        // scaled position: phase = m . u
-        const double4 U = make_double4(Pi.x * (sc * s.invL[0]), Pi.y * (sc * s.invL[1]),
-                                       Pi.z * (sc * s.invL[2]), 0.0);
-        double Gx = 0.0, Gy = 0.0, Gz = 0.0;
-        // FLUX: sum_p Re(e^{-i theta} rho_p) coef_p, and that times g_p m_a m_b
-        double Ek = 0.0, Txx = 0.0, Tyy = 0.0, Tzz = 0.0, Txy = 0.0, Txz = 0.0, Tyz = 0.0;
-        const uint4 Uf = IPH ? s.ufix[i] : make_uint4(0, 0, 0, 0);
-        auto one = [&](const ModeRec& mr, int p, double gm) {
-            double w, re = 0.0;
-            if (MIXED) {
-                float c, sn;
-                if (IPH) {
-                    const float tf = turns_fix(k.m[3 * p], k.m[3 * p + 1], k.m[3 * p + 2], Uf);
-                    c = __builtin_amdgcn_cosf(tf);
-                    sn = __builtin_amdgcn_sinf(tf);
-                } else {
-                    sincos_turns_f32(mode_phase(mr.mx, mr.my, mr.mz, U), c, sn);
-                }
-                // Im(e^{-i theta} rho) * coef = c * A - s * B
-                w = (double)fmaf(c, mr.Af, -(sn * mr.Bf));
-                // Re(e^{-i theta} rho) * coef = c * B + s * A
-                if (FLUX) re = (double)fmaf(c, mr.Bf, sn * mr.Af);
-            } else {
-                double c, sn;
-                sincos1024(mode_phase(mr.mx, mr.my, mr.mz, U), tab, c, sn);
-                w = fma(c, mr.A, -(sn * mr.B));
-                if (FLUX) re = fma(c, mr.B, sn * mr.A);
-            }
-            Gx = fma(w, mr.mx, Gx);
-            Gy = fma(w, mr.my, Gy);
-            Gz = fma(w, mr.mz, Gz);
-            if (FLUX) {
-                Ek += re;
-                const double rg = re * gm;
-                const double ax = rg * mr.mx, ay = rg * mr.my;
-                Txx = fma(ax, mr.mx, Txx);
-                Tyy = fma(ay, mr.my, Tyy);
-                Tzz = fma(rg * mr.mz, mr.mz, Tzz);
-                Txy = fma(ax, mr.my, Txy);
-                Txz = fma(ax, mr.mz, Txz);
-                Tyz = fma(ay, mr.mz, Tyz);
-            }
-        };
-        int p = 0;
-        for (; p + 2 <= k.n_modes; p += 2) {
-            const ModeRec m0 = k.modes[p];
-            const ModeRec m1 = k.modes[p + 1];
-            one(m0, p, FLUX ? k.mode_g[p] : 0.0);
-            one(m1, p + 1, FLUX ? k.mode_g[p + 1] : 0.0);
+    double acc[N] = {};
+    if (grouped) {
+        if (i < s.n)
+            for (int g = 0; g < k.kf_groups; ++g)
+#pragma unroll
+                for (int c = 0; c < N; ++c) acc[c] += k.kf_part[((size_t)g * N + c) * k.kf_pad + i];
+    } else if (!SPLIT) {
+        if (i < s.n) kspace_modes<MIXED, FLUX, IPH>(k, tab, kspace_pos<MIXED, IPH>(s, i), 0, k.n_modes, acc);
+    } else {
+        if (i < s.n) {
+            // one wavefront takes every slice, or each takes its own
+            const int q0 = slices == 1 ? 0 : slice, q1 = slices == 1 ? k.kf_slices : slice + 1;
+            kspace_slices<MIXED, FLUX, IPH>(k, tab, kspace_pos<MIXED, IPH>(s, i), q0, q1, acc);
         }
-        if (p < k.n_modes) one(k.modes[p], p, FLUX ? k.mode_g[p] : 0.0);
+        slice_sum<N>(acc, slice_sm, slices, slice, A, ta);
+        if (slice != 0) return;
+    }
+    if (i < s.n) {
         const int ti = s.type[i];
         const double qk = -s.coulomb_k * s.spc->q[ti];
+        const double Gx = acc[0], Gy = acc[1], Gz = acc[2];
         if (!FUSED) {
             s.fx[i] = qk * s.two_pi_L[0] * Gx;
             s.fy[i] = qk * s.two_pi_L[1] * Gy;
@@ -2110,7 +2235,10 @@ __global__ __launch_bounds__(kBlock) void k_kforce(RB_ARGS, const KDev* __restri
             }
             const double m = s.spc->mass[ti];
             if (ENERGY) ke = 0.5 * m * (vx * vx + vy * vy + vz * vz);
-            if (FLUX) {
+            if constexpr (FLUX) {
+                // acc: sum_p Re(e^{-i theta} rho_p) coef_p, and that times g_p m_a m_b
+                const double Ek = acc[3], Txx = acc[4], Tyy = acc[5], Tzz = acc[6], Txy = acc[7], Txz = acc[8],
+                             Tyz = acc[9];
                 const double hq = 0.5 * s.coulomb_k * s.spc->q[ti];
                 const double tx = s.two_pi_L[0], ty = s.two_pi_L[1], tz = s.two_pi_L[2];
                 const double4 a0 = s.at_ew[2 * (size_t)i];
@@ -2743,51 +2871,80 @@ void launch_rho(const Plan& P, bool mixed, hipStream_t st)
     }
 }
 
-void launch_rho_finalize(const Plan& P, hipStream_t st)
+void launch_rho_finalize(const Plan& P, bool energy, hipStream_t st)
 {
-    if (P.modes1.blocks > 0) k_rho_finalize<<<P.modes1.blocks, 64, 0, st>>>(RB_MAP(modes1), P.kd);
+    if (P.modes1.blocks > 0)
+        k_rho_finalize<<<P.modes1.blocks, 64, 0, st>>>(RB_MAP(modes1), P.kd, energy ? 1 : 0);
 }
 
 void launch_finalize(const Plan& P, bool energy, hipStream_t st)
 {
     if (P.R <= 0) return;
     k_finalize_part<<<P.R * P.fin_grid, 256, 0, st>>>(P.sys, P.kd, energy ? 1 : 0, P.fin_grid);
-    k_finalize<<<P.R, 64, 0, st>>>(P.sys, energy ? 1 : 0);
+    k_finalize<<<P.R, 64, 0, st>>>(P.sys, P.kd, energy ? 1 : 0);
+}
+
+// LDS of the slice sums: every thread but slice 0's hands over n values, at
+// most kSlicePass at a time.
+static size_t slice_lds(const Plan& P, int n)
+{
+    return P.kf_sliced ? sizeof(double) * (n < kSlicePass ? n : kSlicePass) * P.kf_threads : 0;
 }
 
 void launch_kforce(const Plan& P, bool mixed, hipStream_t st)
 {
     const int nb = P.kf_atoms.blocks;
-    const int bs = P.tune.kf_block;
+    const int bs = P.kf_threads;
     if (nb <= 0) return;
+    const size_t sm = slice_lds(P, kKfAcc<false>);
+#define RB_KF(M, I)                                                                                          \
+    do {                                                                                                     \
+        if (P.kf_part.blocks > 0)                                                                            \
+            k_kforce_part<M, false, I><<<P.kf_part.blocks, bs, sm, st>>>(RB_MAP(kf_part), P.kd);             \
+        if (P.kf_split)                                                                                      \
+            k_kforce<M, false, false, 0, I, true><<<nb, bs, sm, st>>>(RB_MAP(kf_atoms), P.kd);               \
+        else                                                                                                 \
+            k_kforce<M, false, false, 0, I, false><<<nb, bs, 0, st>>>(RB_MAP(kf_atoms), P.kd);               \
+    } while (0)
     if (mixed && P.iph)
-        k_kforce<true, false, false, 0, true><<<nb, bs, 0, st>>>(RB_MAP(kf_atoms), P.kd);
+        RB_KF(true, true);
     else if (mixed)
-        k_kforce<true, false, false, 0, false><<<nb, bs, 0, st>>>(RB_MAP(kf_atoms), P.kd);
+        RB_KF(true, false);
     else
-        k_kforce<false, false, false, 0, false><<<nb, bs, 0, st>>>(RB_MAP(kf_atoms), P.kd);
+        RB_KF(false, false);
+#undef RB_KF
 }
 
 void launch_kforce_fused(const Plan& P, bool mixed, bool kick, int ke, hipStream_t st)
 {
     const int nb = P.kf_atoms.blocks;
-    const int bs = P.tune.kf_block;
+    const int bs = P.kf_threads;
     if (nb <= 0) return;
-#define RB_KF(M, K, E)                                                                  \
-    do {                                                                                \
-        if (M && P.iph)                                                                 \
-            k_kforce<M, true, K, E, M><<<nb, bs, 0, st>>>(RB_MAP(kf_atoms), P.kd);      \
-        else                                                                            \
-            k_kforce<M, true, K, E, false><<<nb, bs, 0, st>>>(RB_MAP(kf_atoms), P.kd);  \
+    const size_t sm = slice_lds(P, ke == 2 ? kKfAcc<true> : kKfAcc<false>);
+#define RB_KF(M, K, E, I)                                                                                    \
+    do {                                                                                                     \
+        if (P.kf_part.blocks > 0)                                                                            \
+            k_kforce_part<M, E == 2, I><<<P.kf_part.blocks, bs, sm, st>>>(RB_MAP(kf_part), P.kd);            \
+        if (P.kf_split)                                                                                      \
+            k_kforce<M, true, K, E, I, true><<<nb, bs, sm, st>>>(RB_MAP(kf_atoms), P.kd);                    \
+        else                                                                                                 \
+            k_kforce<M, true, K, E, I, false><<<nb, bs, 0, st>>>(RB_MAP(kf_atoms), P.kd);                    \
+    } while (0)
+#define RB_KF_I(M, K, E)                \
+    do {                                \
+        if (M && P.iph)                 \
+            RB_KF(M, K, E, M);          \
+        else                            \
+            RB_KF(M, K, E, false);      \
     } while (0)
 #define RB_KF_KE(M, K)        \
     do {                      \
         if (ke == 2)          \
-            RB_KF(M, K, 2);   \
+            RB_KF_I(M, K, 2); \
         else if (ke == 1)     \
-            RB_KF(M, K, 1);   \
+            RB_KF_I(M, K, 1); \
         else                  \
-            RB_KF(M, K, 0);   \
+            RB_KF_I(M, K, 0); \
     } while (0)
     if (mixed) {
         if (kick) RB_KF_KE(true, true); else RB_KF_KE(true, false);
@@ -2795,6 +2952,7 @@ void launch_kforce_fused(const Plan& P, bool mixed, bool kick, int ke, hipStream
         if (kick) RB_KF_KE(false, true); else RB_KF_KE(false, false);
     }
 #undef RB_KF_KE
+#undef RB_KF_I
 #undef RB_KF
 }
 

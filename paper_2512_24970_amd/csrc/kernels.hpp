@@ -129,8 +129,19 @@ struct KDev {
     int n_sog;            // terms of F^(k): c[m] exp(-s2[m] k^2 / 2), m < n_sog
     const double* sog_c;
     const double* sog_s2;
-    double* mode_g;       // [n_modes] g = G/F^ of each mode (strain derivative), set by the
-                          // finalize of evaluations with energies
+    double* mode_g;       // [n_modes] g = G/F^ of each mode (strain derivative), set by
+                          // evaluations with energies
+    // The k-space force sums the modes in slices and, with groups > 1, groups
+    // of such slices, whose sums go through kf_part [groups][3 or 10][kf_pad].
+    // Both are chosen from the system's own atoms and modes (kforce_split), so
+    // a system sums in the same order alone and in a batch.  kf_waves: 1, or
+    // kf_slices where the launch is short of wavefronts, one per slice.
+    int kf_slices;        // a power of two, like kf_waves
+    int kf_groups;
+    int kf_len;           // modes per slice
+    int kf_waves;
+    int kf_pad;
+    double* kf_part;
 };
 
 // Per-wavefront partial sums written by the pair kernel: F (3), u_core,
@@ -138,21 +149,44 @@ struct KDev {
 constexpr int kPairPart = 5;
 constexpr int kVirPart = 6;
 // The reduction of those partials and of the modes' energies runs in two
-// passes: fin_blocks(n) blocks per system (one per 256 wavefront partials,
-// at most kFinBlocks), each over a fixed slice, then one wavefront per
-// system adding their kFin sums in block order.  The slicing depends on the
-// system's own size only, so a system sums in the same order alone and in a
-// batch.
+// passes: fin_blocks(n, modes) blocks per system (one per 256 wavefront
+// partials or 2048 modes, at most kFinBlocks), each over a fixed slice, then
+// one wavefront per system adding their kFin sums in block order.  The slicing
+// depends on the system's own size only, so a system sums in the same order
+// alone and in a batch.
 constexpr int kFinBlocks = 32;
 constexpr int kFin = kPairPart + kVirPart + 1 + 6;  // pair sums, virial, mode energy, mode virial
-constexpr int fin_blocks(int n)
+constexpr int fin_blocks(int n, int modes)
 {
-    const int b = ((n + 63) / 64 + 255) / 256;
+    const int bw = ((n + 63) / 64 + 255) / 256, bm = (modes + 2047) / 2048;
+    const int b = bw > bm ? bw : bm;
     return b < 1 ? 1 : (b > kFinBlocks ? kFinBlocks : b);
 }
 // Per-wavefront partials of the closing pass of an evaluation with energies:
 // sum m v_a v_b (6), sum (m v^2 / 2) v (3), sum (e_i v + W_i v) (3).
 constexpr int kFluxPart = 12;
+
+// Split of the k-space force's modes.  Slices double while the system's
+// wavefronts would leave SIMDs with fewer than four and a slice keeps at least
+// 24 modes (a slice's own set-up is worth a few modes); groups on top, for the
+// full sum of a small system, until about eight wavefronts a SIMD, each with
+// at least 128 modes.  A launch (all systems of a batch) that has four
+// wavefronts a SIMD without them gives an atom's slices to one wavefront: 64
+// replicas, 100 modes, lost 1.4 % of a step with a wavefront per slice, while
+// the step of 32768 ions and 200 modes alone gained 14 % (FP64) and 9 % (mixed).
+constexpr int kKfThreads = 1024;  // largest workgroup of the k-space force
+constexpr int kKfFill = 4096;     // wavefronts: four on each of 1024 SIMDs
+constexpr int kKfSlices = 16, kKfGroups = 16;
+constexpr int kKfAccMax = 10;     // sums per atom (with the shares of energy and virial)
+inline void kforce_split(int n, int modes, int* slices, int* groups)
+{
+    const int waves = (n + 63) / 64;
+    int S = 1, G = 1;
+    while (S < kKfSlices && waves * S < kKfFill && modes / (2 * S) >= 24) S *= 2;
+    while (S == kKfSlices && G < kKfGroups && (long long)waves * S * G < 2 * kKfFill && modes / (2 * S * G) >= 128) G *= 2;
+    *slices = S;
+    *groups = G;
+}
 
 // The grid of one launch over a batch: block b works on local block map[b].y
 // of system map[b].x.  A null map means one system (system 0, local block b).
@@ -167,7 +201,7 @@ struct Tuning {
     int pair_block = 256;  // atoms per pair-kernel workgroup (64, 128, 256)
     int pair_ku = 4;       // neighbours fetched ahead in the pair kernel (4, 8)
     int rho_mpl = 1;       // modes per lane in the rho kernel (1, 2)
-    int kf_block = 256;    // atoms per k-space force workgroup (64, 128, 256)
+    int kf_block = 256;    // threads per k-space force workgroup (64, 128, 256)
     int kf_aux = 1;        // k-space force on the second stream (1) or after the pair kernel (0)
 };
 
@@ -195,7 +229,11 @@ struct Plan {
     int R = 0;
     Shape atoms;    // 256-atom blocks of every system
     Shape pair_atoms;  // tune.pair_block-atom blocks (pair kernel)
-    Shape kf_atoms;    // tune.kf_block-atom blocks (k-space force kernel)
+    Shape kf_atoms;    // kf_threads-thread blocks (k-space force kernel)
+    Shape kf_part;     // the mode groups of the systems that have several (local block = group * blocks + block)
+    int kf_threads = 256;   // tune.kf_block, or more where a system's slices need it
+    bool kf_split = false;  // some system cuts its modes into slices
+    bool kf_sliced = false; // some system's slices take a wavefront each
     Shape cells;    // one block per cell
     Shape list_cells;  // list_parts blocks per cell (list build)
     // the same cells grouped by the staging capacity kListCaps[q] of their
@@ -239,7 +277,7 @@ void launch_lists(const Plan& P, bool gate, hipStream_t st);
 void launch_ksample(const Plan& P, hipStream_t st);
 void launch_pair(const Plan& P, const SogCoef& sog, bool mixed, bool energy, hipStream_t st);
 void launch_rho(const Plan& P, bool mixed, hipStream_t st);
-void launch_rho_finalize(const Plan& P, hipStream_t st);
+void launch_rho_finalize(const Plan& P, bool energy, hipStream_t st);
 // momentum correction and energies; with `energy` also the virial
 void launch_finalize(const Plan& P, bool energy, hipStream_t st);
 // k-space force (eq. 29) into the total-force arrays

@@ -1,0 +1,87 @@
+"""The k-space force with its modes cut into slices (one wavefront each) and
+groups of slices, at the sizes where the split changes: the smallest systems,
+odd mode counts, the full sum of a few hundred to a few thousand ions, and a
+size that is not split.  Forces, energies, virial and heat flux against the
+oracle, FP64 at its 1e-11 bar and the mixed form at 1e-5 (the split reorders
+FP64 sums of a few hundred terms: 1e-14)."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle as O
+from force_bars import check_forces
+from paper_2512_24970_amd import rbsog as R
+from paper_2512_24970_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _cfg(n):
+    return W.config("nacl_512", n=n, box=(n / 0.0319) ** (1 / 3))
+
+
+def _eval(cfg, precision, want_energy, **over):
+    import torch
+    sysp = dict(cfg["sys"], **over)
+    ctx = R.Context(0)
+    dev = torch.device("cuda", 0)
+    ctx.rbsog_set_system(R.make_params(sysp, precision, n_atoms=len(cfg["types"])),
+                         *(torch.as_tensor(cfg[k], device=dev) for k in ("types", "pos", "vel")))
+    f, e = ctx.rbsog_compute_forces(2, want_energy=want_energy)
+    return f.cpu().numpy(), e, sysp
+
+
+@pytest.mark.parametrize("precision,tol", [(R.FP64, 1e-11), (R.MIXED, 1e-5)])
+@pytest.mark.parametrize("n,p_f", [(514, 1), (514, 47), (642, 48), (1000, 193), (2050, 767), (4096, 1200)])
+def test_sliced_modes(n, p_f, precision, tol):
+    print(f"case: sliced modes n {n} p_f {p_f} precision {precision}", flush=True)
+    cfg = _cfg(n)
+    f, e, sysp = _eval(cfg, precision, True, p_f=p_f)
+    g, _, _ = _eval(cfg, precision, False, p_f=p_f)  # the unfused pass
+    assert np.abs(f - g).max() <= 1e-12 * np.abs(f).max()
+    fo, eo = O.System(sysp, cfg["types"], cfg["pos"], cfg["vel"]).forces(2)
+    check_forces(f, fo, tol, "force")
+    for key in ("u_kspace", "u_total", "virial", "stress", "heat_flux"):
+        a, b = np.atleast_1d(e[key]), np.atleast_1d(eo[key])
+        assert np.abs(a - b).max() <= 10 * tol * np.abs(b).max(), key
+
+
+@pytest.mark.parametrize("n", [514, 1000])
+def test_grouped_full_sum(n):
+    """Every shell candidate and the full k-sum: the modes of a small system
+    are summed in groups through memory, with and without energies."""
+    print(f"case: grouped full sum n {n}", flush=True)
+    cfg = _cfg(n)
+    f, e, sysp = _eval(cfg, R.FP64, True, p_r=0, p_f=0)
+    g, _, _ = _eval(cfg, R.FP64, False, p_r=0, p_f=0)
+    fo, eo = O.System(sysp, cfg["types"], cfg["pos"], cfg["vel"]).forces(2)
+    check_forces(f, fo, 1e-11, "force")
+    check_forces(g, fo, 1e-11, "force without energies")
+    for key in ("u_kspace", "u_total", "virial", "stress", "heat_flux"):
+        a, b = np.atleast_1d(e[key]), np.atleast_1d(eo[key])
+        assert np.abs(a - b).max() <= 1e-10 * np.abs(b).max(), key
+
+
+def test_batch_of_split_and_whole_systems_equals_singles():
+    """A batch whose systems differ in slices and groups: each system's forces
+    are bit for bit those of the system alone."""
+    import torch
+    print("case: batch of split and whole systems", flush=True)
+    sizes, p_f = (514, 4000, 642, 33000), (0, 200, 47, 60)
+    cfgs = [_cfg(n) for n in sizes]
+    dev = torch.device("cuda", 0)
+    ctx = R.Context(0)
+    ctx.rbsog_set_batch([R.make_params(dict(c["sys"], p_f=p), R.FP64, n_atoms=len(c["types"]))
+                         for c, p in zip(cfgs, p_f)],
+                        *(torch.as_tensor(np.concatenate([c[k] for c in cfgs]), device=dev)
+                          for k in ("types", "pos", "vel")))
+    f, e = ctx.rbsog_compute_forces(2)
+    f = f.cpu().numpy()
+    at = 0
+    for c, p, er in zip(cfgs, p_f, e):
+        n = len(c["types"])
+        g, eg, _ = _eval(c, R.FP64, True, p_f=p)
+        assert np.array_equal(f[at:at + n], g)
+        assert er == eg
+        at += n
