@@ -318,7 +318,8 @@ Plan one(const rbsog_ctx* c, int r)
     P.R = 1;
     P.tune = c->plan.tune;
     P.atoms.blocks = blocks_for(s.n, kBlock);
-    P.pair_atoms.blocks = blocks_for(s.n, P.tune.pair_block);
+    P.pair_lanes = c->plan.pair_lanes;
+    P.pair_atoms.blocks = blocks_for(s.n, P.pair_lanes > 1 ? 64 : P.tune.pair_block);
     P.kf_threads = c->plan.kf_threads;
     P.kf_split = c->plan.kf_split;
     P.kf_sliced = c->plan.kf_sliced;
@@ -363,6 +364,9 @@ void plan_launches(rbsog_ctx* c)
     P.sc = c->scalars.as<DeviceScalars>();
     P.R = c->R;
     P.fin_grid = 1;
+    size_t waves = 0;
+    for (const auto& s : c->hs) waves += blocks_for(s.n, 64);
+    P.pair_lanes = pair_lanes_for(waves, c->mixed);
     P.kf_threads = P.tune.kf_block;
     P.kf_split = P.kf_sliced = false;
     for (int r = 0; r < c->R; ++r) {
@@ -632,7 +636,7 @@ void enqueue_forces(rbsog_ctx* c, bool energy, bool kick, bool build = false)
         c->end();
     }
     c->begin(RBSOG_PHASE_PAIR);
-    launch_pair(P, c->coef, c->mixed, energy, st);
+    launch_pair(P, c->mixed, energy, st);
     HIP_OK(hipGetLastError());  // a launch the device refuses (e.g. LDS size) must not pass silently
     c->end();
     HIP_OK(hipStreamWaitEvent(st, c->ev_join, 0));
@@ -771,7 +775,7 @@ void autotune(rbsog_ctx* c, int reps)
     try_shape(best);
     launch_rho(c->plan, c->mixed, st);
     launch_rho_finalize(c->plan, false, st);
-    launch_pair(c->plan, c->coef, c->mixed, false, st);
+    launch_pair(c->plan, c->mixed, false, st);
     launch_finalize(c->plan, false, st);
     // a first pick of the k-space force workgroup size, the kernel alone
     // (refined on whole steps below)
@@ -871,6 +875,24 @@ void autotune(rbsog_ctx* c, int reps)
     HIP_OK(hipStreamSynchronize(st));
     c->forces_valid = true;
     c->profiling = was_profiling;
+}
+
+SogCoefF sog_coef_f32(const SogCoef& g)
+{
+    SogCoefF f{};
+    f.n_exp = g.n_exp;
+    f.chain = g.chain;
+    f.n_poly = g.n_poly;
+    for (int m = 0; m < kMaxExplicit; ++m) {
+        f.a[m] = (float)g.a[m];
+        f.fw[m] = (float)g.fw[m];
+        f.ew[m] = (float)g.ew[m];
+    }
+    for (int n = 0; n < kMaxPoly; ++n) {
+        f.pc[n] = (float)g.pc[n];
+        f.pd[n] = (float)g.pd[n];
+    }
+    return f;
 }
 
 // Geometry, cutoffs, species and integrator constants of one system.
@@ -1022,17 +1044,35 @@ void set_batch_impl(rbsog_ctx* c, int R, const rbsog_params* params, const int32
     if (!sog_kernel_coef(c->sog, c->chain, p0.r_shell, c->mixed, &c->coef, &err)) throw Error(RBSOG_E_ARG, err);
     double wsum = 0.0;
     for (double w : c->sog.w) wsum += w;
-    // FP32 near-field table of the mixed form (shared)
-    NearTable nt;
-    if (c->mixed) build_near_table(c->sog, p0.r_shell, &nt);
+    // near-field table of the form, and the split's coefficients (shared)
     c->plan.near = NearTab{};
-    if (nt.nbin > 0) {
-        c->neartab.alloc(sizeof(float) * nt.coef.size());
-        HIP_OK(hipMemcpy(c->neartab.p, nt.coef.data(), sizeof(float) * nt.coef.size(), hipMemcpyHostToDevice));
-        c->plan.near.coef = c->neartab.as<float4>();
+    std::vector<char> near;
+    auto take = [&](const void* src, size_t bytes) {
+        const char* q = static_cast<const char*>(src);
+        near.insert(near.end(), q, q + bytes);
+    };
+    const SogCoefF coef32 = sog_coef_f32(c->coef);
+    if (c->mixed) {
+        NearTable nt;
+        build_near_table(c->sog, p0.r_shell, &nt);
         c->plan.near.lo = (127 + nt.e0) << 6;
         c->plan.near.n = nt.nbin * kNearSub;
+        take(nt.coef.data(), sizeof(float) * nt.coef.size());
+    } else {
+        NearTable64 nt;
+        build_near_table64(c->coef, p0.r_shell, &nt);
+        c->plan.near.lo = (1023 + nt.e0) << kNearBits64;
+        c->plan.near.n = nt.nbin << kNearBits64;
+        take(nt.coef.data(), sizeof(double) * nt.coef.size());
     }
+    const size_t near_coef = near.size();  // a multiple of 16 bytes
+    take(&c->coef, sizeof(SogCoef));
+    take(&coef32, sizeof(SogCoefF));
+    c->neartab.alloc(near.size());
+    HIP_OK(hipMemcpy(c->neartab.p, near.data(), near.size(), hipMemcpyHostToDevice));
+    c->plan.near.coef = c->neartab.as<float4>();
+    c->plan.near.g64 = reinterpret_cast<const SogCoef*>(c->neartab.as<char>() + near_coef);
+    c->plan.near.g32 = reinterpret_cast<const SogCoefF*>(c->neartab.as<char>() + near_coef + sizeof(SogCoef));
 
     c->drop_graphs();
     if (!c->aux) HIP_OK(hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking));

@@ -55,6 +55,16 @@ struct SogCoef {
     double pd[kMaxPoly];       // sum_{m>=n_exp} w_m (-a_m)^n/n!
 };
 
+// The same in FP32, for the mixed form.
+struct SogCoefF {
+    int n_exp, chain, n_poly, pad;
+    float a[kMaxExplicit];
+    float fw[kMaxExplicit];
+    float ew[kMaxExplicit];
+    float pc[kMaxPoly];
+    float pd[kMaxPoly];
+};
+
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11).
 __host__ __device__ inline void philox4x32_10(uint32_t& c0, uint32_t& c1, uint32_t& c2, uint32_t& c3,
                                               uint32_t k0, uint32_t k1)

@@ -1055,62 +1055,57 @@ struct PairCoefF {
     float qq, A, sig, irho, C, D;
 };
 
-struct SogCoefF {
-    int n_exp, chain, n_poly, pad;
-    float a[kMaxExplicit];
-    float fw[kMaxExplicit];
-    float ew[kMaxExplicit];
-    float pc[kMaxPoly];
-    float pd[kMaxPoly];
-};
-
 // Pair force scalar f (F_i += f * r_ij) of eq. (15) with k_e on the Coulomb
-// part, and the pair energy k_e q_i q_j N(r) + B_BMH(r), in FP64.
-template <int J, bool ENERGY>
-__device__ inline double pair_scalar_f64(const PairCoef& c, const SogCoef& g, double r2, double& u)
+// part, and the pair energy k_e q_i q_j N(r) + B_BMH(r), in FP64.  The SOG
+// Coulomb kernels CF = -N'(r)/r and CU = N(r) come from a table in LDS: the
+// exponent and five leading mantissa bits of r^2 pick the interval, whose
+// degree-7 polynomial in t = r^2 - (its midpoint) is evaluated by Horner.
+// Summed directly they took an exponential, five squarings and a 13-term
+// polynomial, 30 FP64 operations whose coefficients came one by one through
+// the scalar unit.  Below the table (closer than 1 A, never reached by a melt)
+// every narrow Gaussian is evaluated by its own exponential.
+template <bool ENERGY>
+__device__ inline double pair_scalar_f64(const PairCoef& c, const SogCoef* gp, const double2* tab, int tab_lo,
+                                         int tab_n, double r2, double& u)
 {
     const double ir = rsqrt(r2);
     const double r = r2 * ir;
     const double ir2 = ir * ir;
-    const int n = g.n_exp;
-    double fsum = 0.0, esum = 0.0;
-    if (J == 1) {
-        double gm = exp(-r2 * g.a[n - 1]);
-        fsum = g.fw[n - 1] * gm;
-        if (ENERGY) esum = g.ew[n - 1] * gm;
-        for (int m = n - 2; m >= 0; --m) {
-            gm = gm * gm;
-            fsum = fma(g.fw[m], gm, fsum);
-            if (ENERGY) esum = fma(g.ew[m], gm, esum);
-        }
+    double cf, cu = 0.0;
+    const uint32_t hi = (uint32_t)((unsigned long long)__double_as_longlong(r2) >> 32);
+    constexpr int kShift = 20 - kNearBits64;
+    const int idx = (int)(hi >> kShift) - tab_lo;
+    if ((unsigned)idx < (unsigned)tab_n) {
+        const double mid = __hiloint2double((int)((hi & ~((1u << kShift) - 1u)) | (1u << (kShift - 1))), 0);
+        const double t = r2 - mid;
+        auto horner = [&](const double2* q) {
+            const double2 a = q[0], b = q[1], d = q[2], e = q[3];
+            return fma(fma(fma(fma(fma(fma(fma(e.y, t, e.x), t, d.y), t, d.x), t, b.y), t, b.x), t, a.y), t, a.x);
+        };
+        const double2* q = tab + (ENERGY ? 8 : 4) * idx;
+        cf = horner(q);
+        if (ENERGY) cu = horner(q + 4);
     } else {
-        double ga = exp(-r2 * g.a[n - 1]);  // g_{m+2}
-        double gb = exp(-r2 * g.a[n - 2]);  // g_{m+1}
-        fsum = fma(g.fw[n - 2], gb, g.fw[n - 1] * ga);
-        if (ENERGY) esum = fma(g.ew[n - 2], gb, g.ew[n - 1] * ga);
-        for (int m = n - 3; m >= 0; --m) {
-            const double gm = ga * ga;
-            ga = gb;
-            gb = gm;
+        const SogCoef& g = *gp;
+        double fsum = 0.0, esum = 0.0;
+        for (int m = 0; m < g.n_exp; ++m) {
+            const double gm = exp(-r2 * g.a[m]);
             fsum = fma(g.fw[m], gm, fsum);
             if (ENERGY) esum = fma(g.ew[m], gm, esum);
         }
-    }
-    if (g.n_poly > 0) {
-        double pf = g.pc[g.n_poly - 1];
-        double pe = g.pd[g.n_poly - 1];
-        for (int k = g.n_poly - 2; k >= 0; --k) {
+        double pf = 0.0, pe = 0.0;
+        for (int k = g.n_poly - 1; k >= 0; --k) {
             pf = fma(pf, r2, g.pc[k]);
             if (ENERGY) pe = fma(pe, r2, g.pd[k]);
         }
-        fsum += pf;
-        if (ENERGY) esum += pe;
+        cf = ir2 * ir - (fsum + pf);
+        if (ENERGY) cu = ir - (esum + pe);
     }
     const double rep = c.A * exp((c.sig - r) * c.irho);
     const double ir6 = ir2 * ir2 * ir2;
     const double ir8 = ir6 * ir2;
-    const double f = c.qq * (ir2 * ir - fsum) + rep * c.irho * ir - 6.0 * c.C * ir8 - 8.0 * c.D * ir8 * ir2;
-    if (ENERGY) u = c.qq * (ir - esum) + rep - c.C * ir6 - c.D * ir8;
+    const double f = c.qq * cf + rep * c.irho * ir - 6.0 * c.C * ir8 - 8.0 * c.D * ir8 * ir2;
+    if (ENERGY) u = c.qq * cu + rep - c.C * ir6 - c.D * ir8;
     return f;
 }
 
@@ -1121,7 +1116,7 @@ __device__ inline double pair_scalar_f64(const PairCoef& c, const SogCoef& g, do
 // a melt) every narrow Gaussian is evaluated by its own exponential.  The
 // BMH terms are evaluated directly.
 template <bool ENERGY>
-__device__ inline float pair_scalar_f32(const PairCoefF& c, const SogCoefF& g, const float4* tab, int tab_lo,
+__device__ inline float pair_scalar_f32(const PairCoefF& c, const SogCoefF* gp, const float4* tab, int tab_lo,
                                         int tab_n, float r2, float& u)
 {
     const float ir = __frsqrt_rn(r2);
@@ -1139,6 +1134,7 @@ __device__ inline float pair_scalar_f32(const PairCoefF& c, const SogCoefF& g, c
             cu = fmaf(fmaf(fmaf(b.w, t, b.z), t, b.y), t, b.x);
         }
     } else {
+        const SogCoefF& g = *gp;
         float fsum = 0.f, esum = 0.f;
         for (int m = 0; m < g.n_exp; ++m) {
             const float gm = __expf(-r2 * g.a[m]);
@@ -1177,9 +1173,9 @@ struct FloydMask {
         const int words = (n + 31) >> 5;
         for (int w = 0; w < words; ++w) m[w * stride] = 0u;
     }
-    __device__ int step(PhiloxStream& st, int jj)
+    __device__ int step(PhiloxStream& st, int jj) { return take(st.bounded((uint32_t)jj + 1u), jj); }
+    __device__ int take(uint32_t t, int jj)
     {
-        const uint32_t t = st.bounded((uint32_t)jj + 1u);
         const uint32_t wt = m[(t >> 5) * stride];
         int e = (int)t;
         if ((wt >> (t & 31)) & 1u) e = jj;
@@ -1188,52 +1184,104 @@ struct FloydMask {
     }
 };
 
-// Adds one pair's force f r_ij to F and, with energies, half its energy to
-// U and half of r_ij (x) f r_ij to the virial W (xx, yy, zz, xy, xz, yz).
+// Sums over some of an atom's pairs: force F, energy U (half of each pair's)
+// and, with energies, the virial W, half of r_ij (x) f r_ij (xx, yy, zz, xy,
+// xz, yz).
 template <bool ENERGY>
-__device__ inline void add_pair(double f, double uu, double dx, double dy, double dz, double& Fx, double& Fy,
-                                double& Fz, double& U, double* W)
-{
-    Fx = fma(f, dx, Fx);
-    Fy = fma(f, dy, Fy);
-    Fz = fma(f, dz, Fz);
-    if (ENERGY) {
-        U += 0.5 * uu;
-        const double hx = 0.5 * f * dx, hy = 0.5 * f * dy;
-        W[0] = fma(hx, dx, W[0]);
-        W[1] = fma(hy, dy, W[1]);
-        W[2] = fma(0.5 * f * dz, dz, W[2]);
-        W[3] = fma(hx, dy, W[3]);
-        W[4] = fma(hx, dz, W[4]);
-        W[5] = fma(hy, dz, W[5]);
+struct PairSum {
+    static constexpr int N = ENERGY ? 10 : 3;  // F, then U and W
+    double v[N];
+    __device__ void clear()
+    {
+#pragma unroll
+        for (int c = 0; c < N; ++c) v[c] = 0.0;
     }
+    __device__ void add(double f, double uu, double dx, double dy, double dz)
+    {
+        v[0] = fma(f, dx, v[0]);
+        v[1] = fma(f, dy, v[1]);
+        v[2] = fma(f, dz, v[2]);
+        if constexpr (ENERGY) {
+            v[3] += 0.5 * uu;
+            const double hx = 0.5 * f * dx, hy = 0.5 * f * dy;
+            v[4] = fma(hx, dx, v[4]);
+            v[5] = fma(hy, dy, v[5]);
+            v[6] = fma(0.5 * f * dz, dz, v[6]);
+            v[7] = fma(hx, dy, v[7]);
+            v[8] = fma(hx, dz, v[8]);
+            v[9] = fma(hy, dz, v[9]);
+        }
+    }
+};
+
+// Keeps the compiler from moving a wavefront's LDS accesses across (the
+// hardware completes them in order).
+__device__ inline void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
-// Pair forces of A atoms per workgroup (A = blockDim.x / 2): the first A
-// threads (whole wavefronts) take the core lists, the other A the shell
-// batches of the same atoms, so twice as many independent gather chains are
-// in flight and no wavefront diverges between the two loops.  The shell
-// thread adds its reweighted sum to the core sum passed through LDS, in the
-// same order as one thread doing both.
-template <bool MIXED, bool ENERGY, int J, int KU>
-__global__ __launch_bounds__(2 * kBlock) void k_pair(RB_ARGS, SogCoef g, SogCoefF gf, NearTab nt)
+constexpr int kPairGroup = 4;  // list entries whose sums are formed together, then added in list order
+constexpr int kDrawMax = 64;   // largest batch drawn by several lanes together
+
+// Pair forces.  Half of a workgroup's threads (whole wavefronts) take the core
+// lists, the other half the shell batches of the same atoms, so no wavefront
+// diverges between the two loops and twice as many gather chains are in
+// flight.  LPA lanes of each half share an atom: with one the kernel is bound
+// by vector-memory addressing (mixed) or FP64 issue, but a small system's
+// wavefronts are too few, and each is a chain of dependent loads and
+// evaluations; with more lanes the chain is 1/LPA as long (pair_lanes_for).  An atom's pairs are summed in groups of kPairGroup list
+// entries, the groups added in list order, whatever LPA, so the result does
+// not depend on it.  The shell sum, reweighted, is added to the core sum
+// passed through LDS.
+// LPA = 1: blockDim.x / 2 atoms per workgroup; else 64.
+template <bool MIXED, bool ENERGY, int KU, int LPA>
+__global__ __launch_bounds__(LPA == 1 ? 2 * kBlock : 128 * LPA) void k_pair(RB_ARGS, NearTab nt)
 {
+    static_assert(KU % kPairGroup == 0 && (LPA == 1 || KU == kPairGroup), "whole groups per fetch");
     RB_SYS(xcd_block(blockIdx.x, gridDim.x))
-    // dynamic LDS, sized by the launch: the near-field table (mixed form; F
-    // coefficients, with energies also U), the core lanes' sums handed to the
-    // shell lanes (F, and with energies u and the virial: 4 or 10 per atom),
-    // then the Floyd masks of the per-evaluation draw.  Kept small: the
-    // kernel waits on neighbour gathers, so resident waves are what counts.
+    // dynamic LDS, sized by the launch: the near-field table (F coefficients,
+    // with energies also U), the sums handed to the
+    // final lanes (the core half's, and with LPA > 1 the shell half's and its
+    // weight), then the Floyd masks of the per-evaluation draw, and with LPA >
+    // 1 the drawn ranks.  Kept small: the kernel waits on neighbour gathers,
+    // so resident waves are what counts.
     extern __shared__ float4 dyn_sm[];
-    const int tab_vecs = MIXED ? nt.n * (ENERGY ? 2 : 1) : 0;
-    const int A = blockDim.x >> 1;
-    constexpr int kXch = ENERGY ? 10 : 4;
+    using Sum = PairSum<ENERGY>;
+    constexpr int N = Sum::N;
+    constexpr int kVecs = MIXED ? 1 : 4;  // float4s of one interval's F (or U) coefficients
+    const int tab_vecs = nt.n * kVecs * (ENERGY ? 2 : 1);
+    const int A = LPA == 1 ? blockDim.x >> 1 : 64;
     float4* tab = dyn_sm;
-    double* xch = reinterpret_cast<double*>(dyn_sm + tab_vecs);  // [kXch][A]
-    uint32_t* mask_sm = reinterpret_cast<uint32_t*>(xch + kXch * A);
-    if (MIXED) {
+    double* xch = reinterpret_cast<double*>(dyn_sm + tab_vecs);  // [N][A], LPA > 1: [2 N + 1][A]
+    uint32_t* mask_sm = reinterpret_cast<uint32_t*>(xch + (LPA == 1 ? N : 2 * N + 1) * A);
+    uint16_t* drawn = reinterpret_cast<uint16_t*>(mask_sm + ((s.cap_cand + 31) >> 5) * A);  // [p_r][A]
+    const bool shell = (int)threadIdx.x >= A * LPA;  // uniform per wavefront (A is a multiple of 64)
+    const int tt = shell ? threadIdx.x - A * LPA : threadIdx.x;
+    const int ta = tt / LPA, sub = tt % LPA;
+    const int i = lb * A + ta;
+    // What the lane's list walk starts from, read before the tables are staged
+    // so the two latencies overlap: the atom's record, its list length, and in
+    // the mixed form the first entries of a tile row (any entry below the row's
+    // capacity holds an atom index; the FP64 form has no registers for them).
+    const int ic = min(i, s.n - 1);
+    const double4 Pi = MIXED ? make_double4(0.0, 0.0, 0.0, 0.0) : s.p[ic];
+    const uint4 Ui = MIXED ? s.ufix[ic] : make_uint4(0u, 0u, 0u, 0u);
+    const int list_n = shell ? min(s.cand_cnt[ic], s.cap_cand - 1) : min(s.core_cnt[ic], s.cap_core - 1);
+    const uint32_t atom_id = shell ? (uint32_t)s.id[ic] : 0u;
+    const bool tiled = !shell || s.shell_stored;  // the list is a tile row (core list, stored batch)
+    const int tile_cap = shell ? s.p_r : s.cap_core;
+    const int32_t* tile = (shell ? s.bat_idx : s.core_idx) + (size_t)(ic >> 6) * tile_cap * 64 + (ic & 63);
+    int first[KU];
+#pragma unroll
+    for (int u = 0; u < KU; ++u)
+        first[u] = (MIXED && tiled && sub * KU + u < tile_cap) ? __builtin_nontemporal_load(tile + (size_t)(sub * KU + u) * 64) : 0;
+    {
+        // intervals hold F's vectors, then U's
         const float4* src = glob(nt.coef);
-        for (int t = threadIdx.x; t < tab_vecs; t += blockDim.x) tab[t] = ENERGY ? src[t] : src[2 * t];
+        for (int t = threadIdx.x; t < tab_vecs; t += blockDim.x)
+            tab[t] = ENERGY ? src[t] : src[2 * kVecs * (t / kVecs) + t % kVecs];
     }
     // pair coefficients: FP64 for the FP64 form; the mixed form keeps FP32
     // copies and only the FP64 core radii (the core/shell test stays FP64)
@@ -1251,12 +1299,9 @@ __global__ __launch_bounds__(2 * kBlock) void k_pair(RB_ARGS, SogCoef g, SogCoef
     }
     __syncthreads();
 
-    const bool shell = threadIdx.x >= A;  // uniform per wavefront (A is a multiple of 64)
-    const int ta = shell ? threadIdx.x - A : threadIdx.x;
-    const int i = lb * A + ta;
-    double Fx = 0.0, Fy = 0.0, Fz = 0.0, Uc = 0.0, Us = 0.0;
-    double Sx = 0.0, Sy = 0.0, Sz = 0.0, Su = 0.0, wgt = 1.0;
-    double Wv[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // this lane's virial (core or shell sum)
+    Sum tot;  // this atom's core or shell sum (each of its LPA lanes)
+    tot.clear();
+    double wgt = 1.0;
     // A wavefront whose atoms all lie at least the list radius plus a skin
     // inside every face (inner_lo <= x <= inner_hi) has no list neighbour
     // across the box edge: each stored difference already is the minimum
@@ -1265,7 +1310,6 @@ __global__ __launch_bounds__(2 * kBlock) void k_pair(RB_ARGS, SogCoef g, SogCoef
     // whose differences wrap by themselves).
     bool inner = true;
     if (!MIXED && i < s.n) {
-        const double4 Pi = s.p[i];
         inner = Pi.x >= s.inner_lo[0] && Pi.x <= s.inner_hi[0] && Pi.y >= s.inner_lo[1] && Pi.y <= s.inner_hi[1] &&
                 Pi.z >= s.inner_lo[2] && Pi.z <= s.inner_hi[2];
     }
@@ -1274,10 +1318,7 @@ __global__ __launch_bounds__(2 * kBlock) void k_pair(RB_ARGS, SogCoef g, SogCoef
     constexpr bool INNER = decltype(inner_tag)::value;
     auto mi = [&](double d, int a) { return INNER ? d : min_image(d, s.L[a], s.invL[a]); };
     if (i < s.n) {
-        const double4 Pi = s.p[i];
-        const double xi = Pi.x, yi = Pi.y, zi = Pi.z;
-        const int ti = s.type[i];
-        const uint4 Ui = MIXED ? s.ufix[i] : make_uint4(0u, 0u, 0u, 0u);
+        const int ti = MIXED ? (int)Ui.w : (int)Pi.w;
         // fixed-point units per axis (L 2^-32, exact)
         const double ux = s.L[0] * 0x1p-32, uy = s.L[1] * 0x1p-32, uz = s.L[2] * 0x1p-32;
         // pair force scalar for r2 of species pair (ti, tj)
@@ -1285,11 +1326,11 @@ __global__ __launch_bounds__(2 * kBlock) void k_pair(RB_ARGS, SogCoef g, SogCoef
             const int t = ti * S + tj;
             if (MIXED) {
                 float uf = 0.f;
-                const double f = (double)pair_scalar_f32<ENERGY>(pcf[t], gf, tab, nt.lo, nt.n, (float)r2, uf);
+                const double f = (double)pair_scalar_f32<ENERGY>(pcf[t], nt.g32, tab, nt.lo, nt.n, (float)r2, uf);
                 u = uf;
                 return f;
             }
-            return pair_scalar_f64<J, ENERGY>(pc[t], g, r2, u);
+            return pair_scalar_f64<ENERGY>(pc[t], nt.g64, reinterpret_cast<const double2*>(tab), nt.lo, nt.n, r2, u);
         };
         // Neighbours jj[0..kU) (entries k0.. of a list of cnt; padding past
         // cnt) are fetched before any arithmetic, so the gathers overlap; the
@@ -1300,9 +1341,22 @@ __global__ __launch_bounds__(2 * kBlock) void k_pair(RB_ARGS, SogCoef g, SogCoef
         // record differences give r^2 within fix_guard of the FP64 value, and
         // the rare pair that close to a cutoff is decided (and evaluated)
         // from the FP64 positions, so the pair set is the FP64 one.
-        auto visit = [&](auto shell_tag, const int* jj, int k0, int cnt, double& Ax, double& Ay, double& Az,
-                         double& Au) {
+        auto visit = [&](auto shell_tag, const int* jj, int k0, int cnt) {
             constexpr bool SH = decltype(shell_tag)::value;
+            Sum grp;
+            grp.clear();
+            auto fold = [&] {
+                if (LPA == 1) {
+#pragma unroll
+                    for (int c = 0; c < N; ++c) tot.v[c] += grp.v[c];
+                } else {
+                    // the groups of the atom's lanes, in list order
+#pragma unroll
+                    for (int q = 0; q < LPA; ++q)
+#pragma unroll
+                        for (int c = 0; c < N; ++c) tot.v[c] += __shfl(grp.v[c], q, LPA);
+                }
+            };
             if (MIXED) {
                 uint4 Q[KU];
 #pragma unroll
@@ -1310,6 +1364,10 @@ __global__ __launch_bounds__(2 * kBlock) void k_pair(RB_ARGS, SogCoef g, SogCoef
 #pragma unroll
                 for (int u = 0; u < KU; ++u) {
                     if (k0 + u >= cnt) break;
+                    if (u > 0 && u % kPairGroup == 0) {
+                        fold();
+                        grp.clear();
+                    }
                     double dx = (double)(int32_t)(Ui.x - Q[u].x) * ux;
                     double dy = (double)(int32_t)(Ui.y - Q[u].y) * uy;
                     double dz = (double)(int32_t)(Ui.z - Q[u].z) * uz;
@@ -1317,16 +1375,16 @@ __global__ __launch_bounds__(2 * kBlock) void k_pair(RB_ARGS, SogCoef g, SogCoef
                     const int tj = (int)Q[u].w;
                     const double rc2 = s.species_cut ? rc2s[ti * S + tj] : s.rc2;
                     if (fabs(r2 - rc2) <= s.fix_guard || (SH && fabs(r2 - s.rs2) <= s.fix_guard)) {
-                        const double4 Q64 = s.p[jj[u]];
-                        dx = min_image(xi - Q64.x, s.L[0], s.invL[0]);
-                        dy = min_image(yi - Q64.y, s.L[1], s.invL[1]);
-                        dz = min_image(zi - Q64.z, s.L[2], s.invL[2]);
+                        const double4 P64 = s.p[i], Q64 = s.p[jj[u]];
+                        dx = min_image(P64.x - Q64.x, s.L[0], s.invL[0]);
+                        dy = min_image(P64.y - Q64.y, s.L[1], s.invL[1]);
+                        dz = min_image(P64.z - Q64.z, s.L[2], s.invL[2]);
                         r2 = (dx * dx + dy * dy) + dz * dz;
                     }
                     if (SH ? (r2 >= rc2 && r2 < s.rs2) : (r2 < rc2)) {
                         double uu = 0.0;
                         const double f = pair_f(tj, r2, uu);
-                        add_pair<ENERGY>(f, uu, dx, dy, dz, Ax, Ay, Az, Au, Wv);
+                        grp.add(f, uu, dx, dy, dz);
                     }
                 }
             } else {
@@ -1343,67 +1401,112 @@ __global__ __launch_bounds__(2 * kBlock) void k_pair(RB_ARGS, SogCoef g, SogCoef
 #pragma unroll
                 for (int u = 0; u < KU; ++u) {
                     if (k0 + u >= cnt) break;
-                    const double dx = mi(xi - X[u], 0);
-                    const double dy = mi(yi - Y[u], 1);
-                    const double dz = mi(zi - Z[u], 2);
+                    if (u > 0 && u % kPairGroup == 0) {
+                        fold();
+                        grp.clear();
+                    }
+                    const double dx = mi(Pi.x - X[u], 0);
+                    const double dy = mi(Pi.y - Y[u], 1);
+                    const double dz = mi(Pi.z - Z[u], 2);
                     const double r2 = (dx * dx + dy * dy) + dz * dz;
                     const double rc2 = s.species_cut ? rc2s[ti * S + T[u]] : s.rc2;
                     if (SH ? (r2 >= rc2 && r2 < s.rs2) : (r2 < rc2)) {
                         double uu = 0.0;
                         const double f = pair_f(T[u], r2, uu);
-                        add_pair<ENERGY>(f, uu, dx, dy, dz, Ax, Ay, Az, Au, Wv);
+                        grp.add(f, uu, dx, dy, dz);
                     }
                 }
             }
+            fold();
         };
-        // Core-list lines are read once: non-temporal loads keep them from
-        // evicting the positions that neighbours re-read (a candidate row is
-        // re-read by its own lane, so it stays cached).
+        // Tile rows are read once: non-temporal loads keep them from evicting
+        // the positions that neighbours re-read (a candidate row is re-read by
+        // its own lane, so it stays cached).  Lane `sub` takes every LPA-th
+        // group.
         constexpr int kU = KU;
-        if (!shell) {
-            // core sum, eq. (24)
-            const int nc = min(s.core_cnt[i], s.cap_core - 1);
-            const int32_t* ctile = s.core_idx + (size_t)(i >> 6) * s.cap_core * 64 + (i & 63);
-            for (int k0 = 0; k0 < nc; k0 += kU) {
+        constexpr int kRound = kU * LPA;
+        auto walk_tile = [&](auto shell_tag, int cnt) {
+            for (int r0 = 0; r0 < cnt; r0 += kRound) {
+                const int k0 = r0 + sub * kU;
                 int jj[kU];
 #pragma unroll
-                for (int u = 0; u < kU; ++u)
-                    jj[u] = (k0 + u < nc) ? __builtin_nontemporal_load(ctile + (size_t)(k0 + u) * 64) : i;
-                visit(std::false_type{}, jj, k0, nc, Fx, Fy, Fz, Uc);
+                for (int u = 0; u < kU; ++u) {
+                    jj[u] = i;
+                    if (k0 + u < cnt)
+                        jj[u] = (MIXED && r0 == 0) ? first[u] : __builtin_nontemporal_load(tile + (size_t)(k0 + u) * 64);
+                }
+                visit(shell_tag, jj, k0, cnt);
             }
+        };
+        if (!shell) {
+            walk_tile(std::false_type{}, list_n);  // core sum, eq. (24)
         } else if (s.shell_stored) {
             // shell batch of eq. (25) drawn at the list build: a tile row per
             // atom, read coalesced like the core list
-            const int n = min(s.cand_cnt[i], s.cap_cand - 1);
+            const int n = list_n;
             const bool take_all = n <= s.p_r;
-            const int cnt = take_all ? n : s.p_r;
             wgt = take_all ? 1.0 : (double)n / (double)s.p_r;
-            const int32_t* btile = s.bat_idx + (size_t)(i >> 6) * s.p_r * 64 + (i & 63);
-            for (int k0 = 0; k0 < cnt; k0 += kU) {
-                int jj[kU];
-#pragma unroll
-                for (int u = 0; u < kU; ++u)
-                    jj[u] = (k0 + u < cnt) ? __builtin_nontemporal_load(btile + (size_t)(k0 + u) * 64) : i;
-                visit(std::true_type{}, jj, k0, cnt, Sx, Sy, Sz, Su);
-            }
+            walk_tile(std::true_type{}, take_all ? n : s.p_r);
         } else {
             // shell batch, eq. (25)
-            const int n = min(s.cand_cnt[i], s.cap_cand - 1);
+            const int n = list_n;
             const int32_t* crow = s.cand_idx + (size_t)i * s.cap_cand;
             const bool take_all = s.p_r <= 0 || n <= s.p_r;
             const int cnt = take_all ? n : s.p_r;
             wgt = take_all ? 1.0 : (double)n / (double)s.p_r;
             FloydMask fm{mask_sm + ta, A};
-            PhiloxStream st(s.seed, (uint32_t)s.id[i], (uint32_t)s.sc->eval, kTagShell, s.replica);
+            const uint32_t ev = (uint32_t)s.sc->eval;
             if (!take_all) {
                 // draw the whole batch first, then visit the ranks in ascending
                 // order: the candidate row is swept once, line by line
-                fm.clear(n);
-                for (int k = 0; k < cnt; ++k) fm.step(st, n - s.p_r + k);
+                PhiloxStream st(s.seed, atom_id, ev, kTagShell, s.replica);
+                if (LPA == 1) {
+                    fm.clear(n);
+                    for (int k = 0; k < cnt; ++k) fm.step(st, n - s.p_r + k);
+                } else {
+                    // The stream's blocks of four words are dealt to the atom's
+                    // lanes; without a rejection word k gives draw k.  A
+                    // rejection (one in 10^7 draws) moves the words on: then,
+                    // and for a large batch, one lane draws in order.
+                    const bool shared = cnt <= kDrawMax;
+                    bool rejected = !shared;
+                    for (int b = sub; shared && 4 * b < cnt; b += LPA) {
+                        uint32_t w[4] = {st.c0, st.c1, st.c2, (uint32_t)b};
+                        philox4x32_10(w[0], w[1], w[2], w[3], st.k0, st.k1);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const int k = 4 * b + q;
+                            if (k >= cnt) break;
+                            const uint32_t range = (uint32_t)(n - s.p_r + k) + 1u;
+                            const uint64_t m = (uint64_t)w[q] * range;
+                            if ((uint32_t)m < range) rejected = rejected || (uint32_t)m < (0u - range) % range;
+                            drawn[k * A + ta] = (uint16_t)(m >> 32);
+                        }
+                    }
+                    for (int w = sub; w < (n + 31) >> 5; w += LPA) fm.m[w * fm.stride] = 0u;
+                    const uint64_t group = ((1ull << LPA) - 1ull) << (threadIdx.x & 63 & ~(LPA - 1));
+                    rejected = (__ballot(rejected) & group) != 0;
+                    wave_lds_fence();
+                    if (sub == 0) {
+                        if (rejected)
+                            for (int k = 0; k < cnt; ++k) fm.step(st, n - s.p_r + k);
+                        else
+                            for (int k = 0; k < cnt; ++k) fm.take(drawn[k * A + ta], n - s.p_r + k);
+                    }
+                    wave_lds_fence();
+                }
             }
             int w_cur = 0;  // ascending walk over the set bits of the mask
             uint32_t m_cur = take_all ? 0u : fm.m[0];
-            for (int k0 = 0; k0 < cnt; k0 += kU) {
+            auto skip = [&](int c) {
+                for (int p; c >= (p = __popc(m_cur)); c -= p) m_cur = fm.m[(++w_cur) * fm.stride];
+                for (; c > 0; --c) m_cur &= m_cur - 1u;
+            };
+            for (int r0 = 0; r0 < cnt; r0 += kRound) {
+                const int k0 = r0 + sub * kU;
+                // past the groups of the lanes before this one, or of the
+                // others since this lane's last
+                if (LPA > 1 && !take_all && k0 < cnt) skip(r0 == 0 ? sub * kU : (LPA - 1) * kU);
                 int jj[kU];
 #pragma unroll
                 for (int u = 0; u < kU; ++u) {
@@ -1419,7 +1522,7 @@ __global__ __launch_bounds__(2 * kBlock) void k_pair(RB_ARGS, SogCoef g, SogCoef
                     }
                     jj[u] = (k0 + u < cnt) ? crow[e] : i;
                 }
-                visit(std::true_type{}, jj, k0, cnt, Sx, Sy, Sz, Su);
+                visit(std::true_type{}, jj, k0, cnt);
             }
         }
     }
@@ -1428,42 +1531,51 @@ __global__ __launch_bounds__(2 * kBlock) void k_pair(RB_ARGS, SogCoef g, SogCoef
         body(std::true_type{});
     else
         body(std::false_type{});
-    if (!shell) {
-        xch[0 * A + ta] = Fx;
-        xch[1 * A + ta] = Fy;
-        xch[2 * A + ta] = Fz;
-        xch[3 * A + ta] = Uc;
-        if (ENERGY)
-            for (int c = 0; c < 6; ++c) xch[(4 + c) * A + ta] = Wv[c];
+    if (!shell && sub == 0)
+#pragma unroll
+        for (int c = 0; c < N; ++c) xch[c * A + ta] = tot.v[c];
+    if (LPA > 1 && shell && sub == 0) {
+#pragma unroll
+        for (int c = 0; c < N; ++c) xch[(N + c) * A + ta] = tot.v[c];
+        xch[2 * N * A + ta] = wgt;
     }
     __syncthreads();
-    if (shell) {
-        if (i < s.n) {
-            Fx = fma(wgt, Sx, xch[0 * A + ta]);
-            Fy = fma(wgt, Sy, xch[1 * A + ta]);
-            Fz = fma(wgt, Sz, xch[2 * A + ta]);
-            Uc = xch[3 * A + ta];
-            if (ENERGY) {
-                Us = wgt * Su;
-                for (int c = 0; c < 6; ++c) Wv[c] = fma(wgt, Wv[c], xch[(4 + c) * A + ta]);
-            }
-            __builtin_nontemporal_store(Fx, s.fsx + i);
-            __builtin_nontemporal_store(Fy, s.fsy + i);
-            __builtin_nontemporal_store(Fz, s.fsz + i);
-            if (ENERGY) {
-                // the atom's shares of the short-range energy and virial
-                s.at_ew[2 * (size_t)i] = make_double4(Uc + Us, Wv[0], Wv[1], Wv[2]);
-                s.at_ew[2 * (size_t)i + 1] = make_double4(Wv[3], Wv[4], Wv[5], 0.0);
-            }
-        }
-        wave_partial(Fx, i, s.n, s.pair_part, kPairPart, 0);
-        wave_partial(Fy, i, s.n, s.pair_part, kPairPart, 1);
-        wave_partial(Fz, i, s.n, s.pair_part, kPairPart, 2);
-        wave_partial(Uc, i, s.n, s.pair_part, kPairPart, 3);
-        wave_partial(Us, i, s.n, s.pair_part, kPairPart, 4);
-        if (ENERGY)
-            for (int c = 0; c < 6; ++c) wave_partial(Wv[c], i, s.n, s.vir_part, kVirPart, c);
+    // one lane per atom again: the shell half's, its first wavefront's with
+    // LPA > 1
+    if (!shell || tt >= A) return;
+    const int o = lb * A + tt;
+    if (LPA > 1) {
+#pragma unroll
+        for (int c = 0; c < N; ++c) tot.v[c] = xch[(N + c) * A + tt];
+        wgt = xch[2 * N * A + tt];
     }
+    double Fx = 0.0, Fy = 0.0, Fz = 0.0, Uc = 0.0, Us = 0.0;
+    double Wv[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (o < s.n) {
+        Fx = fma(wgt, tot.v[0], xch[0 * A + tt]);
+        Fy = fma(wgt, tot.v[1], xch[1 * A + tt]);
+        Fz = fma(wgt, tot.v[2], xch[2 * A + tt]);
+        if constexpr (ENERGY) {
+            Uc = xch[3 * A + tt];
+            Us = wgt * tot.v[3];
+            for (int c = 0; c < 6; ++c) Wv[c] = fma(wgt, tot.v[4 + c], xch[(4 + c) * A + tt]);
+        }
+        __builtin_nontemporal_store(Fx, s.fsx + o);
+        __builtin_nontemporal_store(Fy, s.fsy + o);
+        __builtin_nontemporal_store(Fz, s.fsz + o);
+        if (ENERGY) {
+            // the atom's shares of the short-range energy and virial
+            s.at_ew[2 * (size_t)o] = make_double4(Uc + Us, Wv[0], Wv[1], Wv[2]);
+            s.at_ew[2 * (size_t)o + 1] = make_double4(Wv[3], Wv[4], Wv[5], 0.0);
+        }
+    }
+    wave_partial(Fx, o, s.n, s.pair_part, kPairPart, 0);
+    wave_partial(Fy, o, s.n, s.pair_part, kPairPart, 1);
+    wave_partial(Fz, o, s.n, s.pair_part, kPairPart, 2);
+    wave_partial(Uc, o, s.n, s.pair_part, kPairPart, 3);
+    wave_partial(Us, o, s.n, s.pair_part, kPairPart, 4);
+    if (ENERGY)
+        for (int c = 0; c < 6; ++c) wave_partial(Wv[c], o, s.n, s.vir_part, kVirPart, c);
 }
 
 // Export of the shell ranks drawn by the pair kernel (same selection code).
@@ -2700,24 +2812,6 @@ __global__ void k_refuse_pos(DeviceScalars* sc, int R)
 
 inline int blocks_for(int n, int b) { return (n + b - 1) / b; }
 
-SogCoefF to_f32(const SogCoef& g)
-{
-    SogCoefF f{};
-    f.n_exp = g.n_exp;
-    f.chain = g.chain;
-    f.n_poly = g.n_poly;
-    for (int m = 0; m < kMaxExplicit; ++m) {
-        f.a[m] = (float)g.a[m];
-        f.fw[m] = (float)g.fw[m];
-        f.ew[m] = (float)g.ew[m];
-    }
-    for (int n = 0; n < kMaxPoly; ++n) {
-        f.pc[n] = (float)g.pc[n];
-        f.pd[n] = (float)g.pd[n];
-    }
-    return f;
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------- launchers
@@ -2809,44 +2903,46 @@ void launch_ksample(const Plan& P, hipStream_t st)
     if (P.modes64.blocks > 0) k_ksample<<<P.modes1.blocks, 64, 0, st>>>(RB_MAP(modes1), P.kd);
 }
 
-template <int KU>
-void launch_pair_ku(const Plan& P, const SogCoef& g, const SogCoefF& gf, bool mixed, bool energy, hipStream_t st)
+template <int KU, int LPA>
+void launch_pair_ku(const Plan& P, bool mixed, bool energy, hipStream_t st)
 {
-    const int bs = P.tune.pair_block;  // atoms per workgroup; twice as many threads
-    // near-field table (mixed), then the Floyd masks of the per-evaluation
-    // batch draw (none for a stored batch)
-    const size_t tab = mixed ? sizeof(float4) * (size_t)P.near.n * (energy ? 2 : 1) : 0;
-    const size_t xch = sizeof(double) * (energy ? 10 : 4) * (size_t)bs;
-    const size_t sm = tab + xch + (P.stored ? 0 : sizeof(uint32_t) * (size_t)((P.cap_cand + 31) / 32) * bs);
+    const int A = LPA == 1 ? P.tune.pair_block : 64;  // atoms per workgroup
+    // near-field table, the sums handed over, then the Floyd masks of the
+    // per-evaluation batch draw (none for a stored batch) and the drawn ranks
+    // (LPA > 1)
+    const size_t tab = sizeof(float4) * (mixed ? 1 : 4) * (size_t)P.near.n * (energy ? 2 : 1);
+    const int n_sum = energy ? PairSum<true>::N : PairSum<false>::N;
+    const size_t xch = sizeof(double) * (LPA == 1 ? n_sum : 2 * n_sum + 1) * A;
+    const size_t masks = P.stored ? 0 : sizeof(uint32_t) * (size_t)((P.cap_cand + 31) / 32) * A;
+    const size_t drawn = (P.stored || LPA == 1) ? 0 : sizeof(uint16_t) * kDrawMax * A;
+    const size_t sm = tab + xch + masks + drawn;
     const int nb = P.pair_atoms.blocks;
-#define RB_PAIR(M, E, J) k_pair<M, E, J, KU><<<nb, 2 * bs, sm, st>>>(RB_MAP(pair_atoms), g, gf, P.near)
+#define RB_PAIR(M, E) k_pair<M, E, KU, LPA><<<nb, 2 * LPA * A, sm, st>>>(RB_MAP(pair_atoms), P.near)
     if (mixed) {
         if (energy)
-            RB_PAIR(true, true, 1);
+            RB_PAIR(true, true);
         else
-            RB_PAIR(true, false, 1);
-    } else if (g.chain == 1) {
-        if (energy)
-            RB_PAIR(false, true, 1);
-        else
-            RB_PAIR(false, false, 1);
+            RB_PAIR(true, false);
     } else {
         if (energy)
-            RB_PAIR(false, true, 2);
+            RB_PAIR(false, true);
         else
-            RB_PAIR(false, false, 2);
+            RB_PAIR(false, false);
     }
 #undef RB_PAIR
 }
 
-void launch_pair(const Plan& P, const SogCoef& g, bool mixed, bool energy, hipStream_t st)
+void launch_pair(const Plan& P, bool mixed, bool energy, hipStream_t st)
 {
     if (P.pair_atoms.blocks <= 0) return;
-    const SogCoefF gf = to_f32(g);
-    if (P.tune.pair_ku == 8)
-        launch_pair_ku<8>(P, g, gf, mixed, energy, st);
+    if (P.pair_lanes == 4)
+        launch_pair_ku<4, 4>(P, mixed, energy, st);
+    else if (P.pair_lanes == 2)
+        launch_pair_ku<4, 2>(P, mixed, energy, st);
+    else if (P.tune.pair_ku == 8)
+        launch_pair_ku<8, 1>(P, mixed, energy, st);
     else
-        launch_pair_ku<4>(P, g, gf, mixed, energy, st);
+        launch_pair_ku<4, 1>(P, mixed, energy, st);
 }
 
 void launch_rho(const Plan& P, bool mixed, hipStream_t st)

@@ -3,6 +3,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "setup.hpp"
 
 namespace rbsog {
 
@@ -166,6 +167,21 @@ constexpr int fin_blocks(int n, int modes)
 // sum m v_a v_b (6), sum (m v^2 / 2) v (3), sum (e_i v + W_i v) (3).
 constexpr int kFluxPart = 12;
 
+// Lanes that share an atom's core list, and its shell batch, in the pair
+// kernel: the more the fewer wavefronts the launch (all systems of a batch) has
+// with one, while that adds wavefronts to SIMDs that have under two (FP64) or
+// four (mixed, fewer registers).  Measured with 1, 2 and 4 lanes, us per
+// evaluation: 512 ions FP64 26 / 18 / 17, mixed 21 / 16 / 14; 32768 FP64 31 /
+// 25 / 26, mixed 26 / 21 / 20; 65536 mixed 28 / 25 / 34; 131072 FP64 45 / 67 /
+// 89, mixed 36 / 42 / 63 (each lane repeats the atom's set-up, and one lane of
+// an atom marks its drawn ranks).
+inline int pair_lanes_for(size_t atom_waves, bool mixed)
+{
+    int lanes = 1;
+    while (lanes < 4 && 2 * atom_waves * 2 * lanes <= (mixed ? 4096u : 2048u)) lanes *= 2;
+    return lanes;
+}
+
 // Split of the k-space force's modes.  Slices double while the system's
 // wavefronts would leave SIMDs with fewer than four and a slice keeps at least
 // 24 modes (a slice's own set-up is worth a few modes); groups on top, for the
@@ -205,13 +221,18 @@ struct Tuning {
     int kf_aux = 1;        // k-space force on the second stream (1) or after the pair kernel (0)
 };
 
-// FP32 near-field table of the mixed pair kernel (built on the host, shared
-// by a batch): interval idx = (bits(r^2) >> 17) - lo, valid below n; per
-// interval two float4: CF and CU cubic coefficients in t = r^2 - start.
+// Near-field table of the pair kernel (built on the host, shared by a batch).
+// FP32 for the mixed form: interval idx = (bits(r^2) >> 17) - lo, valid below
+// n; per interval two float4, the CF and CU cubics in t = r^2 - start.  FP64:
+// idx = (high word of r^2 >> 15) - lo; per interval 8 doubles of CF, then 8 of
+// CU, in t = r^2 - midpoint.  g64 / g32: the split's coefficients, read where
+// r^2 is outside the table.
 struct NearTab {
     const float4* coef = nullptr;
     int lo = 0;
     int n = 0;  // 0: no table, the kernel evaluates the near field directly
+    const SogCoef* g64 = nullptr;
+    const SogCoefF* g32 = nullptr;
 };
 
 // Staging capacities of the per-cell list kernel (atoms of a 27-cell stencil
@@ -228,7 +249,8 @@ struct Plan {
     DeviceScalars* sc = nullptr;  // device array [R] (sys[r].sc == sc + r)
     int R = 0;
     Shape atoms;    // 256-atom blocks of every system
-    Shape pair_atoms;  // tune.pair_block-atom blocks (pair kernel)
+    Shape pair_atoms;  // tune.pair_block-atom blocks, 64-atom ones with pair_lanes > 1 (pair kernel)
+    int pair_lanes = 1;  // lanes that share an atom's lists in the pair kernel (pair_lanes_for)
     Shape kf_atoms;    // kf_threads-thread blocks (k-space force kernel)
     Shape kf_part;     // the mode groups of the systems that have several (local block = group * blocks + block)
     int kf_threads = 256;   // tune.kf_block, or more where a system's slices need it
@@ -275,7 +297,7 @@ void launch_lists(const Plan& P, bool gate, hipStream_t st);
 
 // forces
 void launch_ksample(const Plan& P, hipStream_t st);
-void launch_pair(const Plan& P, const SogCoef& sog, bool mixed, bool energy, hipStream_t st);
+void launch_pair(const Plan& P, bool mixed, bool energy, hipStream_t st);
 void launch_rho(const Plan& P, bool mixed, hipStream_t st);
 void launch_rho_finalize(const Plan& P, bool energy, hipStream_t st);
 // momentum correction and energies; with `energy` also the virial

@@ -291,6 +291,66 @@ void build_near_table(const SogSplit& sp, double r_shell, NearTable* t)
         }
 }
 
+void build_near_table64(const SogCoef& c, double r_shell, NearTable64* t)
+{
+    t->e0 = 0;
+    t->nbin = 0;
+    t->coef.clear();
+    int nb = 1;
+    while (std::ldexp(1.0, t->e0 + nb) <= r_shell * r_shell) ++nb;
+    if (nb > kMaxNearBins) return;
+    t->nbin = nb;
+    using ld = long double;
+    // CF and CU at s: the narrow Gaussians by squaring from J exponentials
+    // (g_m = g_{m+J}^2), the wide ones by their Taylor polynomial
+    auto eval = [&](ld s, ld* f) {
+        ld g[kMaxExplicit], gf = 0, gu = 0;
+        for (int m = c.n_exp - 1; m >= 0; --m) {
+            g[m] = m + c.chain < c.n_exp ? g[m + c.chain] * g[m + c.chain] : std::exp(-s * (ld)c.a[m]);
+            gf += (ld)c.fw[m] * g[m];
+            gu += (ld)c.ew[m] * g[m];
+        }
+        ld pf = 0, pu = 0;
+        for (int k = c.n_poly - 1; k >= 0; --k) {
+            pf = pf * s + (ld)c.pc[k];
+            pu = pu * s + (ld)c.pd[k];
+        }
+        const ld is = 1 / s, rs = std::sqrt(is);
+        f[0] = is * rs - gf - pf;
+        f[1] = rs - gu - pu;
+    };
+    constexpr int D = kNearDeg64 + 1, sub = 1 << kNearBits64;
+    ld node[D], cheb[D][D];  // cheb[k][j]: T_k at node j
+    for (int j = 0; j < D; ++j) {
+        node[j] = std::cos((ld)kPi * (2 * j + 1) / (2 * D));
+        cheb[0][j] = 1;
+        cheb[1][j] = node[j];
+        for (int k = 2; k < D; ++k) cheb[k][j] = 2 * node[j] * cheb[k - 1][j] - cheb[k - 2][j];
+    }
+    ld mono[D][D] = {};  // T_k = sum_i mono[k][i] x^i
+    mono[0][0] = 1;
+    mono[1][1] = 1;
+    for (int k = 2; k < D; ++k)
+        for (int i = 0; i < D; ++i) mono[k][i] = (i > 0 ? 2 * mono[k - 1][i - 1] : 0) - mono[k - 2][i];
+    t->coef.assign((size_t)nb * sub * 2 * D, 0.0);
+    for (int q = 0; q < nb * sub; ++q) {
+        const ld h = std::ldexp((ld)1 / (2 * sub), t->e0 + q / sub);  // half width
+        const ld mid = std::ldexp((ld)1, t->e0 + q / sub) + (2 * (q % sub) + 1) * h;
+        ld f[D][2], poly[2][D] = {};
+        for (int j = 0; j < D; ++j) eval(mid + h * node[j], f[j]);
+        for (int w = 0; w < 2; ++w)
+            for (int k = 0; k < D; ++k) {
+                ld a = 0;
+                for (int j = 0; j < D; ++j) a += f[j][w] * cheb[k][j];
+                a *= (k == 0 ? 1 : 2) / (ld)D;
+                for (int i = 0; i <= k; ++i) poly[w][i] += a * mono[k][i];
+            }
+        ld scale = 1;
+        for (int i = 0; i < D; ++i, scale /= h)
+            for (int w = 0; w < 2; ++w) t->coef[((size_t)q * 2 + w) * D + i] = (double)(poly[w][i] * scale);
+    }
+}
+
 void sog_kspace_terms(const SogSplit& sp, std::vector<double>* c, std::vector<double>* s2)
 {
     c->assign(sp.M + 1, 0.0);

@@ -61,6 +61,18 @@ struct NearTable {
 };
 void build_near_table(const SogSplit& sp, double r_shell, NearTable* t);
 
+// The same kernels for the FP64 form: 32 intervals per binade, degree-7
+// polynomials in t = s - (the interval's midpoint) through the Chebyshev nodes
+// (truncation below 1e-16 of the bare Coulomb kernel), coef[interval][16] =
+// CF c0..c7, CU c0..c7.  c: the FP64 kernel coefficients of the split.
+constexpr int kNearBits64 = 5;
+constexpr int kNearDeg64 = 7;
+struct NearTable64 {
+    int e0 = 0, nbin = 0;
+    std::vector<double> coef;
+};
+void build_near_table64(const SogCoef& c, double r_shell, NearTable64* t);
+
 // Terms of F^ for the device: F^(k) = sum_m c[m] exp(-s2[m] k^2 / 2) with
 // c_m = (2 pi)^{3/2} w_m sigma_m^3 and s2_m = sigma_m^2, m = 0..M.
 void sog_kspace_terms(const SogSplit& sp, std::vector<double>* c, std::vector<double>* s2);
