@@ -116,6 +116,7 @@ struct rbsog_ctx {
     // mean-square displacement: [n_user][3] last positions, then [n_user][3]
     // unwrapped displacements; which systems have a marked origin
     DBuf msd_buf;
+    DBuf obs_buf;  // scratch of the pair histogram and the displacement sums, kept between calls
     std::vector<char> msd_marked;
 
     // phase timing (hot_only: the pair, rho and k-space force phases)
@@ -1902,27 +1903,19 @@ rbsog_status rbsog_msd(rbsog_ctx* ctx, int32_t mark, double* msd)
         require(mark != 0 || ctx->msd_marked[r], RBSOG_E_STATE, "msd: no origin marked for this system");
         const size_t nu = (size_t)std::max(ctx->n_user, 1);
         if (!ctx->msd_buf.p) ctx->msd_buf.alloc(sizeof(double) * 6 * nu);
-        const size_t waves = (size_t)std::max(1, (s.n + 63) / 64);
-        DBuf part;
-        part.alloc(sizeof(double) * 2 * kMaxSpecies * waves);
-        HIP_OK(hipMemsetAsync(part.p, 0, part.bytes, ctx->stream));
+        const int waves = blocks_for(s.n, 64);
+        constexpr int Q = 2 * kMaxSpecies;
+        ctx->obs_buf.reserve(sizeof(double) * Q * ((size_t)waves + 1));
+        double* sums = ctx->obs_buf.as<double>();
         double* last = ctx->msd_buf.as<double>();
-        const Plan P1 = one(ctx, r);
-        launch_msd(P1, last, last + 3 * nu, part.as<double>(), mark != 0, ctx->stream);
+        launch_msd(one(ctx, r), last, last + 3 * nu, sums + Q, waves, s.n_species, sums, mark != 0, ctx->stream);
         HIP_OK(hipGetLastError());
-        std::vector<double> h(2 * kMaxSpecies * waves);
-        HIP_OK(hipMemcpyAsync(h.data(), part.p, part.bytes, hipMemcpyDeviceToHost, ctx->stream));
+        double h[Q];
+        HIP_OK(hipMemcpyAsync(h, sums, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
         HIP_OK(hipStreamSynchronize(ctx->stream));
         if (mark) ctx->msd_marked[r] = 1;
         if (msd)
-            for (int a = 0; a < s.n_species; ++a) {
-                double q = 0.0, n = 0.0;
-                for (size_t w = 0; w < waves; ++w) {
-                    q += h[w * 2 * kMaxSpecies + a];
-                    n += h[w * 2 * kMaxSpecies + kMaxSpecies + a];
-                }
-                msd[a] = n > 0.0 ? q / n : 0.0;
-            }
+            for (int a = 0; a < s.n_species; ++a) msd[a] = h[kMaxSpecies + a] > 0.0 ? h[a] / h[kMaxSpecies + a] : 0.0;
     });
 }
 
@@ -1939,13 +1932,13 @@ rbsog_status rbsog_rdf_counts(rbsog_ctx* ctx, double r_max, int32_t n_bins, uint
         require(!s.shell_stored, RBSOG_E_STATE, "rdf: the memory form keeps no candidate rows");
         require(counts != nullptr, RBSOG_E_ARG, "rdf: counts is NULL");
         const size_t nh = (size_t)S * S * n_bins;
-        DBuf out;
-        out.alloc(sizeof(unsigned long long) * nh);
-        HIP_OK(hipMemsetAsync(out.p, 0, out.bytes, ctx->stream));
+        ctx->obs_buf.reserve(sizeof(unsigned long long) * nh);
+        unsigned long long* out = ctx->obs_buf.as<unsigned long long>();
+        launch_zero_u64(out, (int)nh, ctx->stream);
         const Plan P1 = one(ctx, ctx->sel);
-        launch_rdf(P1, S, r_max / (double)n_bins, n_bins, out.as<unsigned long long>(), ctx->stream);
+        launch_rdf(P1, S, r_max / (double)n_bins, n_bins, out, ctx->stream);
         HIP_OK(hipGetLastError());
-        HIP_OK(hipMemcpyAsync(counts, out.p, out.bytes, hipMemcpyDeviceToHost, ctx->stream));
+        HIP_OK(hipMemcpyAsync(counts, out, sizeof(unsigned long long) * nh, hipMemcpyDeviceToHost, ctx->stream));
         HIP_OK(hipStreamSynchronize(ctx->stream));
     });
 }

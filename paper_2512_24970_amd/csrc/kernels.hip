@@ -2583,11 +2583,17 @@ __global__ __launch_bounds__(kBlock) void k_kick_drift(RB_ARGS, int scheduled)
 // with the split the force uses (core entries inside the pair's core radius,
 // candidates from there to r_shell), so every pair within r_shell appears
 // once per direction while the lists are valid.  Bin k holds
-// e_k <= r^2 < e_{k+1}, e_k = (k D)^2 in FP64: an estimate from sqrt is
-// corrected against the exact edges.  Per-workgroup LDS counters, one
-// global atomic per nonzero bin (integer sums: the counts do not depend on
-// the order).
-__global__ __launch_bounds__(kBlock) void k_rdf(RB_ARGS, double D, int n_bins, unsigned long long* counts)
+// e_k <= r^2 < e_{k+1}, e_k = (k D)^2 in FP64: an FP32 estimate is corrected
+// against the exact edges.  r^2 comes from the 16-byte fixed-point records;
+// where their error could decide a bound or a bin, from the FP64 positions.
+// Per-workgroup LDS counters, one global atomic per nonzero bin (integer sums:
+// the counts do not depend on the order).
+// Bound by the gathers (about 225 records per atom).  A candidate
+// row belongs to 16 lanes, four rows to a wavefront, and a core tile to 4 lanes
+// of 16 neighbouring atoms, so list reads coalesce, where one lane per atom
+// read 64 rows at a time (262144 ions: 1087 us).
+constexpr int kRdfThreads = 1024;
+__global__ __launch_bounds__(kRdfThreads) void k_rdf(RB_ARGS, double D, int n_bins, unsigned long long* counts)
 {
     RB_SYS(blockIdx.x)
     extern __shared__ uint32_t hist[];  // [S][S][n_bins]
@@ -2595,38 +2601,86 @@ __global__ __launch_bounds__(kBlock) void k_rdf(RB_ARGS, double D, int n_bins, u
     const int nh = S * S * n_bins;
     for (int t = threadIdx.x; t < nh; t += blockDim.x) hist[t] = 0u;
     __syncthreads();
-    const int i = lb * blockDim.x + threadIdx.x;
+    const double top = ((double)n_bins * D) * ((double)n_bins * D);
+    const float iD = (float)(1.0 / D);
+    auto edge = [&](int k) { return ((double)k * D) * ((double)k * D); };
+    // entries k0, k0 + step, ... below cnt of atom i's list at list[k * stride]
+    constexpr int kU = 4;
+    const double ux = s.L[0] * 0x1p-32, uy = s.L[1] * 0x1p-32, uz = s.L[2] * 0x1p-32;
+    auto walk = [&](int i, const int32_t* list, int stride, int k0, int step, int cnt, bool core) {
+        const uint4 Ui = s.ufix[i];
+        const int ti = (int)Ui.w;
+        for (; k0 < cnt; k0 += kU * step) {
+            uint4 Q[kU];
+            int jj[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                jj[u] = list[(size_t)min(k0 + u * step, cnt - 1) * stride];
+                Q[u] = s.ufix[jj[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                if (k0 + u * step >= cnt) continue;
+                double dx = (double)(int32_t)(Ui.x - Q[u].x) * ux;
+                double dy = (double)(int32_t)(Ui.y - Q[u].y) * uy;
+                double dz = (double)(int32_t)(Ui.z - Q[u].z) * uz;
+                double r2 = (dx * dx + dy * dy) + dz * dz;
+                const int tj = (int)Q[u].w;
+                const double rc2 = s.species_cut ? s.pair[ti * S + tj].rc2 : s.rc2;
+                // bin of r2 (-1: not counted); near: r2 is within the records'
+                // error of a bound that decided it
+                auto bin = [&](bool& near) {
+                    const double gd = s.fix_guard;
+                    near = fabs(r2 - rc2) <= gd || (!core && fabs(r2 - s.rs2) <= gd) || fabs(r2 - top) <= gd;
+                    if (!(core ? r2 < rc2 : (r2 >= rc2 && r2 < s.rs2)) || !(r2 < top)) return -1;
+                    int k = min((int)(__fsqrt_rn((float)r2) * iD), n_bins - 1);
+                    double lo = edge(k), hi = edge(k + 1);
+                    while (k + 1 < n_bins && hi <= r2) {
+                        ++k;
+                        lo = hi;
+                        hi = edge(k + 1);
+                    }
+                    while (k > 0 && lo > r2) {
+                        --k;
+                        hi = lo;
+                        lo = edge(k);
+                    }
+                    near = near || r2 - lo <= gd || hi - r2 <= gd;
+                    return k;
+                };
+                bool near;
+                int k = bin(near);
+                if (near) {
+                    const double4 P = s.p[i], P2 = s.p[jj[u]];
+                    dx = min_image(P.x - P2.x, s.L[0], s.invL[0]);
+                    dy = min_image(P.y - P2.y, s.L[1], s.invL[1]);
+                    dz = min_image(P.z - P2.z, s.L[2], s.invL[2]);
+                    r2 = (dx * dx + dy * dy) + dz * dz;
+                    k = bin(near);
+                }
+                if (k >= 0) atomicAdd(&hist[(ti * S + tj) * n_bins + k], 1u);
+            }
+        }
+    };
+    // kBlock atoms per workgroup, 16 per wavefront
+    const int lane = threadIdx.x & 63;
+    const int a0 = lb * kBlock + (int)(threadIdx.x >> 6) * 16;
+    const int i = a0 + (lane & 15);
     if (i < s.n) {
-        const double4 Pi = s.p[i];
-        const int ti = s.type[i];
-        const double top = ((double)n_bins * D) * ((double)n_bins * D);
-        auto edge = [&](int k) { return ((double)k * D) * ((double)k * D); };
-        auto visit = [&](int j, bool core) {
-            const double4 Q = s.p[j];
-            const double dx = min_image(Pi.x - Q.x, s.L[0], s.invL[0]);
-            const double dy = min_image(Pi.y - Q.y, s.L[1], s.invL[1]);
-            const double dz = min_image(Pi.z - Q.z, s.L[2], s.invL[2]);
-            const double r2 = (dx * dx + dy * dy) + dz * dz;
-            const int tj = (int)Q.w;
-            const double rc2 = s.species_cut ? s.pair[ti * S + tj].rc2 : s.rc2;
-            const bool in = core ? r2 < rc2 : (r2 >= rc2 && r2 < s.rs2);
-            if (!in || !(r2 < top)) return;
-            int k = min((int)(sqrt(r2) / D), n_bins - 1);
-            while (k + 1 < n_bins && edge(k + 1) <= r2) ++k;
-            while (k > 0 && edge(k) > r2) --k;
-            atomicAdd(&hist[(ti * S + tj) * n_bins + k], 1u);
-        };
         const int nc = min(s.core_cnt[i], s.cap_core - 1);
-        const int32_t* ctile = s.core_idx + (size_t)(i >> 6) * s.cap_core * 64 + (i & 63);
-        for (int k = 0; k < nc; ++k) visit(ctile[(size_t)k * 64], true);
-        const int nk = min(s.cand_cnt[i], s.cap_cand - 1);
-        const int32_t* crow = s.cand_idx + (size_t)i * s.cap_cand;
-        for (int k = 0; k < nk; ++k) visit(crow[k], false);
+        walk(i, s.core_idx + (size_t)(i >> 6) * s.cap_core * 64 + (i & 63), 64, lane >> 4, 4, nc, true);
+    }
+    for (int q = 0; q < 16; q += 4) {
+        const int c = a0 + q + (lane >> 4);
+        if (c >= s.n) continue;
+        const int nk = min(s.cand_cnt[c], s.cap_cand - 1);
+        walk(c, s.cand_idx + (size_t)c * s.cap_cand, 1, lane & 15, 16, nk, false);
     }
     __syncthreads();
     for (int t = threadIdx.x; t < nh; t += blockDim.x)
         if (hist[t]) atomicAdd(&counts[t], (unsigned long long)hist[t]);
 }
+static_assert(kRdfThreads / 64 * 16 == kBlock, "the atoms map's blocks");
 
 // Zero fill (a kernel, not a memset node: callers may capture the stream).
 __global__ void k_zero_u64(unsigned long long* p, int n)
@@ -2674,6 +2728,19 @@ __global__ __launch_bounds__(kBlock) void k_msd(RB_ARGS, double* last, double* d
         wave_partial(ti == a ? q : 0.0, i, s.n, part, 2 * kMaxSpecies, a);
         wave_partial(ti == a ? 1.0 : 0.0, i, s.n, part, 2 * kMaxSpecies, kMaxSpecies + a);
     }
+}
+
+// Sums of k_msd's partials over the wavefronts: quantity c by wavefront c.
+__global__ __launch_bounds__(64 * 2 * kMaxSpecies) void k_msd_sum(const double* part, int waves, int n_species, double* out)
+{
+    constexpr int Q = 2 * kMaxSpecies;
+    const int c = threadIdx.x >> 6;
+    double v = 0.0;
+    if (c % kMaxSpecies < n_species)
+#pragma unroll 8
+        for (int w = threadIdx.x & 63; w < waves; w += 64) v += part[(size_t)w * Q + c];
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) out[c] = v;
 }
 
 __global__ void k_to_user3(RB_ARGS, int field, double* out)
@@ -3127,12 +3194,14 @@ void launch_zero_u64(unsigned long long* p, int n, hipStream_t st)
 void launch_rdf(const Plan& P, int n_species, double D, int n_bins, unsigned long long* counts, hipStream_t st)
 {
     const size_t sm = sizeof(uint32_t) * (size_t)n_species * n_species * n_bins;
-    if (P.atoms.blocks > 0) k_rdf<<<P.atoms.blocks, kBlock, sm, st>>>(RB_MAP(atoms), D, n_bins, counts);
+    if (P.atoms.blocks > 0) k_rdf<<<P.atoms.blocks, kRdfThreads, sm, st>>>(RB_MAP(atoms), D, n_bins, counts);
 }
 
-void launch_msd(const Plan& P, double* last, double* disp, double* part, bool mark, hipStream_t st)
+void launch_msd(const Plan& P, double* last, double* disp, double* part, int waves, int n_species, double* sums,
+                bool mark, hipStream_t st)
 {
     if (P.atoms.blocks > 0) k_msd<<<P.atoms.blocks, kBlock, 0, st>>>(RB_MAP(atoms), last, disp, part, mark ? 1 : 0);
+    k_msd_sum<<<1, 64 * 2 * kMaxSpecies, 0, st>>>(part, waves, n_species, sums);
 }
 
 void launch_to_user3(const Plan& P, Field f, double* out, hipStream_t st)

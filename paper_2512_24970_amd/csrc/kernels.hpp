@@ -338,8 +338,10 @@ unsigned long long* noalloc_scratch(int device);
 // zero n counters with a fill kernel
 void launch_zero_u64(unsigned long long* p, int n, hipStream_t st);
 // mean-square displacement bookkeeping of one system (Plan of that system);
-// part: [ceil(n/64)][2 kMaxSpecies] wavefront partials
-void launch_msd(const Plan& P, double* last, double* disp, double* part, bool mark, hipStream_t st);
+// part: [waves][2 kMaxSpecies] wavefront partials, waves = ceil(n/64); sums:
+// [2 kMaxSpecies], sum |D|^2 and the atom count per species
+void launch_msd(const Plan& P, double* last, double* disp, double* part, int waves, int n_species, double* sums,
+                bool mark, hipStream_t st);
 void launch_to_user3(const Plan& P, Field f, double* out, hipStream_t st);
 void launch_pos_to_user(const Plan& P, double* out, hipStream_t st);
 void launch_kspace_part(const Plan& P, double* out, hipStream_t st);
