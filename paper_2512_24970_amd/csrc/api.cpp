@@ -324,6 +324,7 @@ Plan one(const rbsog_ctx* c, int r)
     P.kf_threads = c->plan.kf_threads;
     P.kf_split = c->plan.kf_split;
     P.kf_sliced = c->plan.kf_sliced;
+    P.kf_chain = c->plan.kf_chain;
     const bool grouped = k.kf_groups > 1;
     const int kf_apb = P.kf_threads / std::max(1, k.kf_waves);  // atoms of a workgroup
     P.kf_atoms.blocks = blocks_for(s.n, grouped ? P.kf_threads : kf_apb);
@@ -368,13 +369,16 @@ void plan_launches(rbsog_ctx* c)
     size_t waves = 0;
     for (const auto& s : c->hs) waves += blocks_for(s.n, 64);
     P.pair_lanes = pair_lanes_for(waves, c->mixed);
+    P.max_cells = 0;
+    for (const auto& s : c->hs) P.max_cells = std::max(P.max_cells, s.ncell);
     P.kf_threads = P.tune.kf_block;
-    P.kf_split = P.kf_sliced = false;
+    P.kf_split = P.kf_sliced = P.kf_chain = false;
     for (int r = 0; r < c->R; ++r) {
         P.fin_grid = std::max(P.fin_grid, fin_blocks(c->hs[r].n, c->hk[r].n_modes));
         P.kf_threads = std::max(P.kf_threads, 64 * c->hk[r].kf_waves);
-        if (c->hk[r].kf_slices > 1) P.kf_split = true;
-        if (c->hk[r].kf_waves > 1) P.kf_sliced = true;
+        if (c->hk[r].kf_slices > 1 || c->hk[r].kf_chain) P.kf_split = true;
+        if (c->hk[r].kf_slices > 1 && c->hk[r].kf_waves > 1) P.kf_sliced = true;
+        if (c->hk[r].kf_chain) P.kf_chain = true;
     }
     constexpr int kShapes = 11 + kListPerAtom;
     Shape* dst[kShapes] = {&P.atoms, &P.pair_atoms, &P.kf_atoms, &P.cells, &P.atom1, &P.modes64, &P.rho,
@@ -642,7 +646,7 @@ void enqueue_forces(rbsog_ctx* c, bool energy, bool kick, bool build = false)
     c->end();
     HIP_OK(hipStreamWaitEvent(st, c->ev_join, 0));
     c->begin(RBSOG_PHASE_REDUCE);
-    launch_finalize(P, energy, st);
+    launch_finalize(P, energy, build, st);
     c->end();
     if (aux_kf) {
         c->begin(RBSOG_PHASE_INTEGRATE);
@@ -709,7 +713,6 @@ void check_flags(rbsog_ctx* c, const std::vector<DeviceScalars>& h)
 void enqueue_step(rbsog_ctx* c, bool scheduled, bool energy)
 {
     c->begin(RBSOG_PHASE_INTEGRATE);
-    launch_step_begin(c->plan, c->stream);
     launch_kick_drift(c->plan, scheduled, c->stream);
     c->end();
     enqueue_forces(c, energy, true, true);
@@ -777,7 +780,7 @@ void autotune(rbsog_ctx* c, int reps)
     launch_rho(c->plan, c->mixed, st);
     launch_rho_finalize(c->plan, false, st);
     launch_pair(c->plan, c->mixed, false, st);
-    launch_finalize(c->plan, false, st);
+    launch_finalize(c->plan, false, false, st);
     // a first pick of the k-space force workgroup size, the kernel alone
     // (refined on whole steps below)
     double tb = 1e300;
@@ -1115,7 +1118,7 @@ void set_batch_impl(rbsog_ctx* c, int R, const rbsog_params* params, const int32
     // 3 int32 per slot; system r owns slots [slot_off[r], slot_off[r] + n_r)
     const size_t N = (size_t)std::max(c->n_slots, 1);
     c->atoms.alloc(N * (sizeof(double4) + 12 * sizeof(double) + 3 * sizeof(int32_t)));
-    c->sortbuf.alloc(N * (sizeof(double4) + 6 * sizeof(double) + 5 * sizeof(int32_t)));
+    c->sortbuf.alloc(N * (sizeof(double4) + 6 * sizeof(double) + 4 * sizeof(int32_t)));
     c->counts.alloc(2 * sizeof(int32_t) * N);
     HIP_OK(hipMemsetAsync(c->counts.p, 0, 2 * sizeof(int32_t) * N, c->stream));
     size_t n_cells = 0;
@@ -1166,7 +1169,6 @@ void set_batch_impl(rbsog_ctx* c, int R, const rbsog_params* params, const int32
             s.tid = tip + N + o;
             s.cell_of = tip + 2 * N + o;
             s.slot_of = tip + 3 * N + o;
-            s.order = tip + 4 * N + o;
             s.core_cnt = c->counts.as<int32_t>() + o;
             s.cand_cnt = c->counts.as<int32_t>() + N + o;
             s.cell_count = cells;
@@ -1320,7 +1322,9 @@ void set_batch_impl(rbsog_ctx* c, int R, const rbsog_params* params, const int32
         // quarters read four atoms at a time
         k.chunk = (std::max(1, (n + k.n_chunks - 1) / k.n_chunks) + 15) & ~15;
         k.n_chunks = std::max(1, (n + k.chunk - 1) / k.chunk);
-        kforce_split(n, k.n_modes, &k.kf_slices, &k.kf_groups);
+        const bool chained = c->mixed && k.n_modes <= kKfChainModes;
+        k.kf_slices = k.kf_groups = 1;
+        if (!chained) kforce_split(n, k.n_modes, &k.kf_slices, &k.kf_groups);
         k.kf_len = blocks_for(k.n_modes, k.kf_slices * k.kf_groups);
         k.kf_pad = round_up(std::max(n, 1), 64);
         if (k.kf_groups > 1) kf_part_all += (size_t)k.kf_groups * kKfAccMax * k.kf_pad;
@@ -1328,7 +1332,11 @@ void set_batch_impl(rbsog_ctx* c, int R, const rbsog_params* params, const int32
         rho_part_all += 2 * (size_t)k.n_chunks * k.n_modes_pad;
     }
     // grouped systems always take a wavefront per slice
-    for (auto& k : c->hk) k.kf_waves = (k.kf_groups > 1 || n_waves < (size_t)kKfFill) ? k.kf_slices : 1;
+    for (auto& k : c->hk) {
+        k.kf_waves = (k.kf_groups > 1 || n_waves < (size_t)kKfFill) ? k.kf_slices : 1;
+        k.kf_chain = c->mixed && k.n_modes >= kKfChainMin && k.n_modes <= kKfChainModes && n_waves < (size_t)kKfChainFill;
+        if (k.kf_chain) k.kf_waves = kKfThreads / 64;
+    }
     c->kcdf.alloc(sizeof(double) * std::max<size_t>(1, cdf_doubles) + sizeof(int32_t) * cdf_ints);
     c->kmodes.alloc(std::max<size_t>(1, n_modes_all) * (sizeof(ModeRec) + 3 * sizeof(int32_t)));
     c->krho_part.alloc(sizeof(double) * std::max<size_t>(1, rho_part_all));

@@ -56,7 +56,7 @@ __device__ inline DevSys global_view(DevSys s)
     s.tvx = glob(s.tvx), s.tvy = glob(s.tvy), s.tvz = glob(s.tvz);
     s.tfx = glob(s.tfx), s.tfy = glob(s.tfy), s.tfz = glob(s.tfz);
     s.ttype = glob(s.ttype), s.tid = glob(s.tid), s.cell_of = glob(s.cell_of);
-    s.slot_of = glob(s.slot_of), s.order = glob(s.order);
+    s.slot_of = glob(s.slot_of);
     s.cell_count = glob(s.cell_count), s.cell_start = glob(s.cell_start);
     s.core_cnt = glob(s.core_cnt), s.core_idx = glob(s.core_idx);
     s.cand_cnt = glob(s.cand_cnt), s.cand_idx = glob(s.cand_idx), s.bat_idx = glob(s.bat_idx);
@@ -192,39 +192,57 @@ __global__ void k_set_eval(DeviceScalars* sc, int R, uint64_t eval)
 {
     for (int r = threadIdx.x; r < R; r += blockDim.x) sc[r].eval = eval;
 }
-// Nose-Hoover half step on the thermostat variables (Trotter splitting,
-// one variable): from the kinetic energy K of the velocities it acts on,
-// returns the velocity factor and leaves K scaled by its square.
-__device__ inline double nh_half(const DevSys& s, DeviceScalars* sc, double& K)
+// Nose-Hoover half step of the thermostat variables x and v (Trotter
+// splitting, one variable): from the kinetic energy K of the velocities it
+// acts on, returns the velocity factor and leaves K scaled by its square.
+__device__ inline double nh_half(const DevSys& s, double& K, double& x, double& v)
 {
     const double gkt = s.dof_kb * s.t_target;
-    double v = sc->nh_v + 0.25 * s.dt * (2.0 * K - gkt) / s.nh_q;
-    const double f = exp(-0.5 * s.dt * v);
+    const double w = v + 0.25 * s.dt * (2.0 * K - gkt) / s.nh_q;
+    const double f = exp(-0.5 * s.dt * w);
     K = K * (f * f);
-    sc->nh_x += 0.5 * s.dt * v;
-    sc->nh_v = v + 0.25 * s.dt * (2.0 * K - gkt) / s.nh_q;
+    x += 0.5 * s.dt * w;
+    v = w + 0.25 * s.dt * (2.0 * K - gkt) / s.nh_q;
     return f;
 }
 
 __device__ inline bool is_nh(const DevSys& s) { return s.thermo_c > 0.0 && s.thermostat == kThermoNoseHoover; }
 
-// Start of a step: the Philox counter moves on; Nose-Hoover takes its
-// opening half step from the kinetic energy at the end of the last one and
-// hands the opening kick the product of both pending velocity factors.
-__global__ void k_step_begin(const DevSys* __restrict__ sys, int R)
+// The velocity factor of a step's opening kick: the thermostat's, for
+// Nose-Hoover its opening half step from the kinetic energy at the end of the
+// last step times the factor the velocities still owe.
+__device__ inline double opening_factor(const DevSys& s)
 {
-    for (int r = threadIdx.x; r < R; r += blockDim.x) {
-        const DevSys s = global_view(sys[r]);
-        DeviceScalars* sc = s.sc;
-        sc->eval += 1;
-        if (is_nh(s)) {
-            double K = sc->kinetic;
-            const double f = nh_half(s, sc, K);
-            sc->kinetic = K;
-            sc->vscale = sc->vpend * f;
-            sc->vpend = 1.0;
-        }
+    const DeviceScalars* sc = s.sc;
+    if (!is_nh(s)) return sc->vscale;
+    double K = sc->kinetic, x = sc->nh_x, v = sc->nh_v;
+    return sc->vpend * nh_half(s, K, x, v);
+}
+
+// A step's scalars after its opening kick has read them: the Philox counter
+// moves on and Nose-Hoover's opening half step is kept.
+__device__ inline void open_step(const DevSys& s)
+{
+    DeviceScalars* sc = s.sc;
+    sc->eval += 1;
+    if (is_nh(s)) {
+        double K = sc->kinetic, x = sc->nh_x, v = sc->nh_v;
+        nh_half(s, K, x, v);
+        sc->kinetic = K;
+        sc->nh_x = x;
+        sc->nh_v = v;
+        sc->vpend = 1.0;
     }
+}
+
+// Closes a system's build: lower the flag, restart the displacement tracking.
+// A build that overflowed is discarded and built again, so it takes no number.
+__device__ inline void close_build(DeviceScalars* sc, bool gate)
+{
+    if (gate && (sc->rebuild == 0 || sc->nonfinite)) return;
+    sc->rebuild = 0;
+    sc->max_disp2 = 0.0;
+    if (sc->overflow == 0) sc->n_builds += 1;
 }
 
 __global__ void k_init_scalars(DeviceScalars* sc, int R)
@@ -234,17 +252,10 @@ __global__ void k_init_scalars(DeviceScalars* sc, int R)
         sc[r].vpend = 1.0;
     }
 }
-// Closes a build: lower the flag, restart the displacement tracking.  A
-// build that overflowed is discarded and built again, so it takes no number.
-__global__ void k_build_done(const DevSys* __restrict__ sys, int R, int gate)
+// Outside steps (a step closes its build in the force-sum reduction).
+__global__ void k_build_done(const DevSys* __restrict__ sys, int R)
 {
-    for (int r = threadIdx.x; r < R; r += blockDim.x) {
-        DeviceScalars* sc = glob(sys[r].sc);
-        if (gate && (sc->rebuild == 0 || sc->nonfinite)) continue;
-        sc->rebuild = 0;
-        sc->max_disp2 = 0.0;
-        if (sc->overflow == 0) sc->n_builds += 1;
-    }
+    for (int r = threadIdx.x; r < R; r += blockDim.x) close_build(glob(sys[r].sc), false);
 }
 __global__ void k_clear_flags(DeviceScalars* sc, int R)
 {
@@ -257,9 +268,12 @@ __global__ void k_clear_flags(DeviceScalars* sc, int R)
 }
 
 // ---------------------------------------------------------------- cell sort
+// gate != 0 is a step's build: the step's scalars are opened here, the first
+// pass after the opening kick.
 __global__ void k_bin(RB_ARGS, int gate)
 {
     RB_SYS(blockIdx.x)
+    if (gate && lb == 0 && threadIdx.x == 0) open_step(s);
     RB_GATE
     const int i0 = lb * blockDim.x + threadIdx.x;
     // lanes past the end take part in the wavefront votes with a done flag
@@ -301,7 +315,7 @@ __global__ void k_bin(RB_ARGS, int gate)
 
 // Exclusive scan of count[0..n) into start[0..n], one block of 1024 threads
 // per system, over tiles of kScanTile counts staged in LDS (coalesced loads
-// and stores); counts are zeroed for the next build.
+// and stores).
 constexpr int kScanTile = 8192;
 __global__ __launch_bounds__(1024) void k_scan(const DevSys* __restrict__ sys, int gate)
 {
@@ -351,7 +365,6 @@ __global__ __launch_bounds__(1024) void k_scan(const DevSys* __restrict__ sys, i
             const int i = t + 1024 * k;
             if (i < m) {
                 start[base + i] = tile[i];
-                count[base + i] = 0;  // ready for the next build
             }
         }
         __syncthreads();
@@ -359,13 +372,48 @@ __global__ __launch_bounds__(1024) void k_scan(const DevSys* __restrict__ sys, i
     if (t == 0) start[n] = carry;
 }
 
-__global__ void k_scatter(RB_ARGS, int gate)
+// Atoms into cell order.  own_scan: no k_scan ran (every system has at most
+// kOwnScan cells, about 10^5 atoms): each workgroup scans the counts itself,
+// which a launch costs more than, and the first writes the cell starts.
+constexpr int kOwnScan = 2048;
+__global__ __launch_bounds__(kBlock) void k_scatter(RB_ARGS, int gate, int own_scan)
 {
     RB_SYS(blockIdx.x)
     RB_GATE
+    __shared__ int32_t start[kOwnScan];
+    __shared__ int32_t wsum[kBlock / 64];
+    if (own_scan) {
+        constexpr int per = kOwnScan / kBlock;
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, b = threadIdx.x * per;
+        int32_t v[per], sum = 0;
+#pragma unroll
+        for (int k = 0; k < per; ++k) {
+            v[k] = b + k < s.ncell ? s.cell_count[b + k] : 0;
+            sum += v[k];
+        }
+        int32_t x = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int32_t y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) wsum[wave] = x;
+        __syncthreads();
+        int32_t run = x - sum;
+        for (int w = 0; w < wave; ++w) run += wsum[w];
+#pragma unroll
+        for (int k = 0; k < per; ++k) {
+            start[b + k] = run;
+            if (lb == 0 && b + k <= s.ncell) s.cell_start[b + k] = run;
+            run += v[k];
+        }
+        if (lb == 0 && threadIdx.x == kBlock - 1 && s.ncell == kOwnScan) s.cell_start[kOwnScan] = run;
+        __syncthreads();
+    }
     const int i = lb * blockDim.x + threadIdx.x;
     if (i >= s.n) return;
-    const int d = s.cell_start[s.cell_of[i]] + s.slot_of[i];
+    const int c = s.cell_of[i];
+    const int d = (own_scan ? start[c] : s.cell_start[c]) + s.slot_of[i];
     s.tp[d] = s.p[i];
     s.tvx[d] = s.vx[i];
     s.tvy[d] = s.vy[i];
@@ -377,12 +425,35 @@ __global__ void k_scatter(RB_ARGS, int gate)
     s.tid[d] = s.id[i];
 }
 
+// Atom t of the new order is scattered atom o.
+__device__ inline void gather_atom(const DevSys& s, int t, int o)
+{
+    const double4 P = s.tp[o];
+    s.p[t] = P;
+    s.ufix[t] = fix_record(s, P.x, P.y, P.z, P.w);
+    s.xr[t] = P.x;
+    s.yr[t] = P.y;
+    s.zr[t] = P.z;
+    s.vx[t] = s.tvx[o];
+    s.vy[t] = s.tvy[o];
+    s.vz[t] = s.tvz[o];
+    s.fx[t] = s.tfx[o];
+    s.fy[t] = s.tfy[o];
+    s.fz[t] = s.tfz[o];
+    s.type[t] = s.ttype[o];
+    const int id = s.tid[o];
+    s.id[t] = id;
+    s.inv[id] = t;
+}
+
 // Within each list cell, order atoms by (ordering sub-cell, id): the order is
 // deterministic and each of the eight sub-cells is a contiguous range, whose
 // first positions go to sub_beg.  Keys: sub-cell << 28 | id (ids < 2^28).
 // A cell of up to 64 atoms (nearly every cell of a large box) is sorted by
 // the block's first wavefront in registers, a bitonic network across its
 // lanes; a larger one (a small box is one cell) by the whole block over LDS.
+// The sorted atoms go straight to their places (a pass of its own over the
+// permutation read and wrote it once more, and was one more launch).
 __global__ __launch_bounds__(kBlock) void k_cell_sort(RB_ARGS, int gate)
 {
     RB_SYS(blockIdx.x)
@@ -394,10 +465,11 @@ __global__ __launch_bounds__(kBlock) void k_cell_sort(RB_ARGS, int gate)
     const int beg = s.cell_start[c];
     const int cnt = s.cell_start[c + 1] - beg;
     int32_t* sb = s.sub_beg + (size_t)c * 8;
+    if (threadIdx.x == 0) s.cell_count[c] = 0;  // for the next build
     if (cnt > kCellCap) {
         // keep a valid (unsorted) permutation and in-range sub-cell bounds;
         // the host reports the overflow
-        for (int t = threadIdx.x; t < cnt; t += blockDim.x) s.order[beg + t] = beg + t;
+        for (int t = threadIdx.x; t < cnt; t += blockDim.x) gather_atom(s, beg + t, beg + t);
         if (threadIdx.x < 8) sb[threadIdx.x] = threadIdx.x == 0 ? 0 : cnt;
         if (threadIdx.x == 0) atomicOr(&s.sc->overflow, 2);
         return;
@@ -428,7 +500,7 @@ __global__ __launch_bounds__(kBlock) void k_cell_sort(RB_ARGS, int gate)
                 }
             }
         }
-        if (lane < cnt) s.order[beg + lane] = v;
+        if (lane < cnt) gather_atom(s, beg + lane, v);
         // first sorted position whose sub-cell is >= q: the keys below q << 28
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
@@ -463,7 +535,7 @@ __global__ __launch_bounds__(kBlock) void k_cell_sort(RB_ARGS, int gate)
             __syncthreads();
         }
     }
-    for (int t = threadIdx.x; t < cnt; t += blockDim.x) s.order[beg + t] = val[t];
+    for (int t = threadIdx.x; t < cnt; t += blockDim.x) gather_atom(s, beg + t, val[t]);
     if (threadIdx.x < 8) {
         // first sorted position whose sub-cell is >= this one
         const int32_t want = (int32_t)threadIdx.x << 28;
@@ -477,31 +549,6 @@ __global__ __launch_bounds__(kBlock) void k_cell_sort(RB_ARGS, int gate)
         }
         sb[threadIdx.x] = lo;
     }
-}
-
-__global__ void k_gather(RB_ARGS, int gate)
-{
-    RB_SYS(blockIdx.x)
-    RB_GATE
-    const int t = lb * blockDim.x + threadIdx.x;
-    if (t >= s.n) return;
-    const int o = s.order[t];
-    const double4 P = s.tp[o];
-    s.p[t] = P;
-    s.ufix[t] = fix_record(s, P.x, P.y, P.z, P.w);
-    s.xr[t] = P.x;
-    s.yr[t] = P.y;
-    s.zr[t] = P.z;
-    s.vx[t] = s.tvx[o];
-    s.vy[t] = s.tvy[o];
-    s.vz[t] = s.tvz[o];
-    s.fx[t] = s.tfx[o];
-    s.fy[t] = s.tfy[o];
-    s.fz[t] = s.tfz[o];
-    s.type[t] = s.ttype[o];
-    const int id = s.tid[o];
-    s.id[t] = id;
-    s.inv[id] = t;
 }
 
 // ---------------------------------------------------------------- lists
@@ -1222,7 +1269,18 @@ __device__ inline void wave_lds_fence()
     __builtin_amdgcn_wave_barrier();
 }
 
-constexpr int kPairGroup = 4;  // list entries whose sums are formed together, then added in list order
+// The value that lane Q of every group of LPA neighbouring lanes (two or four)
+// holds, by a quad permutation.
+template <int LPA, int Q>
+__device__ inline double group_lane(double v)
+{
+    constexpr int ctrl = LPA == 4 ? Q * 0x55 : Q | Q << 2 | (Q + 2) << 4 | (Q + 2) << 6;
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)b, ctrl, 0xF, 0xF, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(b >> 32), ctrl, 0xF, 0xF, true);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 constexpr int kDrawMax = 64;   // largest batch drawn by several lanes together
 
 // Pair forces.  Half of a workgroup's threads (whole wavefronts) take the core
@@ -1231,15 +1289,15 @@ constexpr int kDrawMax = 64;   // largest batch drawn by several lanes together
 // flight.  LPA lanes of each half share an atom: with one the kernel is bound
 // by vector-memory addressing (mixed) or FP64 issue, but a small system's
 // wavefronts are too few, and each is a chain of dependent loads and
-// evaluations; with more lanes the chain is 1/LPA as long (pair_lanes_for).  An atom's pairs are summed in groups of kPairGroup list
-// entries, the groups added in list order, whatever LPA, so the result does
-// not depend on it.  The shell sum, reweighted, is added to the core sum
+// evaluations; with more lanes the chain is 1/LPA as long (pair_lanes_for).
+// Every lane of an atom then adds all the pairs that its lanes evaluated, in
+// list order, so LPA changes no bit.  The shell sum, reweighted, is added to the core sum
 // passed through LDS.
 // LPA = 1: blockDim.x / 2 atoms per workgroup; else 64.
 template <bool MIXED, bool ENERGY, int KU, int LPA>
 __global__ __launch_bounds__(LPA == 1 ? 2 * kBlock : 128 * LPA) void k_pair(RB_ARGS, NearTab nt)
 {
-    static_assert(KU % kPairGroup == 0 && (LPA == 1 || KU == kPairGroup), "whole groups per fetch");
+    static_assert(LPA == 1 || LPA == 2 || LPA == 4, "group_lane");
     RB_SYS(xcd_block(blockIdx.x, gridDim.x))
     // dynamic LDS, sized by the launch: the near-field table (F coefficients,
     // with energies also U), the sums handed to the
@@ -1343,18 +1401,21 @@ __global__ __launch_bounds__(LPA == 1 ? 2 * kBlock : 128 * LPA) void k_pair(RB_A
         // from the FP64 positions, so the pair set is the FP64 one.
         auto visit = [&](auto shell_tag, const int* jj, int k0, int cnt) {
             constexpr bool SH = decltype(shell_tag)::value;
-            Sum grp;
-            grp.clear();
-            auto fold = [&] {
+            // LPA > 1: this lane's pairs, zero past the list and outside the
+            // cutoffs (adding f = 0 changes no sum)
+            double pf[KU], pu[KU], px[KU], py[KU], pz[KU];
+            if (LPA > 1)
+#pragma unroll
+                for (int u = 0; u < KU; ++u) pf[u] = pu[u] = px[u] = py[u] = pz[u] = 0.0;
+            auto take = [&](int u, double f, double uu, double dx, double dy, double dz) {
                 if (LPA == 1) {
-#pragma unroll
-                    for (int c = 0; c < N; ++c) tot.v[c] += grp.v[c];
+                    tot.add(f, uu, dx, dy, dz);
                 } else {
-                    // the groups of the atom's lanes, in list order
-#pragma unroll
-                    for (int q = 0; q < LPA; ++q)
-#pragma unroll
-                        for (int c = 0; c < N; ++c) tot.v[c] += __shfl(grp.v[c], q, LPA);
+                    pf[u] = f;
+                    pu[u] = uu;
+                    px[u] = dx;
+                    py[u] = dy;
+                    pz[u] = dz;
                 }
             };
             if (MIXED) {
@@ -1364,10 +1425,6 @@ __global__ __launch_bounds__(LPA == 1 ? 2 * kBlock : 128 * LPA) void k_pair(RB_A
 #pragma unroll
                 for (int u = 0; u < KU; ++u) {
                     if (k0 + u >= cnt) break;
-                    if (u > 0 && u % kPairGroup == 0) {
-                        fold();
-                        grp.clear();
-                    }
                     double dx = (double)(int32_t)(Ui.x - Q[u].x) * ux;
                     double dy = (double)(int32_t)(Ui.y - Q[u].y) * uy;
                     double dz = (double)(int32_t)(Ui.z - Q[u].z) * uz;
@@ -1384,7 +1441,7 @@ __global__ __launch_bounds__(LPA == 1 ? 2 * kBlock : 128 * LPA) void k_pair(RB_A
                     if (SH ? (r2 >= rc2 && r2 < s.rs2) : (r2 < rc2)) {
                         double uu = 0.0;
                         const double f = pair_f(tj, r2, uu);
-                        grp.add(f, uu, dx, dy, dz);
+                        take(u, f, uu, dx, dy, dz);
                     }
                 }
             } else {
@@ -1401,10 +1458,6 @@ __global__ __launch_bounds__(LPA == 1 ? 2 * kBlock : 128 * LPA) void k_pair(RB_A
 #pragma unroll
                 for (int u = 0; u < KU; ++u) {
                     if (k0 + u >= cnt) break;
-                    if (u > 0 && u % kPairGroup == 0) {
-                        fold();
-                        grp.clear();
-                    }
                     const double dx = mi(Pi.x - X[u], 0);
                     const double dy = mi(Pi.y - Y[u], 1);
                     const double dz = mi(Pi.z - Z[u], 2);
@@ -1413,16 +1466,29 @@ __global__ __launch_bounds__(LPA == 1 ? 2 * kBlock : 128 * LPA) void k_pair(RB_A
                     if (SH ? (r2 >= rc2 && r2 < s.rs2) : (r2 < rc2)) {
                         double uu = 0.0;
                         const double f = pair_f(T[u], r2, uu);
-                        grp.add(f, uu, dx, dy, dz);
+                        take(u, f, uu, dx, dy, dz);
                     }
                 }
             }
-            fold();
+            if constexpr (LPA > 1) {
+                auto add_lane = [&](auto q_tag) {
+                    constexpr int q = decltype(q_tag)::value;
+                    if constexpr (q < LPA)
+#pragma unroll
+                        for (int u = 0; u < KU; ++u)
+                            tot.add(group_lane<LPA, q>(pf[u]), ENERGY ? group_lane<LPA, q>(pu[u]) : 0.0,
+                                    group_lane<LPA, q>(px[u]), group_lane<LPA, q>(py[u]), group_lane<LPA, q>(pz[u]));
+                };
+                add_lane(std::integral_constant<int, 0>{});
+                add_lane(std::integral_constant<int, 1>{});
+                add_lane(std::integral_constant<int, 2>{});
+                add_lane(std::integral_constant<int, 3>{});
+            }
         };
         // Tile rows are read once: non-temporal loads keep them from evicting
         // the positions that neighbours re-read (a candidate row is re-read by
         // its own lane, so it stays cached).  Lane `sub` takes every LPA-th
-        // group.
+        // KU entries.
         constexpr int kU = KU;
         constexpr int kRound = kU * LPA;
         auto walk_tile = [&](auto shell_tag, int cnt) {
@@ -2015,37 +2081,62 @@ __global__ __launch_bounds__(64) void k_rho_finalize(RB_ARGS, const KDev* __rest
     }
 }
 
-// Momentum correction (eq. 26) and energy sums, first pass: block b of each
-// system sums slice b of the wavefront partials and of the modes, and writes
-// the kFin sums to fin_part[b].
-__global__ __launch_bounds__(256) void k_finalize_part(const DevSys* __restrict__ sys, const KDev* __restrict__ kd,
-                                                       int energy, int grid)
+// The evaluation's scalars from its kFin sums: momentum correction (eq. 26),
+// energies, virial; close: a step's build, if there was one, ends here.
+__device__ inline void write_sums(const DevSys& s, const double* tot, int energy, int close)
 {
-    const int r = blockIdx.x / grid, b = blockIdx.x - r * grid;
+    DeviceScalars* sc = s.sc;
+    const double inv_n = s.n > 0 ? 1.0 / (double)s.n : 0.0;
+    sc->p_corr[0] = tot[0] * inv_n;
+    sc->p_corr[1] = tot[1] * inv_n;
+    sc->p_corr[2] = tot[2] * inv_n;
+    sc->u_core = tot[3];
+    sc->u_shell = tot[4];
+    const double ut = tot[kPairPart + kVirPart];
+    sc->u_kspace = 0.5 * s.coulomb_k * ut;
+    if (energy)
+        for (int c = 0; c < 6; ++c)
+            sc->virial[c] = tot[kPairPart + c] + 0.5 * s.coulomb_k * tot[kPairPart + kVirPart + 1 + c];
+    if (close) close_build(sc, true);
+}
+
+// Momentum correction (eq. 26) and energy sums, first pass: slice b of each
+// system's wavefront partials and modes is summed by 256 threads, and its kFin
+// sums go to fin_part[b].  grid = 1: one block per system holds all its slices
+// (at most kFinOne), adds them in order and writes the scalars, with no second
+// pass; else one slice per block.
+__global__ __launch_bounds__(256 * kFinOne) void k_finalize_part(const DevSys* __restrict__ sys,
+                                                                 const KDev* __restrict__ kd, int energy, int grid,
+                                                                 int close)
+{
+    const int r = blockIdx.x / grid, slice = threadIdx.x >> 8, tid = threadIdx.x & 255;
+    const int b = grid == 1 ? slice : (int)blockIdx.x - r * grid;
     const DevSys s = global_view(sys[r]);
     const KDev k = global_view(kd[r]);
     const int nf = fin_blocks(s.n, k.n_modes);
-    if (b >= nf) return;  // a smaller system of a batch
+    if (grid > 1 && b >= nf) return;  // a smaller system of a batch
     const double* part = s.pair_part;
     const int nb = (s.n + 63) / 64;  // wavefront partials
-    const int w0 = nb * b / nf, w1 = nb * (b + 1) / nf;  // nb * 32 fits 32 bits
-    __shared__ double red[4];
+    const int bs = min(b, nf);       // a slice past the last is empty
+    const int w0 = nb * bs / nf, w1 = nb * min(b + 1, nf) / nf;  // nb * 32 fits 32 bits
+    __shared__ double red[4 * kFinOne];
+    __shared__ double row[kFinOne][kFin];
     double v[kPairPart + kVirPart];
     for (int c = 0; c < kPairPart + kVirPart; ++c) v[c] = 0.0;
 #pragma unroll 4
-    for (int w = w0 + (int)threadIdx.x; w < w1; w += blockDim.x)
+    for (int w = w0 + tid; w < w1; w += 256)
         for (int c = 0; c < kPairPart; ++c) v[c] += part[(size_t)w * kPairPart + c];
     if (energy) {
 #pragma unroll 4
-        for (int w = w0 + (int)threadIdx.x; w < w1; w += blockDim.x)
+        for (int w = w0 + tid; w < w1; w += 256)
             for (int c = 0; c < kVirPart; ++c) v[kPairPart + c] += s.vir_part[(size_t)w * kVirPart + c];
     }
     const int nc = energy ? kPairPart + kVirPart : kPairPart;
     double ue = 0.0;
     double wk[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     const int nm = s.n > 0 ? k.n_modes : 0;  // an empty system sums no modes
-    const int m0 = (int)((long long)nm * b / nf), m1 = (int)((long long)nm * (b + 1) / nf);
-    for (int p = m0 + (int)threadIdx.x; p < m1; p += blockDim.x) {
+    const int m0 = (int)((long long)nm * bs / nf), m1 = (int)((long long)nm * min(b + 1, nf) / nf);
+    for (int p = m0 + tid; p < m1; p += 256) {
         const ModeRec mr = k.modes[p];
         ue += mr.e;
         if (energy) {
@@ -2060,26 +2151,43 @@ __global__ __launch_bounds__(256) void k_finalize_part(const DevSys* __restrict_
             wk[5] -= eg * ky * kz;
         }
     }
-    // nc and energy are uniform, so every thread takes part in each block_sum
-    double* out = s.fin_part + (size_t)b * kFin;
+    // nc and energy are uniform, so every thread takes part in each sum: the
+    // slice's four wavefronts in order, kept by its first thread
+    auto slice_total = [&](double x, int c) {
+        x = wave_sum(x);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
+        __syncthreads();
+        if (tid == 0) row[slice][c] = ((red[4 * slice] + red[4 * slice + 1]) + red[4 * slice + 2]) + red[4 * slice + 3];
+        __syncthreads();
+    };
+    if (!energy && threadIdx.x < kFin)
+        for (int q = 0; q < (int)(blockDim.x >> 8); ++q) row[q][threadIdx.x] = 0.0;
+    __syncthreads();
 #pragma unroll
-    for (int c = 0; c < kPairPart + kVirPart; ++c) {
-        const double t = c < nc ? block_sum(v[c], red) : 0.0;
-        if (threadIdx.x == 0) out[c] = t;
-    }
-    const double ut = block_sum(ue, red);
-    if (threadIdx.x == 0) out[kPairPart + kVirPart] = ut;
+    for (int c = 0; c < kPairPart + kVirPart; ++c)
+        if (c < nc) slice_total(v[c], c);
+    slice_total(ue, kPairPart + kVirPart);
+    if (energy)
 #pragma unroll
-    for (int c = 0; c < 6; ++c) {
-        const double t = energy ? block_sum(wk[c], red) : 0.0;
-        if (threadIdx.x == 0) out[kPairPart + kVirPart + 1 + c] = t;
+        for (int c = 0; c < 6; ++c) slice_total(wk[c], kPairPart + kVirPart + 1 + c);
+    if (grid > 1) {
+        if (threadIdx.x < kFin) s.fin_part[(size_t)b * kFin + threadIdx.x] = row[0][threadIdx.x];
+    } else if (threadIdx.x == 0) {
+        double tot[kFin];
+#pragma unroll
+        for (int c = 0; c < kFin; ++c) {
+            tot[c] = 0.0;
+            for (int q = 0; q < nf; ++q) tot[c] += row[q][c];
+        }
+        write_sums(s, tot, energy, close);
     }
 }
 
 // Second pass: one wavefront per system; lane q adds quantity q of the
 // system's fin_blocks block sums in block order, and the evaluation's
 // scalars are written from them.
-__global__ __launch_bounds__(64) void k_finalize(const DevSys* __restrict__ sys, const KDev* __restrict__ kd, int energy)
+__global__ __launch_bounds__(64) void k_finalize(const DevSys* __restrict__ sys, const KDev* __restrict__ kd, int energy,
+                                                 int close)
 {
     const DevSys s = global_view(sys[blockIdx.x]);
     const int q = threadIdx.x;
@@ -2097,20 +2205,7 @@ __global__ __launch_bounds__(64) void k_finalize(const DevSys* __restrict__ sys,
     double tot[kFin];
 #pragma unroll
     for (int c = 0; c < kFin; ++c) tot[c] = get(c);
-    if (q == 0) {
-        DeviceScalars* sc = s.sc;
-        const double inv_n = s.n > 0 ? 1.0 / (double)s.n : 0.0;
-        sc->p_corr[0] = tot[0] * inv_n;
-        sc->p_corr[1] = tot[1] * inv_n;
-        sc->p_corr[2] = tot[2] * inv_n;
-        sc->u_core = tot[3];
-        sc->u_shell = tot[4];
-        const double ut = tot[kPairPart + kVirPart];
-        sc->u_kspace = 0.5 * s.coulomb_k * ut;
-        if (energy)
-            for (int c = 0; c < 6; ++c)
-                sc->virial[c] = tot[kPairPart + c] + 0.5 * s.coulomb_k * tot[kPairPart + kVirPart + 1 + c];
-    }
+    if (q == 0) write_sums(s, tot, energy, close);
 }
 
 // Sums over modes [p0, p1) for one atom per lane, two modes at a time:
@@ -2135,26 +2230,35 @@ __device__ inline KPos kspace_pos(const DevSys& s, int i)
                 IPH ? s.ufix[i] : make_uint4(0, 0, 0, 0)};
 }
 
+// The mixed form's FP32 terms of one (atom, mode): w and, with FLUX, re.
+template <bool FLUX, bool IPH>
+__device__ inline void mode_terms_f32(const KDev& k, const KPos& at, const ModeRec& mr, int p, float& w, float& re)
+{
+    float c, sn;
+    if (IPH) {
+        const float tf = turns_fix(k.m[3 * p], k.m[3 * p + 1], k.m[3 * p + 2], at.fix);
+        c = __builtin_amdgcn_cosf(tf);
+        sn = __builtin_amdgcn_sinf(tf);
+    } else {
+        sincos_turns_f32(mode_phase(mr.mx, mr.my, mr.mz, at.u), c, sn);
+    }
+    // Im(e^{-i theta} rho) * coef = c * A - s * B
+    w = fmaf(c, mr.Af, -(sn * mr.Bf));
+    // Re(e^{-i theta} rho) * coef = c * B + s * A
+    re = FLUX ? fmaf(c, mr.Bf, sn * mr.Af) : 0.f;
+}
+
 template <bool MIXED, bool FLUX, bool IPH>
 __device__ inline void kspace_modes(const KDev& k, const double2* tab, const KPos& at, int p0, int p1, double* acc)
 {
     const double4 U = at.u;
-    const uint4 Uf = at.fix;
     auto one = [&](const ModeRec& mr, int p, double gm) {
         double w, re = 0.0;
         if (MIXED) {
-            float c, sn;
-            if (IPH) {
-                const float tf = turns_fix(k.m[3 * p], k.m[3 * p + 1], k.m[3 * p + 2], Uf);
-                c = __builtin_amdgcn_cosf(tf);
-                sn = __builtin_amdgcn_sinf(tf);
-            } else {
-                sincos_turns_f32(mode_phase(mr.mx, mr.my, mr.mz, U), c, sn);
-            }
-            // Im(e^{-i theta} rho) * coef = c * A - s * B
-            w = (double)fmaf(c, mr.Af, -(sn * mr.Bf));
-            // Re(e^{-i theta} rho) * coef = c * B + s * A
-            if (FLUX) re = (double)fmaf(c, mr.Bf, sn * mr.Af);
+            float wf, ref;
+            mode_terms_f32<FLUX, IPH>(k, at, mr, p, wf, ref);
+            w = (double)wf;
+            if (FLUX) re = (double)ref;
         } else {
             double c, sn;
             sincos1024(mode_phase(mr.mx, mr.my, mr.mz, U), tab, c, sn);
@@ -2224,6 +2328,56 @@ __device__ inline void slice_sum(double* acc, double* sm, int slices, int slice,
 #pragma unroll
                 for (int c = 0; c < W; ++c) acc[c0 + c] += sm[((q - 1) * W + c) * A + ta];
     }
+}
+
+// The sums of kspace_modes for a mixed-form launch short of wavefronts, in the
+// same order of every addition (a change of the last bit there can flip an
+// FP32 rounding later in a trajectory): the workgroup's wavefronts share the
+// modes of a tile and leave their FP32 terms in LDS, then wavefront c adds
+// quantity c over the tile's modes.  64 atoms per workgroup; the sums are left
+// in LDS at the returned address, [quantity][atom].
+constexpr int kChainTile = 128;  // modes
+template <bool FLUX, bool IPH>
+__device__ inline const double* kspace_chain(const DevSys& s, const KDev& k, double* sm, int wave, int waves, int i)
+{
+    constexpr int N = kKfAcc<FLUX>;
+    const int lane = threadIdx.x & 63;
+    double* out = sm;                                    // [N][64]
+    float* w_sm = reinterpret_cast<float*>(sm + N * 64);  // [kChainTile][64], then re's
+    float* re_sm = w_sm + kChainTile * 64;
+    const KPos at = kspace_pos<true, IPH>(s, min(i, s.n - 1));
+    double acc = 0.0;
+    for (int t0 = 0; t0 < k.n_modes; t0 += kChainTile) {
+        const int cnt = min(kChainTile, k.n_modes - t0);
+        for (int p = wave; p < cnt; p += waves) {
+            float w, re;
+            mode_terms_f32<FLUX, IPH>(k, at, k.modes[t0 + p], t0 + p, w, re);
+            w_sm[p * 64 + lane] = w;
+            if (FLUX) re_sm[p * 64 + lane] = re;
+        }
+        __syncthreads();
+        auto axis = [](const ModeRec& m, int a) { return a == 0 ? m.mx : (a == 1 ? m.my : m.mz); };
+        if (wave < 3) {
+#pragma unroll 4
+            for (int p = 0; p < cnt; ++p) acc = fma((double)w_sm[p * 64 + lane], axis(k.modes[t0 + p], wave), acc);
+        } else if (FLUX && wave == 3) {
+#pragma unroll 4
+            for (int p = 0; p < cnt; ++p) acc += (double)re_sm[p * 64 + lane];
+        } else if (FLUX && wave < N) {
+            // xx, yy, zz, xy, xz, yz
+            const int c = wave - 4, a = c < 3 ? c : (c == 5 ? 1 : 0), b = c < 3 ? c : (c == 3 ? 1 : 2);
+#pragma unroll 4
+            for (int p = 0; p < cnt; ++p) {
+                const ModeRec m = k.modes[t0 + p];
+                const double rg = (double)re_sm[p * 64 + lane] * k.mode_g[t0 + p];
+                acc = fma(rg * axis(m, a), axis(m, b), acc);
+            }
+        }
+        __syncthreads();
+    }
+    if (wave < N) out[wave * 64 + lane] = acc;
+    __syncthreads();
+    return out;
 }
 
 template <bool MIXED>
@@ -2307,6 +2461,11 @@ __global__ __launch_bounds__(SPLIT ? kKfThreads : kBlock) void k_kforce(RB_ARGS,
             for (int g = 0; g < k.kf_groups; ++g)
 #pragma unroll
                 for (int c = 0; c < N; ++c) acc[c] += k.kf_part[((size_t)g * N + c) * k.kf_pad + i];
+    } else if (MIXED && SPLIT && k.kf_chain) {
+        const double* sums = kspace_chain<FLUX, IPH>(s, k, slice_sm, wave, slices, i);
+        if (wave != 0) return;
+#pragma unroll
+        for (int c = 0; c < N; ++c) acc[c] = sums[c * 64 + ta];
     } else if (!SPLIT) {
         if (i < s.n) kspace_modes<MIXED, FLUX, IPH>(k, tab, kspace_pos<MIXED, IPH>(s, i), 0, k.n_modes, acc);
     } else {
@@ -2449,8 +2608,10 @@ __global__ __launch_bounds__(1024) void k_kinetic_finalize(const DevSys* __restr
             if (step_end) {
                 // closing half step; the velocities owe its factor until the
                 // next opening kick (exports apply it)
-                double K = ke;
-                f = nh_half(s, s.sc, K);
+                double K = ke, x = s.sc->nh_x, v = s.sc->nh_v;
+                f = nh_half(s, K, x, v);
+                s.sc->nh_x = x;
+                s.sc->nh_v = v;
                 s.sc->vpend = f;
                 s.sc->kinetic = K;
             } else {
@@ -2504,7 +2665,7 @@ __global__ __launch_bounds__(kBlock) void k_kick_drift(RB_ARGS, int scheduled)
     double d2 = 0.0;
     bool bad = false;
     const bool langevin = LANGEVIN && s.thermo_c > 0.0 && s.thermostat == kThermoLangevin;
-    const double lam = (s.thermo_c > 0.0 && !langevin) ? s.sc->vscale : 1.0;
+    const double lam = (s.thermo_c > 0.0 && !langevin) ? opening_factor(s) : 1.0;
     if (i < s.n) {
         const int ti = s.type[i];
         const double a = 0.5 * s.dt * s.spc->inv_mass_acc[ti];
@@ -2516,7 +2677,7 @@ __global__ __launch_bounds__(kBlock) void k_kick_drift(RB_ARGS, int scheduled)
         if (langevin) {
             // BAOAB: half drift, Ornstein-Uhlenbeck velocity update with
             // Box-Muller normals of the stream (id, step, kTagLangevin), half drift
-            PhiloxStream st(s.seed, (uint32_t)s.id[i], (uint32_t)s.sc->eval, kTagLangevin, s.replica);
+            PhiloxStream st(s.seed, (uint32_t)s.id[i], (uint32_t)(s.sc->eval + 1), kTagLangevin, s.replica);
             const double u1 = st.uniform(), u2 = st.uniform(), u3 = st.uniform(), u4 = st.uniform();
             // cos(2 pi u) and sin(2 pi u) as sincospi(2u): no large-argument reduction
             double sn2, cs2, sn4, cs4;
@@ -2883,7 +3044,6 @@ inline int blocks_for(int n, int b) { return (n + b - 1) / b; }
 
 // ---------------------------------------------------------------- launchers
 void launch_set_eval(const Plan& P, uint64_t eval, hipStream_t st) { k_set_eval<<<1, 64, 0, st>>>(P.sc, P.R, eval); }
-void launch_step_begin(const Plan& P, hipStream_t st) { k_step_begin<<<1, 64, 0, st>>>(P.sys, P.R); }
 void launch_init_scalars(const Plan& P, hipStream_t st) { k_init_scalars<<<1, 64, 0, st>>>(P.sc, P.R); }
 void launch_clear_flags(const Plan& P, hipStream_t st) { k_clear_flags<<<1, 64, 0, st>>>(P.sc, P.R); }
 
@@ -2894,10 +3054,10 @@ void launch_sort(const Plan& P, bool gate, hipStream_t st)
     if (P.atoms.blocks <= 0) return;
     const int g = gate ? 1 : 0;
     k_bin<<<P.atoms.blocks, kBlock, 0, st>>>(RB_MAP(atoms), g);
-    k_scan<<<P.R, 1024, 0, st>>>(P.sys, g);
-    k_scatter<<<P.atoms.blocks, kBlock, 0, st>>>(RB_MAP(atoms), g);
+    const int own_scan = P.max_cells <= kOwnScan ? 1 : 0;
+    if (!own_scan) k_scan<<<P.R, 1024, 0, st>>>(P.sys, g);
+    k_scatter<<<P.atoms.blocks, kBlock, 0, st>>>(RB_MAP(atoms), g, own_scan);
     k_cell_sort<<<P.cells.blocks, kBlock, 0, st>>>(RB_MAP(cells), g);
-    k_gather<<<P.atoms.blocks, kBlock, 0, st>>>(RB_MAP(atoms), g);
 }
 
 void launch_lists(const Plan& P, bool gate, hipStream_t st)
@@ -2955,7 +3115,7 @@ void launch_lists(const Plan& P, bool gate, hipStream_t st)
         if (P.stored && P.rows64.blocks > 0) k_select<<<P.rows64.blocks, 64, sm_sel, st>>>(RB_MAP(rows64), g, k);
     }
 #undef RB_LISTS
-    k_build_done<<<1, 64, 0, st>>>(P.sys, P.R, g);
+    if (!gate) k_build_done<<<1, 64, 0, st>>>(P.sys, P.R);
 }
 
 void launch_build(const Plan& P, bool gate, hipStream_t st)
@@ -3040,18 +3200,23 @@ void launch_rho_finalize(const Plan& P, bool energy, hipStream_t st)
         k_rho_finalize<<<P.modes1.blocks, 64, 0, st>>>(RB_MAP(modes1), P.kd, energy ? 1 : 0);
 }
 
-void launch_finalize(const Plan& P, bool energy, hipStream_t st)
+void launch_finalize(const Plan& P, bool energy, bool close, hipStream_t st)
 {
     if (P.R <= 0) return;
-    k_finalize_part<<<P.R * P.fin_grid, 256, 0, st>>>(P.sys, P.kd, energy ? 1 : 0, P.fin_grid);
-    k_finalize<<<P.R, 64, 0, st>>>(P.sys, P.kd, energy ? 1 : 0);
+    const int e = energy ? 1 : 0, c = close ? 1 : 0;
+    const bool one = P.fin_grid <= kFinOne;
+    k_finalize_part<<<one ? P.R : P.R * P.fin_grid, one ? 256 * P.fin_grid : 256, 0, st>>>(P.sys, P.kd, e,
+                                                                                         one ? 1 : P.fin_grid, c);
+    if (!one) k_finalize<<<P.R, 64, 0, st>>>(P.sys, P.kd, e, c);
 }
 
-// LDS of the slice sums: every thread but slice 0's hands over n values, at
-// most kSlicePass at a time.
+// LDS of the slice sums (every thread but slice 0's hands over n values, at
+// most kSlicePass at a time) or of kspace_chain.
 static size_t slice_lds(const Plan& P, int n)
 {
-    return P.kf_sliced ? sizeof(double) * (n < kSlicePass ? n : kSlicePass) * P.kf_threads : 0;
+    const size_t slices = P.kf_sliced ? sizeof(double) * (n < kSlicePass ? n : kSlicePass) * P.kf_threads : 0;
+    const size_t chain = P.kf_chain ? 64 * (sizeof(double) * n + sizeof(float) * kChainTile * (n > 3 ? 2 : 1)) : 0;
+    return slices > chain ? slices : chain;
 }
 
 void launch_kforce(const Plan& P, bool mixed, hipStream_t st)

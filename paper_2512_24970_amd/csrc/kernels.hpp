@@ -87,7 +87,7 @@ struct DevSys {
     // sort scratch
     double4* tp;
     double *tvx, *tvy, *tvz, *tfx, *tfy, *tfz;
-    int32_t *ttype, *tid, *cell_of, *slot_of, *order;
+    int32_t *ttype, *tid, *cell_of, *slot_of;
     int32_t *cell_count, *cell_start;
     // [ncell][8]: first position, within its list cell, of each of the
     // cell's eight ordering-grid sub-cells (x fastest); the cell sort keeps
@@ -141,6 +141,8 @@ struct KDev {
     int kf_groups;
     int kf_len;           // modes per slice
     int kf_waves;
+    int kf_chain;         // mixed form, launch short of wavefronts: the kf_waves of a workgroup share the modes
+                          // and the sums keep the order of one wavefront (no slices)
     int kf_pad;
     double* kf_part;
 };
@@ -152,10 +154,12 @@ constexpr int kVirPart = 6;
 // The reduction of those partials and of the modes' energies runs in two
 // passes: fin_blocks(n, modes) blocks per system (one per 256 wavefront
 // partials or 2048 modes, at most kFinBlocks), each over a fixed slice, then
-// one wavefront per system adding their kFin sums in block order.  The slicing
-// depends on the system's own size only, so a system sums in the same order
-// alone and in a batch.
+// one wavefront per system adding their kFin sums in block order.  Where no
+// system has more than kFinOne slices one block per system does both.  The
+// slicing depends on the system's own size only, so a system sums in the same
+// order alone and in a batch.
 constexpr int kFinBlocks = 32;
+constexpr int kFinOne = 4;  // 256 threads each: n up to 65536
 constexpr int kFin = kPairPart + kVirPart + 1 + 6;  // pair sums, virial, mode energy, mode virial
 constexpr int fin_blocks(int n, int modes)
 {
@@ -182,16 +186,21 @@ inline int pair_lanes_for(size_t atom_waves, bool mixed)
     return lanes;
 }
 
-// Split of the k-space force's modes.  Slices double while the system's
-// wavefronts would leave SIMDs with fewer than four and a slice keeps at least
-// 24 modes (a slice's own set-up is worth a few modes); groups on top, for the
-// full sum of a small system, until about eight wavefronts a SIMD, each with
-// at least 128 modes.  A launch (all systems of a batch) that has four
-// wavefronts a SIMD without them gives an atom's slices to one wavefront: 64
-// replicas, 100 modes, lost 1.4 % of a step with a wavefront per slice, while
-// the step of 32768 ions and 200 modes alone gained 14 % (FP64) and 9 % (mixed).
+// Split of the k-space force's modes (FP64 form, and the mixed form's sums of
+// more modes than kKfChainModes, which only the full sum has).  Slices double
+// while the system's wavefronts would leave SIMDs with fewer than four and a
+// slice keeps at least 24 modes (a slice's own set-up is worth a few modes);
+// groups on top, for the full sum of a small system, until about eight
+// wavefronts a SIMD, each with at least 128 modes.  A launch (all systems of a
+// batch) that has four wavefronts a SIMD without them gives an atom's slices to
+// one wavefront: 64 replicas, 100 modes, lost 1.4 % of a step with a wavefront
+// per slice, while the step of 32768 ions and 200 modes alone gained 14 % (FP64).
 constexpr int kKfThreads = 1024;  // largest workgroup of the k-space force
 constexpr int kKfFill = 4096;     // wavefronts: four on each of 1024 SIMDs
+// The mixed form's kf_chain: at least a few modes for each of 16 wavefronts,
+// and fewer than a wavefront a SIMD without it (it keeps three of the sixteen
+// busy while they add).
+constexpr int kKfChainModes = 2048, kKfChainMin = 48, kKfChainFill = 1024;
 constexpr int kKfSlices = 16, kKfGroups = 16;
 constexpr int kKfAccMax = 10;     // sums per atom (with the shares of energy and virial)
 inline void kforce_split(int n, int modes, int* slices, int* groups)
@@ -256,6 +265,7 @@ struct Plan {
     int kf_threads = 256;   // tune.kf_block, or more where a system's slices need it
     bool kf_split = false;  // some system cuts its modes into slices
     bool kf_sliced = false; // some system's slices take a wavefront each
+    bool kf_chain = false;  // some system's modes are shared as KDev::kf_chain says
     Shape cells;    // one block per cell
     Shape list_cells;  // list_parts blocks per cell (list build)
     // the same cells grouped by the staging capacity kListCaps[q] of their
@@ -274,6 +284,7 @@ struct Plan {
     bool iph = false;       // mixed form: k-space phases in 32-bit fixed point
     bool species_cut = false;  // species-dependent core radii
     int n_chunks = 1;     // build chunks (1 unless stored)
+    int max_cells = 0;    // most list cells of a system
     int fin_grid = 1;     // largest fin_blocks over the systems (blocks per system of the first pass)
     int cap_core = 0, cap_cand = 0;
     NearTab near;
@@ -281,14 +292,14 @@ struct Plan {
 };
 
 void launch_set_eval(const Plan& P, uint64_t eval, hipStream_t st);
-// start of a step: eval index + 1, and the opening Nose-Hoover half step
-void launch_step_begin(const Plan& P, hipStream_t st);
 // scalars that start at 1 (velocity factors), after the scalars are zeroed
 void launch_init_scalars(const Plan& P, hipStream_t st);
 void launch_clear_flags(const Plan& P, hipStream_t st);
 
-// cell sort + lists; with gate the kernels of a system run only when its
-// device-side rebuild flag is up (and lower it at the end)
+// cell sort + lists.  gate: a step's build; its first pass opens the step's
+// scalars (eval index + 1, the opening Nose-Hoover half step), the others run
+// for a system only when its device-side rebuild flag is up, and
+// launch_finalize with `close` lowers it
 void launch_build(const Plan& P, bool gate, hipStream_t st);
 // the two halves of launch_build: the cell sort (atoms reordered), then the
 // lists (which read the sorted positions and write only list data)
@@ -300,8 +311,9 @@ void launch_ksample(const Plan& P, hipStream_t st);
 void launch_pair(const Plan& P, bool mixed, bool energy, hipStream_t st);
 void launch_rho(const Plan& P, bool mixed, hipStream_t st);
 void launch_rho_finalize(const Plan& P, bool energy, hipStream_t st);
-// momentum correction and energies; with `energy` also the virial
-void launch_finalize(const Plan& P, bool energy, hipStream_t st);
+// momentum correction and energies; with `energy` also the virial; close: end
+// a step's build
+void launch_finalize(const Plan& P, bool energy, bool close, hipStream_t st);
 // k-space force (eq. 29) into the total-force arrays
 void launch_kforce(const Plan& P, bool mixed, hipStream_t st);
 // total force = short range - momentum correction + k-space; with kick the
