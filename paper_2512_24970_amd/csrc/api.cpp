@@ -369,6 +369,7 @@ void plan_launches(rbsog_ctx* c)
     size_t waves = 0;
     for (const auto& s : c->hs) waves += blocks_for(s.n, 64);
     P.pair_lanes = pair_lanes_for(waves, c->mixed);
+    P.single = single_stream_for(waves);
     P.max_cells = 0;
     for (const auto& s : c->hs) P.max_cells = std::max(P.max_cells, s.ncell);
     P.kf_threads = P.tune.kf_block;
@@ -609,23 +610,28 @@ void enqueue_forces(rbsog_ctx* c, bool energy, bool kick, bool build = false)
     const Plan& P = c->plan;
     // an evaluation with energies takes the fused k-space pass, which forms
     // the per-atom k-space shares of the stress and heat flux
-    const bool aux_kf = P.tune.kf_aux && !energy;
+    // captured, the fork and join cost little; launched one by one they cost a
+    // small system more than its overlap gains
+    const bool fork = !P.single || c->use_graph;
+    const bool aux_kf = P.tune.kf_aux && !energy && fork;
     hipStream_t st = c->stream;
-    hipStream_t ax = c->aux;
+    hipStream_t ax = fork ? c->aux : st;
     if (P.atoms.blocks <= 0) return;
     if (build) {
         c->begin(RBSOG_PHASE_BUILD);
         launch_sort(P, true, st);
         c->end();
     }
-    HIP_OK(hipEventRecord(c->ev_fork, st));
-    HIP_OK(hipStreamWaitEvent(ax, c->ev_fork, 0));
+    if (fork) {
+        HIP_OK(hipEventRecord(c->ev_fork, st));
+        HIP_OK(hipStreamWaitEvent(ax, c->ev_fork, 0));
+    }
     if (P.modes64.blocks > 0) {
-        c->begin(RBSOG_PHASE_KSAMPLE, true);
+        c->begin(RBSOG_PHASE_KSAMPLE, fork);
         launch_ksample(P, ax);
         c->end();
     }
-    c->begin(RBSOG_PHASE_RHO, true);
+    c->begin(RBSOG_PHASE_RHO, fork);
     launch_rho(P, c->mixed, ax);
     launch_rho_finalize(P, energy, ax);
     c->end();
@@ -634,7 +640,7 @@ void enqueue_forces(rbsog_ctx* c, bool energy, bool kick, bool build = false)
         launch_kforce(P, c->mixed, ax);
         c->end();
     }
-    HIP_OK(hipEventRecord(c->ev_join, ax));
+    if (fork) HIP_OK(hipEventRecord(c->ev_join, ax));
     if (build) {
         c->begin(RBSOG_PHASE_BUILD);
         launch_lists(P, true, st);
@@ -644,7 +650,7 @@ void enqueue_forces(rbsog_ctx* c, bool energy, bool kick, bool build = false)
     launch_pair(P, c->mixed, energy, st);
     HIP_OK(hipGetLastError());  // a launch the device refuses (e.g. LDS size) must not pass silently
     c->end();
-    HIP_OK(hipStreamWaitEvent(st, c->ev_join, 0));
+    if (fork) HIP_OK(hipStreamWaitEvent(st, c->ev_join, 0));
     c->begin(RBSOG_PHASE_REDUCE);
     launch_finalize(P, energy, build, st);
     c->end();

@@ -2336,7 +2336,16 @@ __device__ inline void slice_sum(double* acc, double* sm, int slices, int slice,
 // modes of a tile and leave their FP32 terms in LDS, then wavefront c adds
 // quantity c over the tile's modes.  64 atoms per workgroup; the sums are left
 // in LDS at the returned address, [quantity][atom].
-constexpr int kChainTile = 128;  // modes
+constexpr int kChainTile = 128;  // modes, a multiple of 64
+
+// Lane p's value of v (p wave-uniform).
+__device__ inline double lane_value(double v, int p)
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, p);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), p);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
 template <bool FLUX, bool IPH>
 __device__ inline const double* kspace_chain(const DevSys& s, const KDev& k, double* sm, int wave, int waves, int i)
 {
@@ -2347,8 +2356,27 @@ __device__ inline const double* kspace_chain(const DevSys& s, const KDev& k, dou
     float* re_sm = w_sm + kChainTile * 64;
     const KPos at = kspace_pos<true, IPH>(s, min(i, s.n - 1));
     double acc = 0.0;
+    // quantity c of wavefront c: w m_a, re, re g m_a m_b (xx, yy, zz, xy, xz, yz)
+    const int c = wave - 4;
+    const int ax_a = wave < 3 ? wave : (c < 3 ? c : (c == 5 ? 1 : 0)), ax_b = c < 3 ? c : (c == 3 ? 1 : 2);
     for (int t0 = 0; t0 < k.n_modes; t0 += kChainTile) {
         const int cnt = min(kChainTile, k.n_modes - t0);
+        // the adding wavefronts' mode factors, a mode to a lane, on the way
+        // while the terms are formed: the adds read them by lane
+        double fa[kChainTile / 64] = {}, fb[kChainTile / 64] = {}, fg[kChainTile / 64] = {};
+        if (wave < N && wave != 3) {
+#pragma unroll
+            for (int h = 0; h < kChainTile / 64; ++h) {
+                const int p = min(t0 + 64 * h + lane, k.n_modes - 1);
+                const double* m = &k.modes[p].mx;
+                fa[h] = m[ax_a];
+                if (FLUX && wave > 3) {
+                    fb[h] = m[ax_b];
+                    fg[h] = k.mode_g[p];
+                }
+            }
+        }
+#pragma unroll 2
         for (int p = wave; p < cnt; p += waves) {
             float w, re;
             mode_terms_f32<FLUX, IPH>(k, at, k.modes[t0 + p], t0 + p, w, re);
@@ -2356,21 +2384,29 @@ __device__ inline const double* kspace_chain(const DevSys& s, const KDev& k, dou
             if (FLUX) re_sm[p * 64 + lane] = re;
         }
         __syncthreads();
-        auto axis = [](const ModeRec& m, int a) { return a == 0 ? m.mx : (a == 1 ? m.my : m.mz); };
-        if (wave < 3) {
-#pragma unroll 4
-            for (int p = 0; p < cnt; ++p) acc = fma((double)w_sm[p * 64 + lane], axis(k.modes[t0 + p], wave), acc);
-        } else if (FLUX && wave == 3) {
-#pragma unroll 4
-            for (int p = 0; p < cnt; ++p) acc += (double)re_sm[p * 64 + lane];
-        } else if (FLUX && wave < N) {
-            // xx, yy, zz, xy, xz, yz
-            const int c = wave - 4, a = c < 3 ? c : (c == 5 ? 1 : 0), b = c < 3 ? c : (c == 3 ? 1 : 2);
-#pragma unroll 4
-            for (int p = 0; p < cnt; ++p) {
-                const ModeRec m = k.modes[t0 + p];
-                const double rg = (double)re_sm[p * 64 + lane] * k.mode_g[t0 + p];
-                acc = fma(rg * axis(m, a), axis(m, b), acc);
+        if (wave < N) {
+#pragma unroll
+            for (int h = 0; h < kChainTile / 64; ++h) {
+                const int top = min(64, cnt - 64 * h);
+                const float* src = (wave < 3 ? w_sm : re_sm) + 64 * 64 * h + lane;
+                auto add = [&](float x, int p) {
+                    const double v = (double)x;
+                    if (wave < 3)
+                        acc = fma(v, lane_value(fa[h], p), acc);
+                    else if (FLUX && wave == 3)
+                        acc += v;
+                    else if (FLUX)
+                        acc = fma(v * lane_value(fg[h], p) * lane_value(fa[h], p), lane_value(fb[h], p), acc);
+                };
+                int p = 0;
+                for (; p + 8 <= top; p += 8) {
+                    float x[8];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) x[q] = src[64 * (p + q)];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) add(x[q], p + q);
+                }
+                for (; p < top; ++p) add(src[64 * p], p);
             }
         }
         __syncthreads();

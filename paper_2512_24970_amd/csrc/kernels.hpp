@@ -171,6 +171,15 @@ constexpr int fin_blocks(int n, int modes)
 // sum m v_a v_b (6), sum (m v^2 / 2) v (3), sum (e_i v + W_i v) (3).
 constexpr int kFluxPart = 12;
 
+// Whether a launch (all systems of a batch) runs its k-space chain on the one
+// stream, when its kernels are not replayed from a graph: the four event calls
+// of a fork and join take about 28 us a step.  Measured with two streams and
+// with one, us per step launched kernel by kernel: 512 ions FP64 95 / 81, 32768
+// FP64 102 / 93 and mixed 123 / 106, 131072 FP64 187 / 171 and mixed 169 / 152;
+// from graphs two streams win (131072 mixed 140 / 153), as they do at 10^6.
+constexpr size_t kSingleWaves = 2048;
+inline bool single_stream_for(size_t atom_waves) { return atom_waves <= kSingleWaves; }
+
 // Lanes that share an atom's core list, and its shell batch, in the pair
 // kernel: the more the fewer wavefronts the launch (all systems of a batch) has
 // with one, while that adds wavefronts to SIMDs that have under two (FP64) or
@@ -278,6 +287,7 @@ struct Plan {
     Shape modes64;  // 64-mode blocks of the systems that draw modes
     Shape rho;      // rho blocks: local block = mode tile * n_chunks + chunk (tiles of 64 rho_mpl modes)
     Shape modes1;   // one block per mode
+    bool single = false;  // one stream: the fork and join cost more than the overlap gains (single_stream_for)
     int list_mode = 0;  // < kListPerAtom: per-cell list kernel staging kListCaps[mode] atoms; else per-atom kernel
     bool stored = false;  // memory form: batch drawn at the build
     bool langevin = false;  // some system runs the Langevin thermostat
