@@ -370,7 +370,8 @@ void plan_launches(rbsog_ctx* c)
     for (const auto& s : c->hs) waves += blocks_for(s.n, 64);
     P.pair_lanes = pair_lanes_for(waves, c->mixed);
     P.single = single_stream_for(waves);
-    P.max_cells = 0;
+    P.max_cells = P.rho_chunk = 0;
+    for (const auto& k : c->hk) P.rho_chunk = std::max(P.rho_chunk, k.chunk);
     for (const auto& s : c->hs) P.max_cells = std::max(P.max_cells, s.ncell);
     P.kf_threads = P.tune.kf_block;
     P.kf_split = P.kf_sliced = P.kf_chain = false;
@@ -1340,7 +1341,7 @@ void set_batch_impl(rbsog_ctx* c, int R, const rbsog_params* params, const int32
     // grouped systems always take a wavefront per slice
     for (auto& k : c->hk) {
         k.kf_waves = (k.kf_groups > 1 || n_waves < (size_t)kKfFill) ? k.kf_slices : 1;
-        k.kf_chain = c->mixed && k.n_modes >= kKfChainMin && k.n_modes <= kKfChainModes && n_waves < (size_t)kKfChainFill;
+        k.kf_chain = c->mixed && k.n_modes >= kKfChainMin && k.n_modes <= kKfChainModes && n_waves <= (size_t)kKfChainFill;
         if (k.kf_chain) k.kf_waves = kKfThreads / 64;
     }
     c->kcdf.alloc(sizeof(double) * std::max<size_t>(1, cdf_doubles) + sizeof(int32_t) * cdf_ints);

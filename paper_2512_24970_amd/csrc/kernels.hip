@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include <climits>
+#include <cstddef>
 #include <cstdint>
 #include <mutex>
 #include <type_traits>
@@ -1891,7 +1892,13 @@ __device__ inline float turns_fix(int mx, int my, int mz, const uint4& U)
     return (float)(int32_t)ph * 2.3283064365386963e-10f;
 }
 
-template <bool MIXED, int MPL, bool IPH>
+// STAGE: every chunk has at most kRhoStage atoms, which each wavefront copies
+// to LDS first: in a launch with few wavefronts the loop waits for every scalar
+// read of four atoms, while a large one hides them behind its other wavefronts
+// (with the reduction, 200 modes: 32768 ions FP64 24 -> 16 us, mixed 17 -> 13;
+// 131072 FP64 58 -> 34, mixed 28 -> 23; from 262144 the chunks are longer).
+constexpr int kRhoStage = 256;
+template <bool MIXED, int MPL, bool IPH, bool STAGE>
 __global__ __launch_bounds__(kBlock) void k_rho(RB_ARGS, const KDev* __restrict__ kd)
 {
     RB_SYS(blockIdx.x)
@@ -1900,6 +1907,7 @@ __global__ __launch_bounds__(kBlock) void k_rho(RB_ARGS, const KDev* __restrict_
     const int tile = lb / k.n_chunks;
     __shared__ double2 tab[MIXED ? 1 : kTableSize];
     __shared__ double red[4][64 * MPL][2];
+    __shared__ double4 staged[STAGE ? kRhoStage : 1];  // x, y, z, charge
     using qreal = typename std::conditional<MIXED, float, double>::type;
     __shared__ qreal qs[kMaxSpecies];
     if (!MIXED)
@@ -1928,6 +1936,15 @@ __global__ __launch_bounds__(kBlock) void k_rho(RB_ARGS, const KDev* __restrict_
     const int qw = k.chunk >> 2;
     const int a0 = chunk * k.chunk + wave * qw;
     const int a1 = min(s.n, a0 + qw);
+    double4* own = staged + (STAGE ? wave * qw : 0);
+    if (STAGE) {
+        for (int t = a0 + lane; t < a1; t += 64) {
+            double4 P = s.p[t];
+            P.w = (double)qs[(int)P.w];
+            own[t - a0] = P;
+        }
+        wave_lds_fence();
+    }
     int a = a0;
     if (IPH) {
         for (; a + 4 <= a1; a += 4) {
@@ -1961,9 +1978,15 @@ __global__ __launch_bounds__(kBlock) void k_rho(RB_ARGS, const KDev* __restrict_
         }
     }
     for (; !IPH && a + 4 <= a1; a += 4) {
-        const double4 P0 = s.p[a], P1 = s.p[a + 1], P2 = s.p[a + 2], P3 = s.p[a + 3];
-        const int4 T = *reinterpret_cast<const int4*>(s.type + a);
-        const qreal q0 = qs[T.x], q1 = qs[T.y], q2 = qs[T.z], q3 = qs[T.w];
+        const double4* src = STAGE ? own + (a - a0) : s.p + a;
+        const double4 P0 = src[0], P1 = src[1], P2 = src[2], P3 = src[3];
+        qreal q0, q1, q2, q3;
+        if (STAGE) {
+            q0 = (qreal)P0.w, q1 = (qreal)P1.w, q2 = (qreal)P2.w, q3 = (qreal)P3.w;
+        } else {
+            const int4 T = *reinterpret_cast<const int4*>(s.type + a);
+            q0 = qs[T.x], q1 = qs[T.y], q2 = qs[T.z], q3 = qs[T.w];
+        }
 #pragma unroll
         for (int j = 0; j < MPL; ++j) {
             const double t0 = mode_phase(kx[j], ky[j], kz[j], P0), t1 = mode_phase(kx[j], ky[j], kz[j], P1);
@@ -2336,23 +2359,19 @@ __device__ inline void slice_sum(double* acc, double* sm, int slices, int slice,
 // modes of a tile and leave their FP32 terms in LDS, then wavefront c adds
 // quantity c over the tile's modes.  64 atoms per workgroup; the sums are left
 // in LDS at the returned address, [quantity][atom].
-constexpr int kChainTile = 128;  // modes, a multiple of 64
+constexpr int kChainTile = 128;  // modes
 
-// Lane p's value of v (p wave-uniform).
-__device__ inline double lane_value(double v, int p)
-{
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, p);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), p);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
+constexpr int kRecWords = sizeof(ModeRec) / sizeof(double);
+static_assert(sizeof(ModeRec) == 64 && offsetof(ModeRec, my) == 8 && offsetof(ModeRec, mz) == 16, "m by axis");
 template <bool FLUX, bool IPH>
 __device__ inline const double* kspace_chain(const DevSys& s, const KDev& k, double* sm, int wave, int waves, int i)
 {
     constexpr int N = kKfAcc<FLUX>;
     const int lane = threadIdx.x & 63;
-    double* out = sm;                                    // [N][64]
-    float* w_sm = reinterpret_cast<float*>(sm + N * 64);  // [kChainTile][64], then re's
+    double* out = sm;                                         // [N][64]
+    double* rec = sm + N * 64;                                // [kChainTile] mode records
+    double* g_sm = rec + kChainTile * kRecWords;              // their g
+    float* w_sm = reinterpret_cast<float*>(g_sm + kChainTile);  // [kChainTile][64], then re's
     float* re_sm = w_sm + kChainTile * 64;
     const KPos at = kspace_pos<true, IPH>(s, min(i, s.n - 1));
     double acc = 0.0;
@@ -2361,53 +2380,37 @@ __device__ inline const double* kspace_chain(const DevSys& s, const KDev& k, dou
     const int ax_a = wave < 3 ? wave : (c < 3 ? c : (c == 5 ? 1 : 0)), ax_b = c < 3 ? c : (c == 3 ? 1 : 2);
     for (int t0 = 0; t0 < k.n_modes; t0 += kChainTile) {
         const int cnt = min(kChainTile, k.n_modes - t0);
-        // the adding wavefronts' mode factors, a mode to a lane, on the way
-        // while the terms are formed: the adds read them by lane
-        double fa[kChainTile / 64] = {}, fb[kChainTile / 64] = {}, fg[kChainTile / 64] = {};
-        if (wave < N && wave != 3) {
-#pragma unroll
-            for (int h = 0; h < kChainTile / 64; ++h) {
-                const int p = min(t0 + 64 * h + lane, k.n_modes - 1);
-                const double* m = &k.modes[p].mx;
-                fa[h] = m[ax_a];
-                if (FLUX && wave > 3) {
-                    fb[h] = m[ax_b];
-                    fg[h] = k.mode_g[p];
-                }
-            }
-        }
+        // the tile's mode records by one read of the workgroup (read one by one
+        // through the scalar unit, each was waited for)
+        const double* src = reinterpret_cast<const double*>(k.modes + t0);
+        for (int t = threadIdx.x; t < cnt * kRecWords; t += blockDim.x) rec[t] = src[t];
+        if (FLUX && (int)threadIdx.x < cnt) g_sm[threadIdx.x] = k.mode_g[t0 + threadIdx.x];
+        __syncthreads();
 #pragma unroll 2
         for (int p = wave; p < cnt; p += waves) {
             float w, re;
-            mode_terms_f32<FLUX, IPH>(k, at, k.modes[t0 + p], t0 + p, w, re);
+            mode_terms_f32<FLUX, IPH>(k, at, *reinterpret_cast<const ModeRec*>(rec + p * kRecWords), t0 + p, w, re);
             w_sm[p * 64 + lane] = w;
             if (FLUX) re_sm[p * 64 + lane] = re;
         }
         __syncthreads();
         if (wave < N) {
+            const float* v_sm = (wave < 3 ? w_sm : re_sm) + lane;
+            auto add = [&](int p) {
+                const double v = (double)v_sm[64 * p];
+                const double* m = rec + p * kRecWords;
+                if (wave < 3)
+                    acc = fma(v, m[ax_a], acc);
+                else if (FLUX && wave == 3)
+                    acc += v;
+                else if (FLUX)
+                    acc = fma(v * g_sm[p] * m[ax_a], m[ax_b], acc);
+            };
+            int p = 0;
+            for (; p + 8 <= cnt; p += 8)
 #pragma unroll
-            for (int h = 0; h < kChainTile / 64; ++h) {
-                const int top = min(64, cnt - 64 * h);
-                const float* src = (wave < 3 ? w_sm : re_sm) + 64 * 64 * h + lane;
-                auto add = [&](float x, int p) {
-                    const double v = (double)x;
-                    if (wave < 3)
-                        acc = fma(v, lane_value(fa[h], p), acc);
-                    else if (FLUX && wave == 3)
-                        acc += v;
-                    else if (FLUX)
-                        acc = fma(v * lane_value(fg[h], p) * lane_value(fa[h], p), lane_value(fb[h], p), acc);
-                };
-                int p = 0;
-                for (; p + 8 <= top; p += 8) {
-                    float x[8];
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) x[q] = src[64 * (p + q)];
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) add(x[q], p + q);
-                }
-                for (; p < top; ++p) add(src[64 * p], p);
-            }
+                for (int q = 0; q < 8; ++q) add(p + q);
+            for (; p < cnt; ++p) add(p);
         }
         __syncthreads();
     }
@@ -3213,21 +3216,27 @@ void launch_rho(const Plan& P, bool mixed, hipStream_t st)
     if (P.rho.blocks <= 0) return;
     const int nb = P.rho.blocks;
     const bool iph = mixed && P.iph;
-    if (P.tune.rho_mpl == 2) {
-        if (iph)
-            k_rho<true, 2, true><<<nb, kBlock, 0, st>>>(RB_MAP(rho), P.kd);
-        else if (mixed)
-            k_rho<true, 2, false><<<nb, kBlock, 0, st>>>(RB_MAP(rho), P.kd);
-        else
-            k_rho<false, 2, false><<<nb, kBlock, 0, st>>>(RB_MAP(rho), P.kd);
-    } else {
-        if (iph)
-            k_rho<true, 1, true><<<nb, kBlock, 0, st>>>(RB_MAP(rho), P.kd);
-        else if (mixed)
-            k_rho<true, 1, false><<<nb, kBlock, 0, st>>>(RB_MAP(rho), P.kd);
-        else
-            k_rho<false, 1, false><<<nb, kBlock, 0, st>>>(RB_MAP(rho), P.kd);
-    }
+    const bool stage = P.rho_chunk <= kRhoStage;
+#define RB_RHO(M, L, I, S) k_rho<M, L, I, S><<<nb, kBlock, 0, st>>>(RB_MAP(rho), P.kd)
+#define RB_RHO_L(L)                     \
+    do {                                \
+        if (iph)                        \
+            RB_RHO(true, L, true, false);   \
+        else if (mixed && stage)        \
+            RB_RHO(true, L, false, true);   \
+        else if (mixed)                 \
+            RB_RHO(true, L, false, false);  \
+        else if (stage)                 \
+            RB_RHO(false, L, false, true);  \
+        else                            \
+            RB_RHO(false, L, false, false); \
+    } while (0)
+    if (P.tune.rho_mpl == 2)
+        RB_RHO_L(2);
+    else
+        RB_RHO_L(1);
+#undef RB_RHO_L
+#undef RB_RHO
 }
 
 void launch_rho_finalize(const Plan& P, bool energy, hipStream_t st)
@@ -3251,7 +3260,9 @@ void launch_finalize(const Plan& P, bool energy, bool close, hipStream_t st)
 static size_t slice_lds(const Plan& P, int n)
 {
     const size_t slices = P.kf_sliced ? sizeof(double) * (n < kSlicePass ? n : kSlicePass) * P.kf_threads : 0;
-    const size_t chain = P.kf_chain ? 64 * (sizeof(double) * n + sizeof(float) * kChainTile * (n > 3 ? 2 : 1)) : 0;
+    const size_t chain = P.kf_chain ? 64 * (sizeof(double) * n + sizeof(float) * kChainTile * (n > 3 ? 2 : 1)) +
+                                          sizeof(double) * kChainTile * (kRecWords + 1)
+                                    : 0;
     return slices > chain ? slices : chain;
 }
 

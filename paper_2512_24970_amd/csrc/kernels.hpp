@@ -207,8 +207,10 @@ inline int pair_lanes_for(size_t atom_waves, bool mixed)
 constexpr int kKfThreads = 1024;  // largest workgroup of the k-space force
 constexpr int kKfFill = 4096;     // wavefronts: four on each of 1024 SIMDs
 // The mixed form's kf_chain: at least a few modes for each of 16 wavefronts,
-// and fewer than a wavefront a SIMD without it (it keeps three of the sixteen
-// busy while they add).
+// and at most a wavefront a SIMD without it (65536 atoms).  Three of the sixteen
+// add while the others wait, so a launch that fills the SIMDs is better without:
+// 200 modes, us per launch, one wavefront per 64 atoms / shared: 512 ions 36 / 11,
+// 32768 37 / 15.
 constexpr int kKfChainModes = 2048, kKfChainMin = 48, kKfChainFill = 1024;
 constexpr int kKfSlices = 16, kKfGroups = 16;
 constexpr int kKfAccMax = 10;     // sums per atom (with the shares of energy and virial)
@@ -295,6 +297,7 @@ struct Plan {
     bool species_cut = false;  // species-dependent core radii
     int n_chunks = 1;     // build chunks (1 unless stored)
     int max_cells = 0;    // most list cells of a system
+    int rho_chunk = 0;    // largest atom chunk of the rho kernel
     int fin_grid = 1;     // largest fin_blocks over the systems (blocks per system of the first pass)
     int cap_core = 0, cap_cand = 0;
     NearTab near;
