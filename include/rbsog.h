@@ -308,18 +308,20 @@ rbsog_status rbsog_set_list_capacity(rbsog_ctx* ctx, int32_t cap_core, int32_t c
  * calls.  Needs no GPU work. */
 rbsog_status rbsog_set_list_chunks(rbsog_ctx* ctx, int32_t chunks);
 
-/* Launch shapes of the hot kernels and the stream of the k-space force.  No
- * choice changes a result bit: partial sums are taken per 64-atom wavefront
+/* Launch shapes of the hot kernels and the stream of the k-space force; a set
+ * chooses them from the form and the number of atoms.  No choice changes a result bit: partial sums are taken per 64-atom wavefront
  * and every structure factor is summed over the atoms in the same order
  * whatever the shape. */
 typedef struct {
-    int32_t pair_block; /* atoms per workgroup of the pair kernel: 64, 128, 256 (default 256) */
-    int32_t pair_ku;    /* neighbour positions fetched ahead per lane (shell-batch tile): 4, 8 (4) */
-    int32_t rho_mpl;    /* k-modes per lane of the rho kernel (64 rho_mpl per workgroup): 1, 2 (1) */
+    int32_t pair_block; /* atoms per workgroup of the pair kernel: 64, 128, 256 (small systems:
+                           64, several lanes an atom) */
+    int32_t pair_ku;    /* neighbour positions fetched ahead per lane (shell-batch tile): 4, 8 */
+    int32_t rho_mpl;    /* k-modes per lane of the rho kernel (64 rho_mpl per workgroup): 1, 2 */
     int32_t kf_block;   /* threads per workgroup of the k-space force kernel: 64, 128, 256 (256); a
                            small system takes more (its modes are split over wavefronts) */
     int32_t kf_aux;     /* 1: the k-space force follows rho on the second stream, beside the pair
-                           kernel; 0: it runs after the pair kernel on the context's stream (1) */
+                           kernel; 0: it runs after the pair kernel on the context's stream (1;
+                           small systems launched kernel by kernel use one stream) */
 } rbsog_tuning;
 
 /* Choose the launch shapes by timing from the current state (HIP events on

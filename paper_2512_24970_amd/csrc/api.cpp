@@ -1095,7 +1095,6 @@ void set_batch_impl(rbsog_ctx* c, int R, const rbsog_params* params, const int32
     c->msd_marked.assign(R, 0);
     c->sel = 0;
     c->row_slack = 1.25;
-    c->plan.tune = Tuning{};
     c->plan.langevin = false;
     c->plan.species_cut = false;
     c->plan.iph = (p0.flags & RBSOG_FLAG_INT_PHASE) != 0;
@@ -1338,6 +1337,9 @@ void set_batch_impl(rbsog_ctx* c, int R, const rbsog_params* params, const int32
         n_modes_all += (size_t)k.n_modes;
         rho_part_all += 2 * (size_t)k.n_chunks * k.n_modes_pad;
     }
+    int modes_max = 0;
+    for (const auto& k : c->hk) modes_max = std::max(modes_max, k.n_modes);
+    c->plan.tune = default_tuning(c->mixed, n_waves, modes_max);
     // grouped systems always take a wavefront per slice
     for (auto& k : c->hk) {
         k.kf_waves = (k.kf_groups > 1 || n_waves < (size_t)kKfFill) ? k.kf_slices : 1;

@@ -3205,8 +3205,8 @@ void launch_pair(const Plan& P, bool mixed, bool energy, hipStream_t st)
         launch_pair_ku<4, 4>(P, mixed, energy, st);
     else if (P.pair_lanes == 2)
         launch_pair_ku<4, 2>(P, mixed, energy, st);
-    else if (P.tune.pair_ku == 8)
-        launch_pair_ku<8, 1>(P, mixed, energy, st);
+    else if (P.tune.pair_ku == 8 && !energy)  // with energies eight more records cost a wavefront a SIMD
+        launch_pair_ku<8, 1>(P, mixed, false, st);
     else
         launch_pair_ku<4, 1>(P, mixed, energy, st);
 }

@@ -241,6 +241,23 @@ struct Tuning {
     int kf_aux = 1;        // k-space force on the second stream (1) or after the pair kernel (0)
 };
 
+// Launch shapes before any tuning, from the form, the wavefronts of all
+// systems' atoms and the most modes of a system.  10 steps in ms with 256 atoms,
+// 4 fetched ahead and one mode a lane for every size, and with these: 10^6 ions
+// mixed 11.2 / 10.2 and FP64 15.2 / 14.5, 64 replicas 4.56 / 4.35, 3 10^5 mixed
+// 3.66 / 3.40.  Smaller pair workgroups let the k-space chain's wavefronts in
+// between; two modes a lane halve the reads of the atoms, where the launch has
+// wavefronts enough with half of them (5 10^6 ions with 1000 modes are better
+// with one).
+inline Tuning default_tuning(bool mixed, size_t atom_waves, int modes)
+{
+    Tuning t;
+    t.pair_block = 128;
+    if (mixed && atom_waves > 3000) t.pair_ku = 8;
+    if (atom_waves > (mixed ? 3000u : 4096u) && modes <= 768) t.rho_mpl = 2;
+    return t;
+}
+
 // Near-field table of the pair kernel (built on the host, shared by a batch).
 // FP32 for the mixed form: interval idx = (bits(r^2) >> 17) - lo, valid below
 // n; per interval two float4, the CF and CU cubics in t = r^2 - start.  FP64:
