@@ -101,6 +101,9 @@ struct rbsog_ctx {
 
     std::vector<DevSys> hs;          // host images of the device system records
     std::vector<KDev> hk;
+    // every mode of the full k-sum, in enumeration order, where the device holds
+    // its second half (mode q and mode n-1-q are opposite)
+    std::vector<std::vector<int32_t>> full_modes;
     Plan plan;
 
     // device memory
@@ -528,16 +531,12 @@ void snapshot(rbsog_ctx* c, bool save)
         void* p;
         size_t b;
     };
-    const Arr arr[] = {{s.p, sizeof(double4)}, {s.vx, 8}, {s.vy, 8}, {s.vz, 8}, {s.fx, 8}, {s.fy, 8},
-                       {s.fz, 8},              {s.type, 4}, {s.id, 4}, {s.inv, 4},
-                       {c->plan.sc, 0}};
+    // positions, velocities and forces follow each other, as do the integers
+    const Arr arr[] = {{s.p, N * (sizeof(double4) + 6 * sizeof(double))}, {s.type, N * 3 * sizeof(int32_t)},
+                       {c->plan.sc, sizeof(DeviceScalars) * c->R}};
     for (const Arr& a : arr) {
-        const size_t b = a.b ? a.b * N : sizeof(DeviceScalars) * c->R;
-        if (save)
-            HIP_OK(hipMemcpyAsync(d, a.p, b, hipMemcpyDeviceToDevice, c->stream));
-        else
-            HIP_OK(hipMemcpyAsync(a.p, d, b, hipMemcpyDeviceToDevice, c->stream));
-        d += b;
+        HIP_OK(hipMemcpyAsync(save ? d : a.p, save ? a.p : d, a.b, hipMemcpyDeviceToDevice, c->stream));
+        d += a.b;
     }
 }
 
@@ -1292,6 +1291,7 @@ void set_batch_impl(rbsog_ctx* c, int R, const rbsog_params* params, const int32
     HIP_OK(hipMemcpy(c->sogk.as<double>() + sog_c.size(), sog_s2.data(), sizeof(double) * sog_s2.size(),
                      hipMemcpyHostToDevice));
     std::vector<std::vector<int32_t>> em(R);
+    c->full_modes.assign(R, {});
     std::vector<std::vector<double>> ecoef(R);
     size_t cdf_doubles = 0, cdf_ints = 0, n_modes_all = 0, rho_part_all = 0, kf_part_all = 0;
     for (int r = 0; r < R; ++r) {
@@ -1316,6 +1316,17 @@ void set_batch_impl(rbsog_ctx* c, int R, const rbsog_params* params, const int32
         } else {
             enumerate_modes(c->sog, p.box, &em[r], &ecoef[r]);
             k.sampled = 0;
+            if (!c->mixed) {
+                // k and -k give each ion the same force and the same energy
+                // (rho(-k) is rho(k)'s conjugate): FP64 sums the second half
+                // of the list, which mirrors the first, with twice the weight.
+                // The mixed form keeps both (their FP32 phases round apart).
+                const size_t half = ecoef[r].size() / 2;
+                c->full_modes[r] = em[r];
+                em[r].erase(em[r].begin(), em[r].begin() + 3 * half);
+                ecoef[r].erase(ecoef[r].begin(), ecoef[r].begin() + half);
+                for (double& v : ecoef[r]) v *= 2.0;
+            }
             k.n_modes = (int)ecoef[r].size();
             k.S = 0.0;
         }
@@ -2114,7 +2125,11 @@ rbsog_status rbsog_get_kmodes(rbsog_ctx* ctx, uint64_t eval, int32_t* m, double*
             launch_set_eval(P1, ctx->eval, ctx->stream);
         }
         HIP_OK(hipStreamSynchronize(ctx->stream));
-        HIP_OK(hipMemcpy(m, k.m, sizeof(int32_t) * 3 * (size_t)k.n_modes, hipMemcpyDeviceToHost));
+        const auto& full = ctx->full_modes[ctx->sel];
+        if (!full.empty())
+            std::memcpy(m, full.data(), sizeof(int32_t) * full.size());
+        else
+            HIP_OK(hipMemcpy(m, k.m, sizeof(int32_t) * 3 * (size_t)k.n_modes, hipMemcpyDeviceToHost));
     });
 }
 
@@ -2125,8 +2140,13 @@ rbsog_status rbsog_get_rho(rbsog_ctx* ctx, double* rho)
         require(rho != nullptr, RBSOG_E_ARG, "rho is NULL");
         const KDev& k = ctx->hk[ctx->sel];
         HIP_OK(hipStreamSynchronize(ctx->stream));
-        if (k.n_modes > 0)
-            HIP_OK(hipMemcpy(rho, k.rho, sizeof(double) * 2 * (size_t)k.n_modes, hipMemcpyDeviceToHost));
+        const size_t half = k.n_modes, n = ctx->full_modes[ctx->sel].size() / 3;
+        double* out = n > 0 ? rho + 2 * (n - half) : rho;
+        if (k.n_modes > 0) HIP_OK(hipMemcpy(out, k.rho, sizeof(double) * 2 * half, hipMemcpyDeviceToHost));
+        for (size_t q = 0; q < n - half && n > 0; ++q) {
+            rho[2 * q] = rho[2 * (n - 1 - q)];
+            rho[2 * q + 1] = -rho[2 * (n - 1 - q) + 1];
+        }
     });
 }
 

@@ -2142,7 +2142,7 @@ __global__ __launch_bounds__(256 * kFinOne) void k_finalize_part(const DevSys* _
     const int nb = (s.n + 63) / 64;  // wavefront partials
     const int bs = min(b, nf);       // a slice past the last is empty
     const int w0 = nb * bs / nf, w1 = nb * min(b + 1, nf) / nf;  // nb * 32 fits 32 bits
-    __shared__ double red[4 * kFinOne];
+    __shared__ double red[4 * kFinOne][kFin];
     __shared__ double row[kFinOne][kFin];
     double v[kPairPart + kVirPart];
     for (int c = 0; c < kPairPart + kVirPart; ++c) v[c] = 0.0;
@@ -2174,25 +2174,22 @@ __global__ __launch_bounds__(256 * kFinOne) void k_finalize_part(const DevSys* _
             wk[5] -= eg * ky * kz;
         }
     }
-    // nc and energy are uniform, so every thread takes part in each sum: the
-    // slice's four wavefronts in order, kept by its first thread
-    auto slice_total = [&](double x, int c) {
-        x = wave_sum(x);
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
-        __syncthreads();
-        if (tid == 0) row[slice][c] = ((red[4 * slice] + red[4 * slice + 1]) + red[4 * slice + 2]) + red[4 * slice + 3];
-        __syncthreads();
-    };
-    if (!energy && threadIdx.x < kFin)
-        for (int q = 0; q < (int)(blockDim.x >> 8); ++q) row[q][threadIdx.x] = 0.0;
+    // each quantity over the slice's four wavefronts in order
+    double all[kFin];
+#pragma unroll
+    for (int c = 0; c < kPairPart + kVirPart; ++c) all[c] = c < nc ? wave_sum(v[c]) : 0.0;
+    all[kPairPart + kVirPart] = wave_sum(ue);
+#pragma unroll
+    for (int c = 0; c < 6; ++c) all[kPairPart + kVirPart + 1 + c] = energy ? wave_sum(wk[c]) : 0.0;
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int c = 0; c < kFin; ++c) red[threadIdx.x >> 6][c] = all[c];
     __syncthreads();
-#pragma unroll
-    for (int c = 0; c < kPairPart + kVirPart; ++c)
-        if (c < nc) slice_total(v[c], c);
-    slice_total(ue, kPairPart + kVirPart);
-    if (energy)
-#pragma unroll
-        for (int c = 0; c < 6; ++c) slice_total(wk[c], kPairPart + kVirPart + 1 + c);
+    if (tid < kFin) {
+        const double(*q)[kFin] = red + 4 * slice;
+        row[slice][tid] = ((q[0][tid] + q[1][tid]) + q[2][tid]) + q[3][tid];
+    }
+    __syncthreads();
     if (grid > 1) {
         if (threadIdx.x < kFin) s.fin_part[(size_t)b * kFin + threadIdx.x] = row[0][threadIdx.x];
     } else if (threadIdx.x == 0) {
@@ -2626,20 +2623,39 @@ __global__ __launch_bounds__(1024) void k_kinetic_finalize(const DevSys* __restr
     const DevSys s = global_view(sys[blockIdx.x]);
     const double* part = s.kin_part;
     const int nb = (s.n + 63) / 64;  // wavefront partials
-    __shared__ double red[16];
-    double v = 0.0;
-#pragma unroll 4
-    for (int b = threadIdx.x; b < nb; b += blockDim.x) v += part[b];
-    const double t = block_sum(v, red);
-    double ft[kFluxPart];
+    // every quantity by all threads, then over the sixteen wavefronts in order
+    __shared__ double red[16][1 + kFluxPart];
+    __shared__ double sums[1 + kFluxPart];
+    double v[1 + kFluxPart];
+#pragma unroll
+    for (int c = 0; c < 1 + kFluxPart; ++c) v[c] = 0.0;
     if (flux) {
-        for (int c = 0; c < kFluxPart; ++c) {
-            double x = 0.0;
-#pragma unroll 4
-            for (int b = threadIdx.x; b < nb; b += blockDim.x) x += s.flux_part[(size_t)b * kFluxPart + c];
-            ft[c] = block_sum(x, red);
+#pragma unroll 2
+        for (int b = threadIdx.x; b < nb; b += blockDim.x) {
+            v[0] += part[b];
+#pragma unroll
+            for (int c = 0; c < kFluxPart; ++c) v[1 + c] += s.flux_part[(size_t)b * kFluxPart + c];
         }
+    } else {
+#pragma unroll 8
+        for (int b = threadIdx.x; b < nb; b += blockDim.x) v[0] += part[b];
     }
+    const int nq = flux ? 1 + kFluxPart : 1;
+#pragma unroll
+    for (int c = 0; c < 1 + kFluxPart; ++c)
+        if (c < nq) {
+            const double w = wave_sum(v[c]);
+            if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][c] = w;
+        }
+    __syncthreads();
+    if ((int)threadIdx.x < nq) {
+        double x = 0.0;
+        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) x += red[w][threadIdx.x];
+        sums[threadIdx.x] = x;
+    }
+    __syncthreads();
+    const double t = sums[0];
+    const double* ft = sums + 1;
     if (threadIdx.x == 0) {
         const double ke = t / kAccUnit;
         double f = 1.0;

@@ -63,6 +63,34 @@ def test_grouped_full_sum(n):
         assert np.abs(a - b).max() <= 1e-10 * np.abs(b).max(), key
 
 
+def test_full_sum_exports_every_mode():
+    """FP64 sums one of each pair k, -k; the exported modes and structure
+    factors are still every k != 0 of the sum, in order, as the oracle's."""
+    import ctypes as C
+
+    import torch
+    print("case: full sum exports", flush=True)
+    cfg = _cfg(514)
+    sysp = dict(cfg["sys"], p_r=0, p_f=0)
+    ctx = R.Context(0)
+    dev = torch.device("cuda", 0)
+    ctx.rbsog_set_system(R.make_params(sysp, R.FP64, n_atoms=514),
+                         *(torch.as_tensor(cfg[k], device=dev) for k in ("types", "pos", "vel")))
+    ctx.rbsog_compute_forces(0)
+    L, s = cfg["sys"]["box"][0], ctx.rbsog_get_sog()["s"]
+    top = int(np.floor(np.sqrt(90.0) / (s * 2 * np.pi / L)))
+    g = np.arange(-top, top + 1)
+    m = np.stack(np.meshgrid(g, g, g, indexing="ij"), -1).reshape(-1, 3)
+    k2 = ((m * (2 * np.pi / L)) ** 2).sum(1)
+    m = m[(k2 > 0) & (0.5 * s * s * k2 <= 45.0)].astype(np.int32)
+    got = np.zeros((len(m) + 8, 3), np.int32)
+    assert R.lib().rbsog_get_kmodes(ctx._h, 0, C.c_void_p(got.ctypes.data), None) == 0
+    assert np.array_equal(got[:len(m)], m) and not got[len(m):].any()
+    rho = ctx.rbsog_get_rho(len(m))
+    ref = O.System(sysp, cfg["types"], cfg["pos"], cfg["vel"]).rho(m)
+    assert np.abs(rho - ref).max() <= 1e-11 * np.abs(ref).max()
+
+
 def test_batch_of_split_and_whole_systems_equals_singles():
     """A batch whose systems differ in slices and groups: each system's forces
     are bit for bit those of the system alone."""
