@@ -1846,16 +1846,20 @@ __global__ __launch_bounds__(64) void k_ksample(RB_ARGS, const KDev* __restrict_
 }
 
 // e^{2 pi i t / 1024} for a phase t in units of 2 pi / 1024: table entry
-// rint(t) mod 1024 rotated by the remainder, whose sine and cosine come from
-// short Taylor series (|x| <= pi/1024, truncation below 1e-18).
+// rint(t) mod 1024 rotated by the remainder d, whose sine and cosine come from
+// short Taylor series in d (an angle of at most pi/1024, truncation below
+// 1e-18).  Adding 1.5 2^52 rounds t to the nearest integer and leaves it in the
+// low bits (|t| < 2^31: a mode component times 1024).
 __device__ inline void sincos1024(double t, const double2* tab, double& c, double& s)
 {
-    const double j = rint(t);
-    const double x = (t - j) * (2.0 * kPi / kTableSize);
-    const double x2 = x * x;
-    const double cd = fma(x2, fma(x2, 1.0 / 24.0, -0.5), 1.0);
-    const double sd = fma(x * x2, fma(x2, 1.0 / 120.0, -1.0 / 6.0), x);
-    const double2 T = tab[((int)j) & (kTableSize - 1)];
+    constexpr double kUnit = 2.0 * kPi / kTableSize, kUnit2 = kUnit * kUnit;
+    constexpr double kRound = 6755399441055744.0;
+    const double tj = t + kRound;
+    const double d = t - (tj - kRound);
+    const double d2 = d * d;
+    const double cd = fma(d2, fma(d2, kUnit2 * kUnit2 / 24.0, -0.5 * kUnit2), 1.0);
+    const double sd = d * fma(d2, fma(d2, kUnit2 * kUnit2 * kUnit / 120.0, -kUnit2 * kUnit / 6.0), kUnit);
+    const double2 T = tab[(int)(uint32_t)(unsigned long long)__double_as_longlong(tj) & (kTableSize - 1)];
     c = fma(T.x, cd, -(T.y * sd));
     s = fma(T.y, cd, T.x * sd);
 }
