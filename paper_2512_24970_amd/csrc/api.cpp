@@ -70,6 +70,28 @@ struct DBuf {
     ~DBuf() { release(); }
 };
 
+// Pinned host memory owned by the context: copies into it need no staging.
+struct HBuf {
+    void* p = nullptr;
+    size_t bytes = 0;
+    void reserve(size_t b)
+    {
+        if (bytes >= b) return;
+        if (p) (void)hipHostFree(p);
+        p = nullptr;
+        bytes = 0;
+        if (hipHostMalloc(&p, b, hipHostMallocDefault) != hipSuccess) {
+            p = nullptr;
+            throw Error(RBSOG_E_OOM, "hipHostMalloc of " + std::to_string(b) + " bytes failed");
+        }
+        bytes = b;
+    }
+    ~HBuf()
+    {
+        if (p) (void)hipHostFree(p);
+    }
+};
+
 }  // namespace
 
 struct rbsog_ctx {
@@ -119,6 +141,11 @@ struct rbsog_ctx {
     // mean-square displacement: [n_user][3] last positions, then [n_user][3]
     // unwrapped displacements; which systems have a marked origin
     DBuf msd_buf;
+    HBuf h_scalars;  // [R] the device scalars as last read
+    // the scalars hold the kinetic energy and velocity factor of the current
+    // velocities in the current atom order: the last call was a step (and no
+    // system is Nose-Hoover, whose closing half step rounds them differently)
+    bool kinetic_fresh = false;
     DBuf obs_buf;  // scratch of the pair histogram and the displacement sums, kept between calls
     std::vector<char> msd_marked;
 
@@ -504,10 +531,11 @@ void enqueue_build(rbsog_ctx* c, bool gate)
 
 std::vector<DeviceScalars> read_scalars(rbsog_ctx* c)
 {
-    std::vector<DeviceScalars> h(c->R);
-    HIP_OK(hipMemcpyAsync(h.data(), c->plan.sc, sizeof(DeviceScalars) * c->R, hipMemcpyDeviceToHost, c->stream));
+    const size_t bytes = sizeof(DeviceScalars) * c->R;
+    HIP_OK(hipMemcpyAsync(c->h_scalars.p, c->plan.sc, bytes, hipMemcpyDeviceToHost, c->stream));
     HIP_OK(hipStreamSynchronize(c->stream));
-    return h;
+    const DeviceScalars* h = static_cast<const DeviceScalars*>(c->h_scalars.p);
+    return std::vector<DeviceScalars>(h, h + c->R);
 }
 
 int any_overflow(const std::vector<DeviceScalars>& h)
@@ -534,10 +562,15 @@ void snapshot(rbsog_ctx* c, bool save)
     // positions, velocities and forces follow each other, as do the integers
     const Arr arr[] = {{s.p, N * (sizeof(double4) + 6 * sizeof(double))}, {s.type, N * 3 * sizeof(int32_t)},
                        {c->plan.sc, sizeof(DeviceScalars) * c->R}};
+    CopyList list{};
     for (const Arr& a : arr) {
-        HIP_OK(hipMemcpyAsync(save ? d : a.p, save ? a.p : d, a.b, hipMemcpyDeviceToDevice, c->stream));
+        list.dst[list.n] = save ? d : a.p;
+        list.src[list.n] = save ? a.p : d;
+        list.bytes[list.n++] = a.b;
         d += a.b;
     }
+    launch_copy(list, c->stream);
+    HIP_OK(hipGetLastError());
 }
 
 // After a build that overflowed: grow what overflowed (bit 1: list
@@ -576,6 +609,7 @@ void grow_after_overflow(rbsog_ctx* c, int o)
 // Build; if a list or cell capacity overflowed, grow it and build again.
 void build_checked(rbsog_ctx* c)
 {
+    c->kinetic_fresh = false;
     for (int attempt = 0; attempt < 6; ++attempt) {
         launch_clear_flags(c->plan, c->stream);
         enqueue_build(c, false);
@@ -592,6 +626,13 @@ bool any_thermostat(const rbsog_ctx* c)
 {
     for (const auto& s : c->hs)
         if (s.thermo_c > 0.0 && s.thermostat != RBSOG_THERMO_LANGEVIN) return true;
+    return false;
+}
+
+bool any_nose_hoover(const rbsog_ctx* c)
+{
+    for (const auto& s : c->hs)
+        if (s.thermo_c > 0.0 && s.thermostat == RBSOG_THERMO_NOSE_HOOVER) return true;
     return false;
 }
 
@@ -774,6 +815,7 @@ void autotune(rbsog_ctx* c, int reps)
 {
     const bool was_profiling = c->profiling;
     c->profiling = false;
+    c->kinetic_fresh = false;
     hipStream_t st = c->stream;
     launch_set_eval(c->plan, c->eval, st);
     enqueue_forces(c, false, false);
@@ -1142,6 +1184,7 @@ void set_batch_impl(rbsog_ctx* c, int R, const rbsog_params* params, const int32
     c->at_ew.alloc(sizeof(double4) * 2 * N);
     c->ufix.alloc(sizeof(uint4) * N);
     c->scalars.alloc(sizeof(DeviceScalars) * R);
+    c->h_scalars.reserve(sizeof(DeviceScalars) * R);
     HIP_OK(hipMemsetAsync(c->scalars.p, 0, sizeof(DeviceScalars) * R, c->stream));
     {
         Plan p1;
@@ -1442,6 +1485,7 @@ void set_batch_impl(rbsog_ctx* c, int R, const rbsog_params* params, const int32
         HIP_OK(hipStreamSynchronize(c->stream));
     }
     c->have_system = true;
+    c->kinetic_fresh = false;
     c->eval = 0;
     c->forces_valid = false;
     c->stale = false;
@@ -1702,6 +1746,7 @@ rbsog_status rbsog_compute_forces(rbsog_ctx* ctx, uint64_t eval, double* force_o
         require(!ctx->stale, RBSOG_E_LIST_STALE,
                 "an atom moved more than skin/2 since the last list build; call rbsog_build_lists");
         launch_set_eval(ctx->plan, eval, ctx->stream);
+        ctx->kinetic_fresh = false;
         enqueue_forces(ctx, e_out != nullptr, false);
         ctx->eval = eval;
         ctx->forces_valid = true;
@@ -1748,7 +1793,7 @@ void step_impl(rbsog_ctx* ctx, int32_t n_steps, rbsog_energy* e_last)
             ctx->forces_valid = true;
         }
         launch_set_eval(ctx->plan, ctx->eval, ctx->stream);
-        if (any_thermostat(ctx)) {
+        if (any_thermostat(ctx) && !ctx->kinetic_fresh) {
             // velocity factor of the first step from the current velocities
             launch_kinetic(ctx->plan, ctx->stream);
             launch_kinetic_finalize(ctx->plan, false, false, ctx->stream);
@@ -1758,6 +1803,7 @@ void step_impl(rbsog_ctx* ctx, int32_t n_steps, rbsog_energy* e_last)
         // with larger lists
         for (int attempt = 0;; ++attempt) {
             snapshot(ctx, true);
+            ctx->kinetic_fresh = false;
             for (int k = 0; k < n_steps; ++k) {
                 const uint64_t step = ctx->eval + 1 + (uint64_t)k;
                 const bool scheduled = step % (uint64_t)every == 0;
@@ -1769,6 +1815,7 @@ void step_impl(rbsog_ctx* ctx, int32_t n_steps, rbsog_energy* e_last)
             const int o = any_overflow(h);
             if (o == 0) {
                 ctx->eval += (uint64_t)n_steps;
+                ctx->kinetic_fresh = !any_nose_hoover(ctx);
                 if (e_last) fill_energy(ctx, h, e_last);
                 return;
             }

@@ -321,6 +321,16 @@ struct Plan {
     Tuning tune;
 };
 
+// Device-to-device copies in one launch (each a runtime call and a kernel of
+// its own otherwise); addresses and sizes are multiples of 4 bytes.
+struct CopyList {
+    int n;
+    void* dst[3];
+    const void* src[3];
+    size_t bytes[3];
+};
+void launch_copy(const CopyList& c, hipStream_t st);
+
 void launch_set_eval(const Plan& P, uint64_t eval, hipStream_t st);
 // scalars that start at 1 (velocity factors), after the scalars are zeroed
 void launch_init_scalars(const Plan& P, hipStream_t st);
