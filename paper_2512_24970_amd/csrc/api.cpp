@@ -399,7 +399,8 @@ void plan_launches(rbsog_ctx* c)
     size_t waves = 0;
     for (const auto& s : c->hs) waves += blocks_for(s.n, 64);
     P.pair_lanes = pair_lanes_for(waves, c->mixed);
-    P.single = single_stream_for(waves);
+    P.single = single_stream_for(waves, false, c->mixed);
+    P.single_graph = single_stream_for(waves, true, c->mixed);
     P.max_cells = P.rho_chunk = 0;
     for (const auto& k : c->hk) P.rho_chunk = std::max(P.rho_chunk, k.chunk);
     for (const auto& s : c->hs) P.max_cells = std::max(P.max_cells, s.ncell);
@@ -645,37 +646,43 @@ bool any_nose_hoover(const rbsog_ctx* c)
 // build: a step's gated list build goes in first.  Only its cell sort
 // (which reorders the atoms) precedes the fork: the k-space chain needs the
 // sorted positions but not the lists, so it runs beside the list kernels.
+// A small launch (single_stream_for) keeps the chain on the one stream instead:
+// the modes are drawn beside the cell sort, the structure factors summed beside
+// the pair kernel and finalized beside the force sums, each pair in one launch.
 void enqueue_forces(rbsog_ctx* c, bool energy, bool kick, bool build = false)
 {
     const bool ke = energy || (kick && any_thermostat(c));
     const Plan& P = c->plan;
     // an evaluation with energies takes the fused k-space pass, which forms
     // the per-atom k-space shares of the stress and heat flux
-    // captured, the fork and join cost little; launched one by one they cost a
-    // small system more than its overlap gains
-    const bool fork = !P.single || c->use_graph;
+    const bool fork = !(c->use_graph ? P.single_graph : P.single);
     const bool aux_kf = P.tune.kf_aux && !energy && fork;
+    // on one stream, kernels that neither wait for each other nor fill the
+    // chip share a launch (but are timed one by one)
+    const bool joint = !fork && !c->profiling;
     hipStream_t st = c->stream;
     hipStream_t ax = fork ? c->aux : st;
     if (P.atoms.blocks <= 0) return;
     if (build) {
         c->begin(RBSOG_PHASE_BUILD);
-        launch_sort(P, true, st);
+        launch_sort(P, true, joint, st);
         c->end();
     }
     if (fork) {
         HIP_OK(hipEventRecord(c->ev_fork, st));
         HIP_OK(hipStreamWaitEvent(ax, c->ev_fork, 0));
     }
-    if (P.modes64.blocks > 0) {
+    if (P.modes64.blocks > 0 && !(joint && build)) {
         c->begin(RBSOG_PHASE_KSAMPLE, fork);
         launch_ksample(P, ax);
         c->end();
     }
-    c->begin(RBSOG_PHASE_RHO, fork);
-    launch_rho(P, c->mixed, ax);
-    launch_rho_finalize(P, energy, ax);
-    c->end();
+    if (!joint) {
+        c->begin(RBSOG_PHASE_RHO, fork);
+        launch_rho(P, c->mixed, ax);
+        launch_rho_finalize(P, energy, ax);
+        c->end();
+    }
     if (aux_kf) {
         c->begin(RBSOG_PHASE_KFORCE, true);
         launch_kforce(P, c->mixed, ax);
@@ -688,12 +695,15 @@ void enqueue_forces(rbsog_ctx* c, bool energy, bool kick, bool build = false)
         c->end();
     }
     c->begin(RBSOG_PHASE_PAIR);
-    launch_pair(P, c->mixed, energy, st);
+    if (joint)
+        launch_pair_rho(P, c->mixed, energy, st);
+    else
+        launch_pair(P, c->mixed, energy, st);
     HIP_OK(hipGetLastError());  // a launch the device refuses (e.g. LDS size) must not pass silently
     c->end();
     if (fork) HIP_OK(hipStreamWaitEvent(st, c->ev_join, 0));
     c->begin(RBSOG_PHASE_REDUCE);
-    launch_finalize(P, energy, build, st);
+    launch_finalize(P, energy, build, joint, st);
     c->end();
     if (aux_kf) {
         c->begin(RBSOG_PHASE_INTEGRATE);
@@ -828,7 +838,7 @@ void autotune(rbsog_ctx* c, int reps)
     launch_rho(c->plan, c->mixed, st);
     launch_rho_finalize(c->plan, false, st);
     launch_pair(c->plan, c->mixed, false, st);
-    launch_finalize(c->plan, false, false, st);
+    launch_finalize(c->plan, false, false, false, st);
     // a first pick of the k-space force workgroup size, the kernel alone
     // (refined on whole steps below)
     double tb = 1e300;

@@ -477,8 +477,20 @@ __device__ inline void gather_atom(const DevSys& s, int t, int o)
 // lanes; a larger one (a small box is one cell) by the whole block over LDS.
 // The sorted atoms go straight to their places (a pass of its own over the
 // permutation read and wrote it once more, and was one more launch).
-__global__ __launch_bounds__(kBlock) void k_cell_sort(RB_ARGS, int gate)
+// Workgroups past n_cells (launches on one stream) draw the step's n_modes
+// k-space modes instead, one per wavefront, whether or not there is a build:
+// with the structure factors finalized beside the force sums, two launches fewer
+// (a step of 32768 ions FP64 84 -> 78 us, of 512 71 -> 67).
+__device__ inline void sample_mode(RB_ARGS, const KDev* __restrict__ kd, int mode);
+__global__ __launch_bounds__(kBlock) void k_cell_sort(RB_ARGS, int gate, int n_cells,
+                                                      const int2* __restrict__ mode_map,
+                                                      const KDev* __restrict__ kd, int n_modes)
 {
+    if ((int)blockIdx.x >= n_cells) {
+        const int mode = ((int)blockIdx.x - n_cells) * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        if (mode < n_modes) sample_mode(sys, mode_map, kd, mode);
+        return;
+    }
     RB_SYS(blockIdx.x)
     RB_GATE
     __shared__ int32_t key[kCellCap];
@@ -1318,17 +1330,16 @@ constexpr int kDrawMax = 64;   // largest batch drawn by several lanes together
 // passed through LDS.
 // LPA = 1: blockDim.x / 2 atoms per workgroup; else 64.
 template <bool MIXED, bool ENERGY, int KU, int LPA>
-__global__ __launch_bounds__(LPA == 1 ? 2 * kBlock : 128 * LPA) void k_pair(RB_ARGS, NearTab nt)
+__device__ inline void pair_block(RB_ARGS, const NearTab& nt, float4* dyn_sm, int block)
 {
     static_assert(LPA == 1 || LPA == 2 || LPA == 4, "group_lane");
-    RB_SYS(xcd_block(blockIdx.x, gridDim.x))
+    RB_SYS(block)
     // dynamic LDS, sized by the launch: the near-field table (F coefficients,
     // with energies also U), the sums handed to the
     // final lanes (the core half's, and with LPA > 1 the shell half's and its
     // weight), then the Floyd masks of the per-evaluation draw, and with LPA >
     // 1 the drawn ranks.  Kept small: the kernel waits on neighbour gathers,
     // so resident waves are what counts.
-    extern __shared__ float4 dyn_sm[];
     using Sum = PairSum<ENERGY>;
     constexpr int N = Sum::N;
     constexpr int kVecs = MIXED ? 1 : 4;  // float4s of one interval's F (or U) coefficients
@@ -1824,9 +1835,9 @@ __device__ inline int first_above_wave(const double* cdf, int len, double u)
 // Draw the P_F modes of eq. (28): component (m, d) by its mass, then the
 // three axis indices from their 1D lattice distributions, then signs.  One
 // wavefront per mode (the searches are wave-cooperative).
-__global__ __launch_bounds__(64) void k_ksample(RB_ARGS, const KDev* __restrict__ kd)
+__device__ inline void sample_mode(RB_ARGS, const KDev* __restrict__ kd, int mode)
 {
-    RB_SYS(blockIdx.x)
+    RB_SYS(mode)
     const KDev k = global_view(kd[rb_m.x]);
     const int p = lb;
     if (!k.sampled || p >= k.n_modes) return;
@@ -1845,7 +1856,7 @@ __global__ __launch_bounds__(64) void k_ksample(RB_ARGS, const KDev* __restrict_
         if (nn > 0 && ((signs >> a) & 1u)) nn = -nn;
         mi[a] = nn;
     }
-    if (threadIdx.x != 0) return;
+    if ((threadIdx.x & 63) != 0) return;
     k.m[3 * p] = mi[0];
     k.m[3 * p + 1] = mi[1];
     k.m[3 * p + 2] = mi[2];
@@ -1865,6 +1876,11 @@ __global__ __launch_bounds__(64) void k_ksample(RB_ARGS, const KDev* __restrict_
     r.Af = 0.0f;
     r.Bf = 0.0f;
     k.modes[p] = r;
+}
+
+__global__ __launch_bounds__(64) void k_ksample(RB_ARGS, const KDev* __restrict__ kd)
+{
+    sample_mode(sys, bmap, kd, blockIdx.x);
 }
 
 // e^{2 pi i t / 1024} for a phase t in units of 2 pi / 1024: table entry
@@ -1924,20 +1940,28 @@ __device__ inline float turns_fix(int mx, int my, int mz, const uint4& U)
 // (with the reduction, 200 modes: 32768 ions FP64 24 -> 16 us, mixed 17 -> 13;
 // 131072 FP64 58 -> 34, mixed 28 -> 23; from 262144 the chunks are longer).
 constexpr int kRhoStage = 256;
+template <bool MIXED, int MPL, bool STAGE>
+struct RhoLds {
+    using qreal = typename std::conditional<MIXED, float, double>::type;
+    double4 staged[STAGE ? kRhoStage : 1];  // x, y, z, charge
+    double2 tab[MIXED ? 1 : kTableSize];
+    double red[4][64 * MPL][2];
+    qreal qs[kMaxSpecies];
+};
 template <bool MIXED, int MPL, bool IPH, bool STAGE>
-__global__ __launch_bounds__(kBlock) void k_rho(RB_ARGS, const KDev* __restrict__ kd)
+__device__ inline void rho_block(RB_ARGS, const KDev* __restrict__ kd, RhoLds<MIXED, MPL, STAGE>& lds, int block)
 {
-    RB_SYS(blockIdx.x)
+    RB_SYS(block)
     const KDev k = global_view(kd[rb_m.x]);
     const int chunk = lb % k.n_chunks;
     const int tile = lb / k.n_chunks;
-    __shared__ double2 tab[MIXED ? 1 : kTableSize];
-    __shared__ double red[4][64 * MPL][2];
-    __shared__ double4 staged[STAGE ? kRhoStage : 1];  // x, y, z, charge
-    using qreal = typename std::conditional<MIXED, float, double>::type;
-    __shared__ qreal qs[kMaxSpecies];
+    using qreal = typename RhoLds<MIXED, MPL, STAGE>::qreal;
+    double2* tab = lds.tab;
+    auto& red = lds.red;
+    double4* staged = lds.staged;
+    qreal* qs = lds.qs;
     if (!MIXED)
-        for (int t = threadIdx.x; t < kTableSize; t += blockDim.x)
+        for (int t = threadIdx.x; t < kTableSize; t += kBlock)
             tab[t] = make_double2(k.table[2 * t], k.table[2 * t + 1]);
     if (threadIdx.x < kMaxSpecies) qs[threadIdx.x] = (qreal)s.spc->q[threadIdx.x];
     __syncthreads();
@@ -2078,6 +2102,40 @@ __global__ __launch_bounds__(kBlock) void k_rho(RB_ARGS, const KDev* __restrict_
     }
 }
 
+template <bool MIXED, int MPL, bool IPH, bool STAGE>
+__global__ __launch_bounds__(kBlock) void k_rho(RB_ARGS, const KDev* __restrict__ kd)
+{
+    __shared__ RhoLds<MIXED, MPL, STAGE> lds;
+    rho_block<MIXED, MPL, IPH, STAGE>(sys, bmap, kd, lds, blockIdx.x);
+}
+
+template <bool MIXED, bool ENERGY, int KU, int LPA>
+__global__ __launch_bounds__(LPA == 1 ? 2 * kBlock : 128 * LPA) void k_pair(RB_ARGS, NearTab nt)
+{
+    extern __shared__ float4 dyn_sm[];
+    pair_block<MIXED, ENERGY, KU, LPA>(sys, bmap, nt, dyn_sm, xcd_block(blockIdx.x, gridDim.x));
+}
+
+// Both in one launch, for launches on one stream: neither reads what the other
+// writes, and a small launch leaves SIMDs idle beside either.  The first n_pair
+// workgroups are the pair kernel's, the others (their first 256 threads) the
+// structure factors'; the two share the dynamic LDS.  A step without energies,
+// us separate / joint: 4096 ions, 200 modes FP64 61 / 55, mixed 57 / 53; 32768
+// ions FP64 78 / 70, 801 modes 107 / 100.
+constexpr int kJointRho = 512;
+template <bool MIXED, bool ENERGY, int LPA>
+__global__ __launch_bounds__(128 * LPA) void k_pair_rho(RB_ARGS, NearTab nt, const int2* __restrict__ rho_map,
+                                                        const KDev* __restrict__ kd, int n_pair)
+{
+    extern __shared__ float4 dyn_sm[];
+    if ((int)blockIdx.x < n_pair) {
+        pair_block<MIXED, ENERGY, 4, LPA>(sys, bmap, nt, dyn_sm, xcd_block(blockIdx.x, n_pair));
+    } else if (threadIdx.x < kBlock) {
+        using Lds = RhoLds<MIXED, 1, true>;
+        rho_block<MIXED, 1, false, true>(sys, rho_map, kd, *reinterpret_cast<Lds*>(dyn_sm), blockIdx.x - n_pair);
+    }
+}
+
 // g = -F^'(k)/(k F^(k)) of a mode (strain derivative of F^) by one wavefront,
 // the Gaussians over its lanes; every lane returns it.
 __device__ inline double mode_g(const KDev& k, double k2)
@@ -2096,12 +2154,12 @@ __device__ inline double mode_g(const KDev& k, double k2)
 // rho_p = sum over chunks (fixed tree), then the per-mode force coefficients
 // and, with energies, the mode's g (in the force-sum reduction, whose blocks
 // are few, the full sum's exponentials took 3.6 ms of a 4096-ion evaluation).
-__global__ __launch_bounds__(64) void k_rho_finalize(RB_ARGS, const KDev* __restrict__ kd, int energy)
+__device__ inline void finalize_mode(RB_ARGS, const KDev* __restrict__ kd, int energy, int mode)
 {
-    RB_SYS(blockIdx.x)
+    RB_SYS(mode)
     const KDev k = global_view(kd[rb_m.x]);
     const int p = lb;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
     double re = 0.0, im = 0.0;
     // unrolled so the loads are in flight together; the sum order is unchanged
 #pragma unroll 8
@@ -2130,6 +2188,11 @@ __global__ __launch_bounds__(64) void k_rho_finalize(RB_ARGS, const KDev* __rest
     }
 }
 
+__global__ __launch_bounds__(64) void k_rho_finalize(RB_ARGS, const KDev* __restrict__ kd, int energy)
+{
+    finalize_mode(sys, bmap, kd, energy, blockIdx.x);
+}
+
 // The evaluation's scalars from its kFin sums: momentum correction (eq. 26),
 // energies, virial; close: a step's build, if there was one, ends here.
 __device__ inline void write_sums(const DevSys& s, const double* tot, int energy, int close)
@@ -2141,11 +2204,11 @@ __device__ inline void write_sums(const DevSys& s, const double* tot, int energy
     sc->p_corr[2] = tot[2] * inv_n;
     sc->u_core = tot[3];
     sc->u_shell = tot[4];
-    const double ut = tot[kPairPart + kVirPart];
-    sc->u_kspace = 0.5 * s.coulomb_k * ut;
-    if (energy)
+    if (energy) {
+        sc->u_kspace = 0.5 * s.coulomb_k * tot[kPairPart + kVirPart];
         for (int c = 0; c < 6; ++c)
             sc->virial[c] = tot[kPairPart + c] + 0.5 * s.coulomb_k * tot[kPairPart + kVirPart + 1 + c];
+    }
     if (close) close_build(sc, true);
 }
 
@@ -2153,11 +2216,20 @@ __device__ inline void write_sums(const DevSys& s, const double* tot, int energy
 // system's wavefront partials and modes is summed by 256 threads, and its kFin
 // sums go to fin_part[b].  grid = 1: one block per system holds all its slices
 // (at most kFinOne), adds them in order and writes the scalars, with no second
-// pass; else one slice per block.
+// pass; else one slice per block.  Workgroups past n_fin (an evaluation without
+// energies on one stream, which sums no modes) finalize the structure factors
+// instead, one mode per wavefront: one launch fewer.
 __global__ __launch_bounds__(256 * kFinOne) void k_finalize_part(const DevSys* __restrict__ sys,
                                                                  const KDev* __restrict__ kd, int energy, int grid,
-                                                                 int close)
+                                                                 int close, int n_fin,
+                                                                 const int2* __restrict__ mode_map, int n_modes)
 {
+    if ((int)blockIdx.x >= n_fin) {
+        const int mode = ((int)blockIdx.x - n_fin) * ((int)blockDim.x >> 6) +
+                         __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        if (mode < n_modes) finalize_mode(sys, mode_map, kd, 0, mode);
+        return;
+    }
     const int r = blockIdx.x / grid, slice = threadIdx.x >> 8, tid = threadIdx.x & 255;
     const int b = grid == 1 ? slice : (int)blockIdx.x - r * grid;
     const DevSys s = global_view(sys[r]);
@@ -2183,28 +2255,26 @@ __global__ __launch_bounds__(256 * kFinOne) void k_finalize_part(const DevSys* _
     const int nc = energy ? kPairPart + kVirPart : kPairPart;
     double ue = 0.0;
     double wk[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    const int nm = s.n > 0 ? k.n_modes : 0;  // an empty system sums no modes
+    const int nm = energy && s.n > 0 ? k.n_modes : 0;  // an empty system sums no modes
     const int m0 = (int)((long long)nm * bs / nf), m1 = (int)((long long)nm * min(b + 1, nf) / nf);
     for (int p = m0 + tid; p < m1; p += 256) {
         const ModeRec mr = k.modes[p];
         ue += mr.e;
-        if (energy) {
-            // strain derivative of the mode's energy: e (delta_ab - g k_a k_b)
-            const double kx = s.two_pi_L[0] * mr.mx, ky = s.two_pi_L[1] * mr.my, kz = s.two_pi_L[2] * mr.mz;
-            const double eg = mr.e * k.mode_g[p];
-            wk[0] += mr.e - eg * kx * kx;
-            wk[1] += mr.e - eg * ky * ky;
-            wk[2] += mr.e - eg * kz * kz;
-            wk[3] -= eg * kx * ky;
-            wk[4] -= eg * kx * kz;
-            wk[5] -= eg * ky * kz;
-        }
+        // strain derivative of the mode's energy: e (delta_ab - g k_a k_b)
+        const double kx = s.two_pi_L[0] * mr.mx, ky = s.two_pi_L[1] * mr.my, kz = s.two_pi_L[2] * mr.mz;
+        const double eg = mr.e * k.mode_g[p];
+        wk[0] += mr.e - eg * kx * kx;
+        wk[1] += mr.e - eg * ky * ky;
+        wk[2] += mr.e - eg * kz * kz;
+        wk[3] -= eg * kx * ky;
+        wk[4] -= eg * kx * kz;
+        wk[5] -= eg * ky * kz;
     }
     // each quantity over the slice's four wavefronts in order
     double all[kFin];
 #pragma unroll
     for (int c = 0; c < kPairPart + kVirPart; ++c) all[c] = c < nc ? wave_sum(v[c]) : 0.0;
-    all[kPairPart + kVirPart] = wave_sum(ue);
+    all[kPairPart + kVirPart] = energy ? wave_sum(ue) : 0.0;
 #pragma unroll
     for (int c = 0; c < 6; ++c) all[kPairPart + kVirPart + 1 + c] = energy ? wave_sum(wk[c]) : 0.0;
     if ((threadIdx.x & 63) == 0)
@@ -3138,7 +3208,7 @@ void launch_clear_flags(const Plan& P, hipStream_t st) { k_clear_flags<<<1, 64, 
 
 #define RB_MAP(shape) P.sys, P.shape.map
 
-void launch_sort(const Plan& P, bool gate, hipStream_t st)
+void launch_sort(const Plan& P, bool gate, bool sample, hipStream_t st)
 {
     if (P.atoms.blocks <= 0) return;
     const int g = gate ? 1 : 0;
@@ -3146,7 +3216,9 @@ void launch_sort(const Plan& P, bool gate, hipStream_t st)
     const int own_scan = P.max_cells <= kOwnScan ? 1 : 0;
     if (!own_scan) k_scan<<<P.R, 1024, 0, st>>>(P.sys, g);
     k_scatter<<<P.atoms.blocks, kBlock, 0, st>>>(RB_MAP(atoms), g, own_scan);
-    k_cell_sort<<<P.cells.blocks, kBlock, 0, st>>>(RB_MAP(cells), g);
+    const int modes = sample && P.modes64.blocks > 0 ? P.modes1.blocks : 0;
+    k_cell_sort<<<P.cells.blocks + blocks_for(modes, kBlock / 64), kBlock, 0, st>>>(RB_MAP(cells), g, P.cells.blocks,
+                                                                                   P.modes1.map, P.kd, modes);
 }
 
 void launch_lists(const Plan& P, bool gate, hipStream_t st)
@@ -3209,7 +3281,7 @@ void launch_lists(const Plan& P, bool gate, hipStream_t st)
 
 void launch_build(const Plan& P, bool gate, hipStream_t st)
 {
-    launch_sort(P, gate, st);
+    launch_sort(P, gate, false, st);
     launch_lists(P, gate, st);
 }
 
@@ -3219,19 +3291,26 @@ void launch_ksample(const Plan& P, hipStream_t st)
     if (P.modes64.blocks > 0) k_ksample<<<P.modes1.blocks, 64, 0, st>>>(RB_MAP(modes1), P.kd);
 }
 
-template <int KU, int LPA>
-void launch_pair_ku(const Plan& P, bool mixed, bool energy, hipStream_t st)
+// Dynamic LDS of the pair kernel with `lanes` lanes an atom and A atoms per
+// workgroup.
+static size_t pair_lds(const Plan& P, bool mixed, bool energy, int lanes, int A)
 {
-    const int A = LPA == 1 ? P.tune.pair_block : 64;  // atoms per workgroup
     // near-field table, the sums handed over, then the Floyd masks of the
     // per-evaluation batch draw (none for a stored batch) and the drawn ranks
     // (LPA > 1)
     const size_t tab = sizeof(float4) * (mixed ? 1 : 4) * (size_t)P.near.n * (energy ? 2 : 1);
     const int n_sum = energy ? PairSum<true>::N : PairSum<false>::N;
-    const size_t xch = sizeof(double) * (LPA == 1 ? n_sum : 2 * n_sum + 1) * A;
+    const size_t xch = sizeof(double) * (lanes == 1 ? n_sum : 2 * n_sum + 1) * A;
     const size_t masks = P.stored ? 0 : sizeof(uint32_t) * (size_t)((P.cap_cand + 31) / 32) * A;
-    const size_t drawn = (P.stored || LPA == 1) ? 0 : sizeof(uint16_t) * kDrawMax * A;
-    const size_t sm = tab + xch + masks + drawn;
+    const size_t drawn = (P.stored || lanes == 1) ? 0 : sizeof(uint16_t) * kDrawMax * A;
+    return tab + xch + masks + drawn;
+}
+
+template <int KU, int LPA>
+void launch_pair_ku(const Plan& P, bool mixed, bool energy, hipStream_t st)
+{
+    const int A = LPA == 1 ? P.tune.pair_block : 64;  // atoms per workgroup
+    const size_t sm = pair_lds(P, mixed, energy, LPA, A);
     const int nb = P.pair_atoms.blocks;
 #define RB_PAIR(M, E) k_pair<M, E, KU, LPA><<<nb, 2 * LPA * A, sm, st>>>(RB_MAP(pair_atoms), P.near)
     if (mixed) {
@@ -3289,19 +3368,63 @@ void launch_rho(const Plan& P, bool mixed, hipStream_t st)
 #undef RB_RHO
 }
 
+void launch_pair_rho(const Plan& P, bool mixed, bool energy, hipStream_t st)
+{
+    // where the structure factors have the joint kernel's shape (that of a small
+    // system before tuning) and are no more than a few workgroups a CU: they run
+    // at the pair kernel's registers, which leave two wavefronts a SIMD with
+    // energies in FP64 (16384 ions, 801 modes, 832 workgroups: 168 us separate,
+    // 180 joint; 200 modes, 256: 144 both; 4096 ions, 801 modes, 208: 163 / 155)
+    const int most = energy ? kJointRho : 4 * kJointRho;
+    const bool joint = P.pair_lanes > 1 && P.pair_atoms.blocks > 0 && P.rho.blocks > 0 && P.rho.blocks <= most &&
+                       P.tune.rho_mpl == 1 && !(mixed && P.iph) && P.rho_chunk <= kRhoStage;
+    if (!joint) {
+        launch_rho(P, mixed, st);
+        launch_pair(P, mixed, energy, st);
+        return;
+    }
+    const int nb = P.pair_atoms.blocks;
+#define RB_JOINT(M, E, L)                                                                                        \
+    do {                                                                                                         \
+        const size_t a = pair_lds(P, M, E, L, 64), b = sizeof(RhoLds<M, 1, true>);                               \
+        k_pair_rho<M, E, L><<<nb + P.rho.blocks, 128 * L, a > b ? a : b, st>>>(RB_MAP(pair_atoms), P.near,       \
+                                                                              P.rho.map, P.kd, nb);              \
+    } while (0)
+#define RB_JOINT_L(M, E)       \
+    do {                       \
+        if (P.pair_lanes == 4) \
+            RB_JOINT(M, E, 4); \
+        else                   \
+            RB_JOINT(M, E, 2); \
+    } while (0)
+    if (mixed && energy)
+        RB_JOINT_L(true, true);
+    else if (mixed)
+        RB_JOINT_L(true, false);
+    else if (energy)
+        RB_JOINT_L(false, true);
+    else
+        RB_JOINT_L(false, false);
+#undef RB_JOINT_L
+#undef RB_JOINT
+}
+
 void launch_rho_finalize(const Plan& P, bool energy, hipStream_t st)
 {
     if (P.modes1.blocks > 0)
         k_rho_finalize<<<P.modes1.blocks, 64, 0, st>>>(RB_MAP(modes1), P.kd, energy ? 1 : 0);
 }
 
-void launch_finalize(const Plan& P, bool energy, bool close, hipStream_t st)
+void launch_finalize(const Plan& P, bool energy, bool close, bool with_rho, hipStream_t st)
 {
     if (P.R <= 0) return;
     const int e = energy ? 1 : 0, c = close ? 1 : 0;
     const bool one = P.fin_grid <= kFinOne;
-    k_finalize_part<<<one ? P.R : P.R * P.fin_grid, one ? 256 * P.fin_grid : 256, 0, st>>>(P.sys, P.kd, e,
-                                                                                         one ? 1 : P.fin_grid, c);
+    if (with_rho && energy) launch_rho_finalize(P, energy, st);  // its modes' energies are summed here
+    const int modes = with_rho && !energy ? P.modes1.blocks : 0;
+    const int nb = one ? P.R : P.R * P.fin_grid, bs = one ? 256 * P.fin_grid : 256;
+    k_finalize_part<<<nb + blocks_for(modes, bs / 64), bs, 0, st>>>(P.sys, P.kd, e, one ? 1 : P.fin_grid, c, nb,
+                                                                    P.modes1.map, modes);
     if (!one) k_finalize<<<P.R, 64, 0, st>>>(P.sys, P.kd, e, c);
 }
 

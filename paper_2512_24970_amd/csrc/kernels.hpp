@@ -172,13 +172,19 @@ constexpr int fin_blocks(int n, int modes)
 constexpr int kFluxPart = 12;
 
 // Whether a launch (all systems of a batch) runs its k-space chain on the one
-// stream, when its kernels are not replayed from a graph: the four event calls
-// of a fork and join take about 28 us a step.  Measured with two streams and
-// with one, us per step launched kernel by kernel: 512 ions FP64 95 / 81, 32768
-// FP64 102 / 93 and mixed 123 / 106, 131072 FP64 187 / 171 and mixed 169 / 152;
-// from graphs two streams win (131072 mixed 140 / 153), as they do at 10^6.
-constexpr size_t kSingleWaves = 2048;
-inline bool single_stream_for(size_t atom_waves) { return atom_waves <= kSingleWaves; }
+// stream, sharing launches with the pair kernel and the reductions, or forks it
+// to the second.  Launched kernel by kernel the four event calls of a fork and
+// join take about 28 us a step; from a graph they cost about 15.  us per step,
+// two streams / one, 200 modes: 4096 ions FP64 72 / 55, mixed 70 / 53; 32768 FP64
+// 78 / 70, mixed 80 / 74; 131072 FP64 160 / 153, mixed 130 / 134 (51 modes 108 /
+// 106, 801 256 / 255).  From graphs: 4096 FP64 74 / 57, mixed 71 / 55; 32768 80 /
+// 74 and 81 / 77; 131072 FP64 163 / 155, mixed 133 / 136; 60000 mixed, 801
+// modes, 180 / 186, so the mixed form goes to two streams from graphs sooner.
+constexpr size_t kSingleWaves = 2048, kSingleWavesGraph = 640;
+inline bool single_stream_for(size_t atom_waves, bool graph, bool mixed)
+{
+    return atom_waves <= (graph && mixed ? kSingleWavesGraph : kSingleWaves);
+}
 
 // Lanes that share an atom's core list, and its shell batch, in the pair
 // kernel: the more the fewer wavefronts the launch (all systems of a batch) has
@@ -307,6 +313,7 @@ struct Plan {
     Shape rho;      // rho blocks: local block = mode tile * n_chunks + chunk (tiles of 64 rho_mpl modes)
     Shape modes1;   // one block per mode
     bool single = false;  // one stream: the fork and join cost more than the overlap gains (single_stream_for)
+    bool single_graph = false;  // the same where the steps are replayed from graphs
     int list_mode = 0;  // < kListPerAtom: per-cell list kernel staging kListCaps[mode] atoms; else per-atom kernel
     bool stored = false;  // memory form: batch drawn at the build
     bool langevin = false;  // some system runs the Langevin thermostat
@@ -343,17 +350,21 @@ void launch_clear_flags(const Plan& P, hipStream_t st);
 void launch_build(const Plan& P, bool gate, hipStream_t st);
 // the two halves of launch_build: the cell sort (atoms reordered), then the
 // lists (which read the sorted positions and write only list data)
-void launch_sort(const Plan& P, bool gate, hipStream_t st);
+// sample: the step's k-space modes are drawn beside the last pass
+void launch_sort(const Plan& P, bool gate, bool sample, hipStream_t st);
 void launch_lists(const Plan& P, bool gate, hipStream_t st);
 
 // forces
 void launch_ksample(const Plan& P, hipStream_t st);
 void launch_pair(const Plan& P, bool mixed, bool energy, hipStream_t st);
+// launch_rho and launch_pair, in one launch where there is a kernel for both
+void launch_pair_rho(const Plan& P, bool mixed, bool energy, hipStream_t st);
 void launch_rho(const Plan& P, bool mixed, hipStream_t st);
 void launch_rho_finalize(const Plan& P, bool energy, hipStream_t st);
 // momentum correction and energies; with `energy` also the virial; close: end
 // a step's build
-void launch_finalize(const Plan& P, bool energy, bool close, hipStream_t st);
+// with_rho: launch_rho_finalize as well, in the same launch where there are no energies
+void launch_finalize(const Plan& P, bool energy, bool close, bool with_rho, hipStream_t st);
 // k-space force (eq. 29) into the total-force arrays
 void launch_kforce(const Plan& P, bool mixed, hipStream_t st);
 // total force = short range - momentum correction + k-space; with kick the
