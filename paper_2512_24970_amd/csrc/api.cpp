@@ -630,6 +630,12 @@ bool any_thermostat(const rbsog_ctx* c)
     return false;
 }
 
+bool forked(const rbsog_ctx* c) { return !(c->use_graph ? c->plan.single_graph : c->plan.single); }
+
+// On one stream, kernels that neither wait for each other nor fill the chip
+// share a launch (but are timed one by one).
+bool joint_launches(const rbsog_ctx* c) { return !forked(c) && !c->profiling; }
+
 bool any_nose_hoover(const rbsog_ctx* c)
 {
     for (const auto& s : c->hs)
@@ -647,7 +653,7 @@ bool any_nose_hoover(const rbsog_ctx* c)
 // (which reorders the atoms) precedes the fork: the k-space chain needs the
 // sorted positions but not the lists, so it runs beside the list kernels.
 // A small launch (single_stream_for) keeps the chain on the one stream instead:
-// the modes are drawn beside the cell sort, the structure factors summed beside
+// the modes are drawn beside the step's opening kick, the structure factors summed beside
 // the pair kernel and finalized beside the force sums, each pair in one launch.
 void enqueue_forces(rbsog_ctx* c, bool energy, bool kick, bool build = false)
 {
@@ -655,17 +661,14 @@ void enqueue_forces(rbsog_ctx* c, bool energy, bool kick, bool build = false)
     const Plan& P = c->plan;
     // an evaluation with energies takes the fused k-space pass, which forms
     // the per-atom k-space shares of the stress and heat flux
-    const bool fork = !(c->use_graph ? P.single_graph : P.single);
+    const bool fork = forked(c), joint = joint_launches(c);
     const bool aux_kf = P.tune.kf_aux && !energy && fork;
-    // on one stream, kernels that neither wait for each other nor fill the
-    // chip share a launch (but are timed one by one)
-    const bool joint = !fork && !c->profiling;
     hipStream_t st = c->stream;
     hipStream_t ax = fork ? c->aux : st;
     if (P.atoms.blocks <= 0) return;
     if (build) {
         c->begin(RBSOG_PHASE_BUILD);
-        launch_sort(P, true, joint, st);
+        launch_sort(P, true, st);
         c->end();
     }
     if (fork) {
@@ -770,7 +773,7 @@ void check_flags(rbsog_ctx* c, const std::vector<DeviceScalars>& h)
 void enqueue_step(rbsog_ctx* c, bool scheduled, bool energy)
 {
     c->begin(RBSOG_PHASE_INTEGRATE);
-    launch_kick_drift(c->plan, scheduled, c->stream);
+    launch_kick_drift(c->plan, scheduled, joint_launches(c), c->stream);
     c->end();
     enqueue_forces(c, energy, true, true);
 }

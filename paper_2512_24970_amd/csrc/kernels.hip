@@ -477,20 +477,8 @@ __device__ inline void gather_atom(const DevSys& s, int t, int o)
 // lanes; a larger one (a small box is one cell) by the whole block over LDS.
 // The sorted atoms go straight to their places (a pass of its own over the
 // permutation read and wrote it once more, and was one more launch).
-// Workgroups past n_cells (launches on one stream) draw the step's n_modes
-// k-space modes instead, one per wavefront, whether or not there is a build:
-// with the structure factors finalized beside the force sums, two launches fewer
-// (a step of 32768 ions FP64 84 -> 78 us, of 512 71 -> 67).
-__device__ inline void sample_mode(RB_ARGS, const KDev* __restrict__ kd, int mode);
-__global__ __launch_bounds__(kBlock) void k_cell_sort(RB_ARGS, int gate, int n_cells,
-                                                      const int2* __restrict__ mode_map,
-                                                      const KDev* __restrict__ kd, int n_modes)
+__global__ __launch_bounds__(kBlock) void k_cell_sort(RB_ARGS, int gate)
 {
-    if ((int)blockIdx.x >= n_cells) {
-        const int mode = ((int)blockIdx.x - n_cells) * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        if (mode < n_modes) sample_mode(sys, mode_map, kd, mode);
-        return;
-    }
     RB_SYS(blockIdx.x)
     RB_GATE
     __shared__ int32_t key[kCellCap];
@@ -1801,61 +1789,71 @@ __device__ inline int first_above(const double* cdf, int len, double u)
     return lo < len ? lo : len - 1;
 }
 
-// The same index by one wavefront: each round the lanes probe the ends of 64
-// equal slices of [lo, hi) and keep the first slice that reaches above u,
-// so a table of L entries takes about log64(L) dependent loads instead of
-// log2(L).  Every lane returns the index.
-__device__ inline int first_above_wave(const double* cdf, int len, double u)
+// The same index in N tables at once by one wavefront: each round the lanes
+// probe the ends of 64 equal slices of [lo, hi) and keep the first slice that
+// reaches above u, so a table of L entries takes about log64(L) dependent loads
+// instead of log2(L), and the tables' loads are in flight together.  Every lane
+// returns the indices.
+template <int N>
+__device__ inline void first_above_wave(const double* const (&cdf)[N], const int (&len)[N], const double (&u)[N],
+                                        int (&out)[N])
 {
     const int lane = threadIdx.x & 63;
-    int lo = 0, hi = len;  // the first index above u (len: none) lies in [lo, hi]
-    while (hi - lo > 64) {
-        const int step = (hi - lo + 63) >> 6;
-        const int probe = lo + (lane + 1) * step - 1;
-        const bool above = probe >= hi || u < cdf[probe];
-        const uint64_t m = __builtin_amdgcn_ballot_w64(above);
-        if (m == 0) {
-            lo = hi;
-            break;
+    int lo[N], hi[N];  // the first index above u (len: none) lies in [lo, hi]
+    for (int a = 0; a < N; ++a) lo[a] = 0, hi[a] = len[a];
+    for (bool more = true; more;) {
+        int step[N];
+        double x[N];
+#pragma unroll
+        for (int a = 0; a < N; ++a) {
+            step[a] = (hi[a] - lo[a] + 63) >> 6;
+            x[a] = lo[a] < hi[a] ? cdf[a][min(lo[a] + (lane + 1) * step[a], hi[a]) - 1] : 0.0;
         }
-        const int f = __builtin_ctzll(m);
-        const int nlo = f == 0 ? lo : lo + f * step;
-        hi = min(lo + (f + 1) * step - 1, hi);
-        lo = nlo;
+        more = false;
+#pragma unroll
+        for (int a = 0; a < N; ++a) {
+            if (lo[a] >= hi[a]) continue;
+            const bool above = lo[a] + (lane + 1) * step[a] > hi[a] || u[a] < x[a];
+            const uint64_t m = __builtin_amdgcn_ballot_w64(above);
+            const int f = m == 0 ? 64 : __builtin_ctzll(m);
+            const int end = m == 0 ? hi[a] : min(lo[a] + (f + 1) * step[a] - 1, hi[a]);
+            lo[a] = m == 0 ? hi[a] : lo[a] + f * step[a];
+            hi[a] = end;
+            more = more || lo[a] < hi[a];
+        }
     }
-    if (hi - lo > 0) {
-        const int idx = lo + lane;
-        const bool above = idx >= hi || u < cdf[idx];
-        const uint64_t m = __builtin_amdgcn_ballot_w64(above);
-        lo = m == 0 ? hi : lo + __builtin_ctzll(m);
-    }
-    return lo < len ? lo : len - 1;
+    for (int a = 0; a < N; ++a) out[a] = lo[a] < len[a] ? lo[a] : len[a] - 1;
 }
 
 // Draw the P_F modes of eq. (28): component (m, d) by its mass, then the
 // three axis indices from their 1D lattice distributions, then signs.  One
-// wavefront per mode (the searches are wave-cooperative).
-__device__ inline void sample_mode(RB_ARGS, const KDev* __restrict__ kd, int mode)
+// wavefront per mode (the searches are wave-cooperative).  ahead: evaluations
+// past the current one (a step's opening kick draws the modes of its forces).
+__device__ inline void sample_mode(RB_ARGS, const KDev* __restrict__ kd, int mode, int ahead)
 {
     RB_SYS(mode)
     const KDev k = global_view(kd[rb_m.x]);
     const int p = lb;
     if (!k.sampled || p >= k.n_modes) return;
-    PhiloxStream st(s.seed, (uint32_t)p, (uint32_t)s.sc->eval, kTagKmode, s.replica);
-    const double uc = st.uniform();
+    PhiloxStream st(s.seed, (uint32_t)p, (uint32_t)(s.sc->eval + ahead), kTagKmode, s.replica);
+    const double uc[1] = {st.uniform()};
     double ua[3];
     for (int a = 0; a < 3; ++a) ua[a] = st.uniform();
     const uint32_t signs = st.next();
-    const int c = first_above_wave(k.comp_cdf, k.nm * 3, uc);
-    const int m = c / 3, d = c % 3;
-    int mi[3];
+    const double* const comp[1] = {k.comp_cdf};
+    const int n_comp[1] = {k.nm * 3};
+    int c[1];
+    first_above_wave<1>(comp, n_comp, uc, c);
+    const int m = c[0] / 3, d = c[0] % 3;
+    const double* cdf[3];
+    int len[3], mi[3];
     for (int a = 0; a < 3; ++a) {
-        const int o = k.off[m * 3 + a], L = k.len[m * 3 + a];
-        const double* cdf = (a == d) ? k.g2cdf + o : k.g0cdf + o;
-        int nn = first_above_wave(cdf, L, ua[a]);
-        if (nn > 0 && ((signs >> a) & 1u)) nn = -nn;
-        mi[a] = nn;
+        cdf[a] = (a == d ? k.g2cdf : k.g0cdf) + k.off[m * 3 + a];
+        len[a] = k.len[m * 3 + a];
     }
+    first_above_wave<3>(cdf, len, ua, mi);
+    for (int a = 0; a < 3; ++a)
+        if (mi[a] > 0 && ((signs >> a) & 1u)) mi[a] = -mi[a];
     if ((threadIdx.x & 63) != 0) return;
     k.m[3 * p] = mi[0];
     k.m[3 * p + 1] = mi[1];
@@ -1880,7 +1878,7 @@ __device__ inline void sample_mode(RB_ARGS, const KDev* __restrict__ kd, int mod
 
 __global__ __launch_bounds__(64) void k_ksample(RB_ARGS, const KDev* __restrict__ kd)
 {
-    sample_mode(sys, bmap, kd, blockIdx.x);
+    sample_mode(sys, bmap, kd, blockIdx.x, 0);
 }
 
 // e^{2 pi i t / 1024} for a phase t in units of 2 pi / 1024: table entry
@@ -2807,9 +2805,20 @@ __global__ __launch_bounds__(kBlock) void k_kinetic(RB_ARGS)
 // scheduled for this step.
 // LANGEVIN: the variant launched when some system of the batch runs the
 // Langevin thermostat (its noise path needs many more registers).
-template <bool LANGEVIN>
-__global__ __launch_bounds__(kBlock) void k_kick_drift(RB_ARGS, int scheduled)
+// SAMPLE (launches on one stream): workgroups past n_blocks draw the step's
+// n_modes k-space modes instead, one per wavefront: with the structure factors
+// finalized beside the force sums, two launches fewer.
+template <bool LANGEVIN, bool SAMPLE>
+__global__ __launch_bounds__(kBlock) void k_kick_drift(RB_ARGS, int scheduled, int n_blocks,
+                                                       const int2* __restrict__ mode_map,
+                                                       const KDev* __restrict__ kd, int n_modes)
 {
+    if (SAMPLE && (int)blockIdx.x >= n_blocks) {
+        const int mode =
+            ((int)blockIdx.x - n_blocks) * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        if (mode < n_modes) sample_mode(sys, mode_map, kd, mode, 1);
+        return;
+    }
     RB_SYS(blockIdx.x)
     __shared__ double red[4];
     const int i = lb * blockDim.x + threadIdx.x;
@@ -3208,7 +3217,7 @@ void launch_clear_flags(const Plan& P, hipStream_t st) { k_clear_flags<<<1, 64, 
 
 #define RB_MAP(shape) P.sys, P.shape.map
 
-void launch_sort(const Plan& P, bool gate, bool sample, hipStream_t st)
+void launch_sort(const Plan& P, bool gate, hipStream_t st)
 {
     if (P.atoms.blocks <= 0) return;
     const int g = gate ? 1 : 0;
@@ -3216,9 +3225,7 @@ void launch_sort(const Plan& P, bool gate, bool sample, hipStream_t st)
     const int own_scan = P.max_cells <= kOwnScan ? 1 : 0;
     if (!own_scan) k_scan<<<P.R, 1024, 0, st>>>(P.sys, g);
     k_scatter<<<P.atoms.blocks, kBlock, 0, st>>>(RB_MAP(atoms), g, own_scan);
-    const int modes = sample && P.modes64.blocks > 0 ? P.modes1.blocks : 0;
-    k_cell_sort<<<P.cells.blocks + blocks_for(modes, kBlock / 64), kBlock, 0, st>>>(RB_MAP(cells), g, P.cells.blocks,
-                                                                                   P.modes1.map, P.kd, modes);
+    k_cell_sort<<<P.cells.blocks, kBlock, 0, st>>>(RB_MAP(cells), g);
 }
 
 void launch_lists(const Plan& P, bool gate, hipStream_t st)
@@ -3281,7 +3288,7 @@ void launch_lists(const Plan& P, bool gate, hipStream_t st)
 
 void launch_build(const Plan& P, bool gate, hipStream_t st)
 {
-    launch_sort(P, gate, false, st);
+    launch_sort(P, gate, st);
     launch_lists(P, gate, st);
 }
 
@@ -3531,13 +3538,23 @@ void launch_kinetic(const Plan& P, hipStream_t st)
     if (P.atoms.blocks > 0) k_kinetic<<<P.atoms.blocks, kBlock, 0, st>>>(RB_MAP(atoms));
 }
 
-void launch_kick_drift(const Plan& P, bool scheduled, hipStream_t st)
+void launch_kick_drift(const Plan& P, bool scheduled, bool sample, hipStream_t st)
 {
-    if (P.atoms.blocks <= 0) return;
-    if (P.langevin)
-        k_kick_drift<true><<<P.atoms.blocks, kBlock, 0, st>>>(RB_MAP(atoms), scheduled ? 1 : 0);
+    const int nb = P.atoms.blocks;
+    if (nb <= 0) return;
+    const int modes = sample && P.modes64.blocks > 0 ? P.modes1.blocks : 0;
+    const int all = nb + blocks_for(modes, kBlock / 64);
+#define RB_KD(L, S) \
+    k_kick_drift<L, S><<<all, kBlock, 0, st>>>(RB_MAP(atoms), scheduled ? 1 : 0, nb, P.modes1.map, P.kd, modes)
+    if (P.langevin && modes > 0)
+        RB_KD(true, true);
+    else if (P.langevin)
+        RB_KD(true, false);
+    else if (modes > 0)
+        RB_KD(false, true);
     else
-        k_kick_drift<false><<<P.atoms.blocks, kBlock, 0, st>>>(RB_MAP(atoms), scheduled ? 1 : 0);
+        RB_KD(false, false);
+#undef RB_KD
 }
 
 // Per-device address of `scratch`, looked up once per device at context

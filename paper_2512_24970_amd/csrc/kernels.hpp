@@ -350,8 +350,7 @@ void launch_clear_flags(const Plan& P, hipStream_t st);
 void launch_build(const Plan& P, bool gate, hipStream_t st);
 // the two halves of launch_build: the cell sort (atoms reordered), then the
 // lists (which read the sorted positions and write only list data)
-// sample: the step's k-space modes are drawn beside the last pass
-void launch_sort(const Plan& P, bool gate, bool sample, hipStream_t st);
+void launch_sort(const Plan& P, bool gate, hipStream_t st);
 void launch_lists(const Plan& P, bool gate, hipStream_t st);
 
 // forces
@@ -386,7 +385,8 @@ void launch_kinetic(const Plan& P, hipStream_t st);
 // integrator: opening half kick and drift; raises the rebuild flag of a
 // system when one of its atoms moved more than skin/2 since its build, or
 // when `scheduled`
-void launch_kick_drift(const Plan& P, bool scheduled, hipStream_t st);
+// sample: the k-space modes of the step's forces are drawn in the same launch
+void launch_kick_drift(const Plan& P, bool scheduled, bool sample, hipStream_t st);
 
 // exports into the caller's [N][3] arrays (row user_off + id)
 enum class Field { force = 0, short_force = 1, velocity = 2 };
