@@ -66,9 +66,9 @@ TRANS_SLOTS = 2
 # the wavefronts that touch the box edge (a quarter at the 10^6-ion size), so
 # 10.25 FP64; mixed form the three scaled differences of 32-bit fixed-point
 # records (integer subtractions, then 3 FP64 products) and r^2, 8 FP64;
-# per evaluated pair: FP64 form 181 for the pair function (two
-# software exponentials, the squaring chain of the narrow Gaussians, the
-# 13-term polynomial of the wide ones, BMH terms) plus 6 to accumulate F;
+# per evaluated pair: FP64 form 104 for the pair function (square root, the
+# degree-7 near-field polynomial, one software exponential, BMH terms; counted)
+# plus 6 to accumulate F;
 # mixed form 40 FP32 for the table-driven pair function as compiled (rsqrt
 # and two exponentials among them: 3 transcendentals) plus 6 FP64 to
 # accumulate.  These per-pair constants were checked against the counted
@@ -78,7 +78,7 @@ KSPACE_MODEL = {
     ("mixed", "rho"): (5.5, 6.0, 2.0), ("mixed", "kforce"): (11.0, 5.0, 2.0),
 }  # (FP64 flops, FP32 flops, FP32 transcendentals) per (atom, mode)
 PAIR_MODEL = {
-    "fp64": {"fp64_test": 10.25, "fp64_pair": 187.0, "fp32_pair": 0.0, "trans_pair": 0.0},
+    "fp64": {"fp64_test": 10.25, "fp64_pair": 110.0, "fp32_pair": 0.0, "trans_pair": 0.0},
     "mixed": {"fp64_test": 8.0, "fp64_pair": 6.0, "fp32_pair": 40.0, "trans_pair": 3.0},
 }
 

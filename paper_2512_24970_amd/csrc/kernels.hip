@@ -105,21 +105,6 @@ __device__ inline void wave_partial(double v, int i, int n, double* part, int st
     if ((threadIdx.x & 63) == 0 && (i & ~63) < n) part[(size_t)(i >> 6) * stride + c] = v;
 }
 
-// Sum of v over a block of up to 1024 threads in a fixed order; valid in
-// thread 0.
-__device__ inline double block_sum(double v, double* red /*[blockDim.x / 64]*/)
-{
-    v = wave_sum(v);
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) red[w] = v;
-    __syncthreads();
-    double t = 0.0;
-    if (threadIdx.x == 0)
-        for (int q = 0; q < (int)(blockDim.x >> 6); ++q) t += red[q];
-    __syncthreads();
-    return t;
-}
-
 // Minimum image with the operations in a fixed order (no contraction):
 // d -= L * rint(d / L), d / L evaluated as d * (1/L).
 __device__ inline double min_image(double d, double L, double invL)
@@ -1776,20 +1761,8 @@ __global__ __launch_bounds__(kBlock) void k_batch_ids(RB_ARGS, int32_t* out, int
 }
 
 // ---------------------------------------------------------------- k-space
-__device__ inline int first_above(const double* cdf, int len, double u)
-{
-    int lo = 0, hi = len;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (u < cdf[mid])
-            hi = mid;
-        else
-            lo = mid + 1;
-    }
-    return lo < len ? lo : len - 1;
-}
-
-// The same index in N tables at once by one wavefront: each round the lanes
+// The first index above u in each of N cumulative tables (the last one if there
+// is none) by one wavefront: each round the lanes
 // probe the ends of 64 equal slices of [lo, hi) and keep the first slice that
 // reaches above u, so a table of L entries takes about log64(L) dependent loads
 // instead of log2(L), and the tables' loads are in flight together.  Every lane
@@ -2550,7 +2523,8 @@ __global__ __launch_bounds__(kKfThreads) void k_kforce_part(RB_ARGS, const KDev*
 // The loop over modes is bound by FP64 issue (phases, accumulation), and a
 // small system has too few atoms to fill the SIMDs with one atom per lane:
 // its modes are cut into kf_slices contiguous slices whose sums are added in
-// order, one wavefront each where the launch has too few (kf_waves).
+// order, one wavefront each where the launch has too few (kf_waves): 512 ions,
+// 100 modes FP64 16 -> 10 us, 32768 ions, 200 modes 37 -> 12.
 // FUSED = false: written into the total-force arrays, which hold it until
 // k_combine adds the short-range part (it needs only the positions and rho,
 // so it can run on the second stream beside the pair kernel).  FUSED: the
@@ -2912,7 +2886,8 @@ __global__ __launch_bounds__(kBlock) void k_kick_drift(RB_ARGS, int scheduled, i
 // Bound by the gathers (about 225 records per atom).  A candidate
 // row belongs to 16 lanes, four rows to a wavefront, and a core tile to 4 lanes
 // of 16 neighbouring atoms, so list reads coalesce, where one lane per atom
-// read 64 rows at a time (262144 ions: 1087 us).
+// read 64 rows at a time (262144 ions: 1087 us, now 128; 260 from the FP64
+// positions).
 constexpr int kRdfThreads = 1024;
 __global__ __launch_bounds__(kRdfThreads) void k_rdf(RB_ARGS, double D, int n_bins, unsigned long long* counts)
 {
@@ -3125,8 +3100,8 @@ __global__ void k_from_user(RB_ARGS, const int32_t* type, const double* pos, con
 
 // Raise the device maximum of squared displacements (d2 >= 0, compared by bit
 // pattern) and a flag from a whole block.  Same-address atomics serialise: one
-// per block, and only where it would change the value (one per wavefront took
-// 366 us of a 10^6-ion call).
+// per block, and only where it would change the value (k_set_pos at 10^6 ions
+// 67 us, with one per wavefront 366).
 __device__ inline void block_raise(double d2, bool flagged, unsigned long long* slot, int32_t* flag)
 {
     __shared__ double red[kBlock / 64];
