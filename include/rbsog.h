@@ -330,9 +330,10 @@ typedef struct {
  * (both streams, graphs if enabled), max(reps, 3) steps per candidate from
  * one saved device state, best of three alternating rounds; the chosen
  * shapes are returned in `chosen` (may be NULL).  Restores the saved state
- * (positions, velocities, forces, lists, counters), so the trajectory that
+ * (positions, velocities, forces, lists, counters, modes and structure
+ * factors), so the trajectory that
  * follows is bit for bit the one without tuning; holds a second copy of the
- * atom and list arrays while it runs.  Synchronises. */
+ * atom, list and mode arrays while it runs.  Synchronises. */
 rbsog_status rbsog_autotune(rbsog_ctx* ctx, int32_t reps, rbsog_tuning* chosen);
 /* Set or read the shapes directly (values outside the lists: RBSOG_E_ARG). */
 rbsog_status rbsog_set_tuning(rbsog_ctx* ctx, const rbsog_tuning* t);

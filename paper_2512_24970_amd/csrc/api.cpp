@@ -822,8 +822,10 @@ double time_ms(rbsog_ctx* c, int reps, const std::function<void()>& f)
 }
 
 // Time each kernel under its candidate launch shapes at the current positions
-// and keep the fastest.  Every candidate computes the same bits, so the
-// evaluations it repeats leave the state as it was.
+// and keep the fastest.  What is timed overwrites the forces (the k-space force
+// alone is written where the total is kept) and moves the atoms, so the state
+// and the exported k-space data are saved first and put back: tuning leaves the
+// trajectory bit for bit as it was.
 void autotune(rbsog_ctx* c, int reps)
 {
     const bool was_profiling = c->profiling;
@@ -831,40 +833,11 @@ void autotune(rbsog_ctx* c, int reps)
     c->kinetic_fresh = false;
     hipStream_t st = c->stream;
     launch_set_eval(c->plan, c->eval, st);
-    enqueue_forces(c, false, false);
-    Tuning best = c->plan.tune;
-    auto try_shape = [&](Tuning t) {
-        c->plan.tune = t;
-        plan_launches(c);
-    };
-    try_shape(best);
-    launch_rho(c->plan, c->mixed, st);
-    launch_rho_finalize(c->plan, false, st);
-    launch_pair(c->plan, c->mixed, false, st);
-    launch_finalize(c->plan, false, false, false, st);
-    // a first pick of the k-space force workgroup size, the kernel alone
-    // (refined on whole steps below)
-    double tb = 1e300;
-    for (int bs : {64, 128, 256}) {
-        Tuning t = best;
-        t.kf_block = bs;
-        try_shape(t);
-        const double ms = time_ms(c, reps, [&] { launch_kforce(c->plan, c->mixed, st); });
-        if (ms < tb) {
-            tb = ms;
-            best.kf_block = bs;
-        }
-    }
-    // The pair kernel shares the device with the k-space chain on the second
-    // stream, and the passes around it in a step (drift, gated build) change
-    // what the caches hold when it starts: its shape, the rho modes per lane
-    // and where the k-space force runs are chosen together on whole steps
-    // (timed on back-to-back force evaluations, larger pair workgroups look
-    // faster and still lengthen the step).  Every candidate runs the same
-    // steps from one saved device state (atoms, list counts, lists and
-    // scalars), which is put back afterwards: tuning leaves the trajectory
-    // bit for bit as it was.  Alternating rounds, best of three.
-    DBuf* state[] = {&c->atoms, &c->ufix, &c->counts, &c->lists_core, &c->lists_cand, &c->lists_bat, &c->scalars};
+    // forces that are there stay: an evaluation with energies sums the k-space
+    // part in another order than this one
+    if (!c->forces_valid) enqueue_forces(c, false, false);
+    DBuf* state[] = {&c->atoms, &c->ufix, &c->counts, &c->lists_core, &c->lists_cand, &c->lists_bat, &c->scalars,
+                     &c->kmodes, &c->krho};
     constexpr int kState = sizeof(state) / sizeof(state[0]);
     std::unique_ptr<DBuf[]> saved(new DBuf[kState]);
     auto copy_state = [&](bool save) {
@@ -877,23 +850,23 @@ void autotune(rbsog_ctx* c, int reps)
         }
     };
     copy_state(true);
+    Tuning best = c->plan.tune;
+    auto try_shape = [&](Tuning t) {
+        c->plan.tune = t;
+        plan_launches(c);
+    };
+    // The pair kernel shares the device with the k-space chain on the second
+    // stream, and the passes around it in a step (drift, gated build) change
+    // what the caches hold when it starts: its shape, the rho modes per lane
+    // and where the k-space force runs are chosen together on whole steps
+    // (timed on back-to-back force evaluations, larger pair workgroups look
+    // faster and still lengthen the step).  Every candidate runs the same
+    // steps from the saved state.  Alternating rounds, best of three.
     const int n_steps = std::max(reps, 3);
     struct Cand {
         Tuning t;
         double ms;
     };
-    std::vector<Cand> cands;
-    for (int bs : {64, 128, 256})
-        for (int ku : {4, 8})
-            for (int mpl : {1, 2})
-                for (int aux : {1, 0}) {
-                    Tuning t = best;
-                    t.pair_block = bs;
-                    t.pair_ku = ku;
-                    t.rho_mpl = mpl;
-                    t.kf_aux = aux;
-                    cands.push_back(Cand{t, 1e300});
-                }
     auto search = [&](std::vector<Cand>& cs) {
         for (int round = 0; round < 3; ++round)
             for (Cand& cd : cs) {
@@ -912,7 +885,43 @@ void autotune(rbsog_ctx* c, int reps)
                 best = cd.t;
             }
     };
+    auto restore = [&] {
+        try_shape(best);
+        copy_state(false);
+        HIP_OK(hipStreamSynchronize(st));
+        c->forces_valid = true;
+    };
     try {
+        try_shape(best);
+        launch_rho(c->plan, c->mixed, st);
+        launch_rho_finalize(c->plan, false, st);
+        launch_pair(c->plan, c->mixed, false, st);
+        launch_finalize(c->plan, false, false, false, st);
+        // a first pick of the k-space force workgroup size, the kernel alone
+        // (refined on whole steps below)
+        double tb = 1e300;
+        for (int bs : {64, 128, 256}) {
+            Tuning t = best;
+            t.kf_block = bs;
+            try_shape(t);
+            const double ms = time_ms(c, reps, [&] { launch_kforce(c->plan, c->mixed, st); });
+            if (ms < tb) {
+                tb = ms;
+                best.kf_block = bs;
+            }
+        }
+        std::vector<Cand> cands;
+        for (int bs : {64, 128, 256})
+            for (int ku : {4, 8})
+                for (int mpl : {1, 2})
+                    for (int aux : {1, 0}) {
+                        Tuning t = best;
+                        t.pair_block = bs;
+                        t.pair_ku = ku;
+                        t.rho_mpl = mpl;
+                        t.kf_aux = aux;
+                        cands.push_back(Cand{t, 1e300});
+                    }
         search(cands);
         // then the k-space force workgroup again, on whole steps with the
         // shapes just chosen (alone it ranks sizes that run beside the pair
@@ -927,18 +936,13 @@ void autotune(rbsog_ctx* c, int reps)
     } catch (...) {
         // put the saved state back before reporting the failure
         try {
-            try_shape(best);
-            copy_state(false);
-            (void)hipStreamSynchronize(st);
+            restore();
         } catch (...) {
         }
         c->profiling = was_profiling;
         throw;
     }
-    try_shape(best);
-    copy_state(false);
-    HIP_OK(hipStreamSynchronize(st));
-    c->forces_valid = true;
+    restore();
     c->profiling = was_profiling;
 }
 
