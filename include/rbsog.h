@@ -313,9 +313,11 @@ rbsog_status rbsog_set_list_chunks(rbsog_ctx* ctx, int32_t chunks);
  * and every structure factor is summed over the atoms in the same order
  * whatever the shape. */
 typedef struct {
-    int32_t pair_block; /* atoms per workgroup of the pair kernel: 64, 128, 256 (small systems:
-                           64, several lanes an atom) */
-    int32_t pair_ku;    /* neighbour positions fetched ahead per lane (shell-batch tile): 4, 8 */
+    int32_t pair_block; /* atoms per workgroup of the pair kernel: 64, 128, 256 (fewer where its
+                           tables and draw masks do not fit in 160 KB of LDS; small systems: 64,
+                           several lanes an atom) */
+    int32_t pair_ku;    /* neighbour positions fetched ahead per lane (shell-batch tile): 4, 8 (with
+                           energies and in small systems always 4) */
     int32_t rho_mpl;    /* k-modes per lane of the rho kernel (64 rho_mpl per workgroup): 1, 2 */
     int32_t kf_block;   /* threads per workgroup of the k-space force kernel: 64, 128, 256 (256); a
                            small system takes more (its modes are split over wavefronts) */

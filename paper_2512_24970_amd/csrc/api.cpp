@@ -350,7 +350,8 @@ Plan one(const rbsog_ctx* c, int r)
     P.tune = c->plan.tune;
     P.atoms.blocks = blocks_for(s.n, kBlock);
     P.pair_lanes = c->plan.pair_lanes;
-    P.pair_atoms.blocks = blocks_for(s.n, P.pair_lanes > 1 ? 64 : P.tune.pair_block);
+    P.pair_block = c->plan.pair_block;
+    P.pair_atoms.blocks = blocks_for(s.n, P.pair_block);
     P.kf_threads = c->plan.kf_threads;
     P.kf_split = c->plan.kf_split;
     P.kf_sliced = c->plan.kf_sliced;
@@ -399,6 +400,7 @@ void plan_launches(rbsog_ctx* c)
     size_t waves = 0;
     for (const auto& s : c->hs) waves += blocks_for(s.n, 64);
     P.pair_lanes = pair_lanes_for(waves, c->mixed);
+    P.pair_block = P.pair_lanes > 1 ? 64 : fit_pair_block(P, c->mixed, P.tune.pair_block);
     P.single = single_stream_for(waves, false, c->mixed);
     P.single_graph = single_stream_for(waves, true, c->mixed);
     P.max_cells = P.rho_chunk = 0;

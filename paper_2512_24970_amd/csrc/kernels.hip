@@ -1350,7 +1350,7 @@ __device__ inline void pair_block(RB_ARGS, const NearTab& nt, float4* dyn_sm, in
     }
     // pair coefficients: FP64 for the FP64 form; the mixed form keeps FP32
     // copies and only the FP64 core radii (the core/shell test stays FP64)
-    __shared__ PairCoef pc[MIXED ? 1 : kMaxSpecies * kMaxSpecies];
+    __shared__ PairCoef pc[MIXED ? 1 : kMaxSpecies * kMaxSpecies];  // kPairStatic counts these
     __shared__ PairCoefF pcf[MIXED ? kMaxSpecies * kMaxSpecies : 1];
     __shared__ double rc2s[kMaxSpecies * kMaxSpecies];
     const int S = s.n_species;
@@ -3288,10 +3288,25 @@ static size_t pair_lds(const Plan& P, bool mixed, bool energy, int lanes, int A)
     return tab + xch + masks + drawn;
 }
 
+// The draw masks grow with the candidate capacity (32 KB per 64 atoms at 4096)
+// and the table with r_shell (28 KB with energies in FP64 at 8 to 11.3 A), so
+// the workgroup that was asked for may not fit.  No shape changes a bit.  Sized
+// for energies, that a shape chosen without them takes them too.
+int fit_pair_block(const Plan& P, bool mixed, int want)
+{
+    constexpr size_t kLds = 160 * 1024;  // of a CU, and of a workgroup
+    constexpr size_t kPairs = kMaxSpecies * kMaxSpecies;
+    constexpr size_t kPairStatic[2] = {kPairs * (sizeof(PairCoef) + sizeof(double)) + sizeof(PairCoefF),
+                                       kPairs * (sizeof(PairCoefF) + sizeof(double)) + sizeof(PairCoef)};
+    int A = want;
+    while (A > 64 && pair_lds(P, mixed, true, 1, A) + kPairStatic[mixed ? 1 : 0] + 64 > kLds) A /= 2;
+    return A;
+}
+
 template <int KU, int LPA>
 void launch_pair_ku(const Plan& P, bool mixed, bool energy, hipStream_t st)
 {
-    const int A = LPA == 1 ? P.tune.pair_block : 64;  // atoms per workgroup
+    const int A = P.pair_block;  // atoms per workgroup
     const size_t sm = pair_lds(P, mixed, energy, LPA, A);
     const int nb = P.pair_atoms.blocks;
 #define RB_PAIR(M, E) k_pair<M, E, KU, LPA><<<nb, 2 * LPA * A, sm, st>>>(RB_MAP(pair_atoms), P.near)

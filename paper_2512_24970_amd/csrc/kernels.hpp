@@ -292,8 +292,10 @@ struct Plan {
     DeviceScalars* sc = nullptr;  // device array [R] (sys[r].sc == sc + r)
     int R = 0;
     Shape atoms;    // 256-atom blocks of every system
-    Shape pair_atoms;  // tune.pair_block-atom blocks, 64-atom ones with pair_lanes > 1 (pair kernel)
+    Shape pair_atoms;  // pair_block-atom blocks (pair kernel)
     int pair_lanes = 1;  // lanes that share an atom's lists in the pair kernel (pair_lanes_for)
+    int pair_block = 64; // atoms per pair workgroup: 64 with several lanes, else tune.pair_block or
+                         // what of it fits in LDS (fit_pair_block)
     Shape kf_atoms;    // kf_threads-thread blocks (k-space force kernel)
     Shape kf_part;     // the mode groups of the systems that have several (local block = group * blocks + block)
     int kf_threads = 256;   // tune.kf_block, or more where a system's slices need it
@@ -356,6 +358,9 @@ void launch_lists(const Plan& P, bool gate, hipStream_t st);
 // forces
 void launch_ksample(const Plan& P, hipStream_t st);
 void launch_pair(const Plan& P, bool mixed, bool energy, hipStream_t st);
+// the most of 256, 128 and 64 atoms per workgroup, up to `want`, whose LDS (one
+// lane an atom, an evaluation with energies) a workgroup can have; 64 if none
+int fit_pair_block(const Plan& P, bool mixed, int want);
 // launch_rho and launch_pair, in one launch where there is a kernel for both
 void launch_pair_rho(const Plan& P, bool mixed, bool energy, hipStream_t st);
 void launch_rho(const Plan& P, bool mixed, hipStream_t st);

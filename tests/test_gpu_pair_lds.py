@@ -49,18 +49,17 @@ def test_largest_capacity_with_every_workgroup(n, precision):
     np.testing.assert_array_equal(_forces(ctx)[0], ref[0])
 
 
-def test_capacity_beyond_the_shared_lanes():
-    """A cutoff of 47 A: about 8300 candidates an atom and a table of twelve
-    binades, which leave no room for several lanes an atom."""
+def test_default_shape_at_a_long_cutoff():
+    """A cutoff of 47 A: about 5100 candidates an atom (room for 7700, masks of
+    60 KB per 64 atoms) and a table of twelve binades, with the shapes a set
+    chooses."""
     print("case: r_shell 47", flush=True)
-    cfg = W.config("nacl_512", n=15900, box=96.2)
-    over = dict(r_shell=47.0, skin=1.0, p_r=20, p_f=20)
-    ctx = _system(cfg, R.FP64, **{k: v for k, v in over.items() if k != "p_f"})
-    ctx.rbsog_set_tuning(pair_block=64)
-    f, g, e = _forces(ctx)
-    osys = O.System(dict(cfg["sys"], **over), cfg["types"], cfg["pos"], cfg["vel"])
-    fo, eo = osys.forces(3)
-    check_forces(f, fo, 1e-11, "force")
-    check_forces(g, fo, 1e-11, "force without energies")
-    for key in ("u_core", "u_shell"):
-        assert abs(e[key] - eo[key]) <= 1e-10 * abs(eo[key])
+    cfg = W.config("nacl_512", n=33002, box=144.2)
+    over = dict(r_shell=47.0, skin=1.0, p_r=20)
+    ctx = _system(cfg, R.FP64, **over)
+    f, g, _ = _forces(ctx)
+    assert np.abs(f - g).max() <= 1e-12 * np.abs(f).max()
+    short = ctx.rbsog_get_force_parts()[0].cpu().numpy()
+    sel = np.sort(np.random.default_rng(1).choice(len(f), 100, replace=False)).astype(np.int32)
+    fo = O.System(dict(cfg["sys"], p_f=20, **over), cfg["types"], cfg["pos"], cfg["vel"]).forces_short_atoms(3, sel)
+    check_forces(short[sel], fo, 1e-11, "short-range force")
