@@ -327,15 +327,17 @@ typedef struct {
 } rbsog_tuning;
 
 /* Choose the launch shapes by timing from the current state (HIP events on
- * the context's stream): the k-space force workgroup alone, then every
- * combination of pair_block, pair_ku, rho_mpl and kf_aux on whole steps
- * (both streams, graphs if enabled), max(reps, 3) steps per candidate from
- * one saved device state, best of three alternating rounds; the chosen
- * shapes are returned in `chosen` (may be NULL).  Restores the saved state
- * (positions, velocities, forces, lists, counters, modes and structure
- * factors), so the trajectory that
- * follows is bit for bit the one without tuning; holds a second copy of the
- * atom, list and mode arrays while it runs.  Synchronises. */
+ * the context's stream, both streams, graphs if enabled): every combination of
+ * pair_block, pair_ku, rho_mpl and kf_aux that makes a difference to the
+ * present system on max(reps, 3) whole steps from one saved device state, best
+ * of two alternating rounds, then kf_block with the fastest of them.  The three
+ * fastest shapes then run against the present ones in five alternating rounds,
+ * over a scheduled rebuild if rebuild_every is at most 10, and one replaces
+ * them only if it was faster in all five.  The shapes in use afterwards are
+ * returned in `chosen` (may be NULL).  Restores the saved state (positions,
+ * velocities, forces, lists, counters, modes and structure factors), so the
+ * trajectory that follows is bit for bit the one without tuning; holds a second
+ * copy of the atom, list and mode arrays while it runs.  Synchronises. */
 rbsog_status rbsog_autotune(rbsog_ctx* ctx, int32_t reps, rbsog_tuning* chosen);
 /* Set or read the shapes directly (values outside the lists: RBSOG_E_ARG). */
 rbsog_status rbsog_set_tuning(rbsog_ctx* ctx, const rbsog_tuning* t);

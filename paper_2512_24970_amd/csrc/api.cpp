@@ -824,10 +824,9 @@ double time_ms(rbsog_ctx* c, int reps, const std::function<void()>& f)
 }
 
 // Time each kernel under its candidate launch shapes at the current positions
-// and keep the fastest.  What is timed overwrites the forces (the k-space force
-// alone is written where the total is kept) and moves the atoms, so the state
-// and the exported k-space data are saved first and put back: tuning leaves the
-// trajectory bit for bit as it was.
+// and keep the fastest.  The timed steps move the atoms and form forces there, so
+// the state and the exported k-space data are saved first and put back: tuning
+// leaves the trajectory bit for bit as it was.
 void autotune(rbsog_ctx* c, int reps)
 {
     const bool was_profiling = c->profiling;
@@ -852,7 +851,8 @@ void autotune(rbsog_ctx* c, int reps)
         }
     };
     copy_state(true);
-    Tuning best = c->plan.tune;
+    const Tuning now = c->plan.tune;
+    Tuning best = now;
     auto try_shape = [&](Tuning t) {
         c->plan.tune = t;
         plan_launches(c);
@@ -863,29 +863,46 @@ void autotune(rbsog_ctx* c, int reps)
     // and where the k-space force runs are chosen together on whole steps
     // (timed on back-to-back force evaluations, larger pair workgroups look
     // faster and still lengthen the step).  Every candidate runs the same
-    // steps from the saved state.  Alternating rounds, best of three.
+    // steps from the saved state.  Alternating rounds, best of two.
+    const int every = c->prm[0].rebuild_every;
     const int n_steps = std::max(reps, 3);
     struct Cand {
         Tuning t;
         double ms;
     };
+    // `steps` steps, the last with a scheduled rebuild if asked; time_ms runs
+    // them once untimed first (which also captures the step graphs when graphs
+    // are on), then once timed
+    auto time_steps = [&](const Tuning& t, int steps, bool rebuild) {
+        try_shape(t);
+        copy_state(false);
+        return time_ms(c, 1, [&] {
+            for (int k = 0; k < steps; ++k) launch_step(c, rebuild && k == steps - 1, false);
+        });
+    };
     auto search = [&](std::vector<Cand>& cs) {
-        for (int round = 0; round < 3; ++round)
-            for (Cand& cd : cs) {
-                try_shape(cd.t);
-                copy_state(false);
-                // time_ms runs the steps once untimed first (which also
-                // captures the step graph when graphs are on), then once timed
-                cd.ms = std::min(cd.ms, time_ms(c, 1, [&] {
-                    for (int k = 0; k < n_steps; ++k) launch_step(c, false, false);
-                }));
-            }
-        double t_best = 1e300;
-        for (const Cand& cd : cs)
-            if (cd.ms < t_best) {
-                t_best = cd.ms;
-                best = cd.t;
-            }
+        for (int round = 0; round < 2; ++round)
+            for (Cand& cd : cs) cd.ms = std::min(cd.ms, time_steps(cd.t, n_steps, false));
+        std::sort(cs.begin(), cs.end(), [](const Cand& x, const Cand& y) { return x.ms < y.ms; });
+    };
+    // What a shape launches: values that the present system gives no meaning
+    // (a small system's pair kernel and k-space force have shapes of their own,
+    // one stream has no place to choose) stay as they are.
+    const bool pair_fixed = c->plan.pair_lanes > 1, aux_fixed = !forked(c);
+    const bool kf_fixed = std::any_of(c->hk.begin(), c->hk.end(), [](const KDev& k) { return 64 * k.kf_waves >= 256; });
+    auto add = [&](std::vector<Cand>& cs, Tuning t) {
+        if (pair_fixed) t.pair_block = now.pair_block, t.pair_ku = now.pair_ku;
+        if (aux_fixed) t.kf_aux = now.kf_aux;
+        if (kf_fixed) t.kf_block = now.kf_block;
+        if (!pair_fixed && fit_pair_block(c->plan, c->mixed, t.pair_block) != t.pair_block) return;
+        auto same = [&](const Tuning& u) {
+            return u.pair_block == t.pair_block && u.pair_ku == t.pair_ku && u.rho_mpl == t.rho_mpl &&
+                   u.kf_block == t.kf_block && u.kf_aux == t.kf_aux;
+        };
+        if (same(now)) return;
+        for (const Cand& x : cs)
+            if (same(x.t)) return;
+        cs.push_back(Cand{t, 1e300});
     };
     auto restore = [&] {
         try_shape(best);
@@ -894,47 +911,45 @@ void autotune(rbsog_ctx* c, int reps)
         c->forces_valid = true;
     };
     try {
-        try_shape(best);
-        launch_rho(c->plan, c->mixed, st);
-        launch_rho_finalize(c->plan, false, st);
-        launch_pair(c->plan, c->mixed, false, st);
-        launch_finalize(c->plan, false, false, false, st);
-        // a first pick of the k-space force workgroup size, the kernel alone
-        // (refined on whole steps below)
-        double tb = 1e300;
-        for (int bs : {64, 128, 256}) {
-            Tuning t = best;
-            t.kf_block = bs;
-            try_shape(t);
-            const double ms = time_ms(c, reps, [&] { launch_kforce(c->plan, c->mixed, st); });
-            if (ms < tb) {
-                tb = ms;
-                best.kf_block = bs;
-            }
-        }
         std::vector<Cand> cands;
         for (int bs : {64, 128, 256})
             for (int ku : {4, 8})
                 for (int mpl : {1, 2})
-                    for (int aux : {1, 0}) {
-                        Tuning t = best;
-                        t.pair_block = bs;
-                        t.pair_ku = ku;
-                        t.rho_mpl = mpl;
-                        t.kf_aux = aux;
-                        cands.push_back(Cand{t, 1e300});
-                    }
+                    for (int aux : {1, 0}) add(cands, Tuning{bs, ku, mpl, now.kf_block, aux});
         search(cands);
-        // then the k-space force workgroup again, on whole steps with the
-        // shapes just chosen (alone it ranks sizes that run beside the pair
-        // kernel differently)
+        // then the k-space force workgroup with the shapes just chosen
         std::vector<Cand> kf;
         for (int bs : {64, 128, 256}) {
-            Tuning t = best;
+            Tuning t = cands.empty() ? now : cands[0].t;
             t.kf_block = bs;
-            kf.push_back(Cand{t, 1e300});
+            add(kf, t);
         }
         search(kf);
+        cands.insert(cands.end(), kf.begin(), kf.end());
+        std::sort(cands.begin(), cands.end(), [](const Cand& x, const Cand& y) { return x.ms < y.ms; });
+        // The smallest of some twenty noisy times need not be the fastest
+        // shape: the three fastest run against the present shapes for five more
+        // rounds, over a rebuild where steps schedule one often enough, and one
+        // replaces them only if it was faster in every round.
+        const int final_steps = every <= 10 ? std::max(every, n_steps) : n_steps;
+        const size_t n_final = std::min<size_t>(3, cands.size());
+        std::vector<int> wins(n_final, 0);
+        std::vector<double> sum(n_final, 0.0);
+        constexpr int kRounds = 5;
+        for (int round = 0; round < kRounds && n_final > 0; ++round) {
+            const double ref = time_steps(now, final_steps, every <= 10);
+            for (size_t q = 0; q < n_final; ++q) {
+                const double ms = time_steps(cands[q].t, final_steps, every <= 10);
+                wins[q] += ms < ref ? 1 : 0;
+                sum[q] += ms;
+            }
+        }
+        double least = 1e300;
+        for (size_t q = 0; q < n_final; ++q)
+            if (wins[q] == kRounds && sum[q] < least) {
+                least = sum[q];
+                best = cands[q].t;
+            }
     } catch (...) {
         // put the saved state back before reporting the failure
         try {

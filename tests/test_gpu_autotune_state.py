@@ -45,3 +45,26 @@ def test_tuning_leaves_the_state(n, moved, precision):
     for x, y in zip(a, b):
         np.testing.assert_array_equal(x, y)
     assert ea["u_total"] == eb["u_total"] and ea["kinetic"] == eb["kinetic"]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("n,p_f,fixed", [(512, 100, ("pair_block", "pair_ku", "kf_block", "kf_aux")),
+                                         (100002, 20, ("kf_aux",))])
+def test_tuning_keeps_values_without_effect(n, p_f, fixed, precision):
+    """Several lanes an atom and shared modes have launch shapes of their own,
+    and one stream (up to 131072 ions) has no place of the k-space force to
+    choose: whatever the tuner times, those values stay as they were set."""
+    import torch
+    print(f"case: values without effect n {n} {precision}", flush=True)
+    cfg = W.config("nacl_512", n=n, box=(n / 0.0319) ** (1 / 3), melt_seed=7)
+    dev = torch.device("cuda", 0)
+    ctx = R.Context(0)
+    ctx.rbsog_set_system(R.make_params(dict(cfg["sys"], p_f=p_f), R.FP64 if precision == "fp64" else R.MIXED, n_atoms=n),
+                         *(torch.as_tensor(cfg[k], device=dev) for k in ("types", "pos", "vel")))
+    for over in (dict(pair_block=256, pair_ku=8, kf_block=64, kf_aux=0),
+                 dict(pair_block=128, pair_ku=4, kf_block=128, kf_aux=1)):
+        ctx.rbsog_set_tuning(**over)
+        got = ctx.rbsog_autotune(1)
+        assert got == ctx.rbsog_get_tuning()
+        for key in fixed:
+            assert got[key] == over[key], (key, got)
