@@ -199,6 +199,14 @@ rbsog_status rbsog_sog_params(double eps, double r_shell, double* b, double* s, 
 rbsog_status rbsog_near_table(double eps, double r_shell, float* coef, int32_t cap, int32_t* e0,
                               int32_t* n_intervals);
 
+/* The FP64 form's near-field table of the same kernels: 32 intervals per binade
+ * (interval index = exponent and five leading mantissa bits of s), per interval
+ * sixteen doubles, the degree-7 coefficients (ascending powers of t = s - the
+ * interval's midpoint) of CF and of CU.  Otherwise as rbsog_near_table, with
+ * cap >= 16 * n_intervals doubles. */
+rbsog_status rbsog_near_table64(double eps, double r_shell, double* coef, int32_t cap, int32_t* e0,
+                                int32_t* n_intervals);
+
 /* Create a context on HIP device `hip_device`, enqueueing on `hip_stream`
  * (a hipStream_t; NULL = the default stream).  Every call's device work is
  * ordered on that stream: work the library puts on its own second stream is

@@ -1600,6 +1600,33 @@ rbsog_status rbsog_near_table(double eps, double r_shell, float* coef, int32_t c
     }
 }
 
+rbsog_status rbsog_near_table64(double eps, double r_shell, double* coef, int32_t cap, int32_t* e0,
+                                int32_t* n_intervals)
+{
+    try {
+        if (!(r_shell > 0.0)) return RBSOG_E_ARG;
+        SogSplit sp;
+        SogCoef c;
+        std::string err;
+        int chain = 1;
+        if (!sog_split(eps, r_shell, &sp, &err)) return RBSOG_E_ARG;
+        sog_base(eps > 0.0 ? eps : 1e-5, &chain);
+        if (!sog_kernel_coef(sp, chain, r_shell, false, &c, &err)) return RBSOG_E_ARG;
+        NearTable64 nt;
+        build_near_table64(c, r_shell, &nt);
+        const int n = nt.nbin << kNearBits64;
+        if (e0) *e0 = nt.e0;
+        if (n_intervals) *n_intervals = n;
+        if (coef) {
+            if (cap < 16 * n) return RBSOG_E_ARG;
+            std::memcpy(coef, nt.coef.data(), sizeof(double) * nt.coef.size());
+        }
+        return RBSOG_OK;
+    } catch (...) {
+        return RBSOG_E_ARG;
+    }
+}
+
 rbsog_status rbsog_create(rbsog_ctx** out, int hip_device, void* hip_stream)
 {
     if (!out) return RBSOG_E_ARG;

@@ -83,6 +83,8 @@ ABI = {
     "rbsog_create": (C.c_int, [C.POINTER(C.c_void_p), C.c_int, C.c_void_p]),
     "rbsog_near_table": (C.c_int, [C.c_double, C.c_double, C.c_void_p, C.c_int32, C.POINTER(C.c_int32),
                                    C.POINTER(C.c_int32)]),
+    "rbsog_near_table64": (C.c_int, [C.c_double, C.c_double, C.c_void_p, C.c_int32, C.POINTER(C.c_int32),
+                                     C.POINTER(C.c_int32)]),
     "rbsog_destroy": (C.c_int, [C.c_void_p]),
     "rbsog_last_error": (C.c_char_p, [C.c_void_p]),
     "rbsog_set_system": (C.c_int, [C.c_void_p, C.POINTER(Params), C.c_void_p, C.c_void_p, C.c_void_p, C.c_int]),
@@ -186,17 +188,27 @@ def make_params(sysp: dict, precision: int = FP64, n_atoms: int | None = None) -
     return p
 
 
+def _near_table(name: str, eps: float, r_shell: float, width: int, dtype) -> dict:
+    fn = getattr(lib(), name)
+    e0, n = C.c_int32(), C.c_int32()
+    rc = fn(eps, r_shell, None, 0, C.byref(e0), C.byref(n))
+    if rc != 0:
+        raise RbsogError(rc, f"{name} failed")
+    coef = np.zeros((max(n.value, 1), width), dtype)
+    rc = fn(eps, r_shell, _np_ptr(coef), coef.size, C.byref(e0), C.byref(n))
+    if rc != 0:
+        raise RbsogError(rc, f"{name} failed")
+    return {"e0": e0.value, "coef": coef[: n.value]}
+
+
 def rbsog_near_table(eps: float, r_shell: float) -> dict:
     """The mixed form's FP32 near-field table: e0, coef[n_intervals][8]."""
-    e0, n = C.c_int32(), C.c_int32()
-    rc = lib().rbsog_near_table(eps, r_shell, None, 0, C.byref(e0), C.byref(n))
-    if rc != 0:
-        raise RbsogError(rc, "rbsog_near_table failed")
-    coef = np.zeros((max(n.value, 1), 8), np.float32)
-    rc = lib().rbsog_near_table(eps, r_shell, _np_ptr(coef), coef.size, C.byref(e0), C.byref(n))
-    if rc != 0:
-        raise RbsogError(rc, "rbsog_near_table failed")
-    return {"e0": e0.value, "coef": coef[: n.value]}
+    return _near_table("rbsog_near_table", eps, r_shell, 8, np.float32)
+
+
+def rbsog_near_table64(eps: float, r_shell: float) -> dict:
+    """The FP64 form's near-field table: e0, coef[n_intervals][16]."""
+    return _near_table("rbsog_near_table64", eps, r_shell, 16, np.float64)
 
 
 def rbsog_sog_params(eps: float, r_shell: float) -> dict:
