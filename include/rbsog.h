@@ -317,9 +317,11 @@ rbsog_status rbsog_set_list_capacity(rbsog_ctx* ctx, int32_t cap_core, int32_t c
 rbsog_status rbsog_set_list_chunks(rbsog_ctx* ctx, int32_t chunks);
 
 /* Launch shapes of the hot kernels and the stream of the k-space force; a set
- * chooses them from the form and the number of atoms.  No choice changes a result bit: partial sums are taken per 64-atom wavefront
- * and every structure factor is summed over the atoms in the same order
- * whatever the shape. */
+ * chooses them from the form, the number of atoms and the modes.  A value that
+ * has no effect on the present system is kept and returned all the same.  No
+ * choice changes a result bit: partial sums are taken per 64-atom wavefront and
+ * every structure factor is summed over the atoms in the same order whatever
+ * the shape. */
 typedef struct {
     int32_t pair_block; /* atoms per workgroup of the pair kernel: 64, 128, 256 (fewer where its
                            tables and draw masks do not fit in 160 KB of LDS; small systems: 64,
@@ -331,7 +333,7 @@ typedef struct {
                            small system takes more (its modes are split over wavefronts) */
     int32_t kf_aux;     /* 1: the k-space force follows rho on the second stream, beside the pair
                            kernel; 0: it runs after the pair kernel on the context's stream (1;
-                           small systems launched kernel by kernel use one stream) */
+                           with energies always after it; small systems use one stream) */
 } rbsog_tuning;
 
 /* Choose the launch shapes by timing from the current state (HIP events on

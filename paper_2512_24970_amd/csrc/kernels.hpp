@@ -202,7 +202,8 @@ inline int pair_lanes_for(size_t atom_waves, bool mixed)
 }
 
 // Split of the k-space force's modes (FP64 form, and the mixed form's sums of
-// more modes than kKfChainModes, which only the full sum has).  Slices double
+// more modes than kKfChainModes: a full sum's, or that many drawn; fewer keep
+// the order of one wavefront).  Slices double
 // while the system's wavefronts would leave SIMDs with fewer than four and a
 // slice keeps at least 24 modes (a slice's own set-up is worth a few modes);
 // groups on top, for the full sum of a small system, until about eight
